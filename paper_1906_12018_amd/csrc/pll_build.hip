@@ -322,8 +322,9 @@ __global__ void k_batch_prep(DevCounters* ctr) {
     }
 }
 
+template <bool PLANES>
 __global__ void __launch_bounds__(kBlock) k_batch_init(BuildArgs A, uint32_t ib, uint32_t bs, uint32_t bstamp) {
-    pll::phase_batch_init(A, grid_exec(A), ib, bs, bstamp);
+    pll::phase_batch_init<PLANES>(A, grid_exec(A), ib, bs, bstamp);
 }
 
 __global__ void __launch_bounds__(kBlock) k_push(BuildArgs A, uint32_t ib, uint32_t p, uint32_t nact, uint32_t rstamp,
@@ -346,18 +347,22 @@ __global__ void __launch_bounds__(kBlock) k_check(BuildArgs A, uint32_t ib, uint
     block_add_stats<7>(A.ctr, v, which);
 }
 
+// The table a fused round's scans read.  kScanPlanes: the bit planes (rounds
+// j <= PLL_PLANES + 1 of a build that keeps them); kScanSmall: the byte table
+// with every prune threshold at most pll::kSmallT (j <= kSmallT), so the
+// scans take the cheaper byte compare; kScanBytes: the byte table with any
+// threshold.  The packed check is not instantiated with kScanBytes.
+enum { kScanBytes, kScanSmall, kScanPlanes };
+
 // Round j's check fused with round j+1's push (NextRound in pll_phases.h).
-// SMALLT: every prune threshold of round j is at most pll::kSmallT (j <= kSmallT),
-// so the scans take the cheaper byte compare.  The packed check is only
-// instantiated with it.
-template <int WM, bool BP, bool PACK = false, bool SMALLT = false>
+template <int WM, bool BP, bool PACK = false, int SCAN = kScanBytes>
 __device__ inline void check_push_body(const BuildArgs& A, const pll::Exec& X, uint32_t ib, uint32_t bs, uint32_t j,
                                        const pll::NextRound& nr, uint32_t relaxed) {
     PhaseStats st;
     if (PACK && !BP)
-        pll::phase_check4<WM, SMALLT>(A, X, ib, bs, j, relaxed != 0, st, nr);
+        pll::phase_check4<WM, SCAN == kScanSmall, SCAN == kScanPlanes>(A, X, ib, bs, j, relaxed != 0, st, nr);
     else
-        pll::phase_check<WM, BP, true, false, SMALLT && !BP>(A, X, ib, bs, j, nr.rin, relaxed != 0, st, &nr);
+        pll::phase_check<WM, BP, true, false, SCAN == kScanSmall && !BP, SCAN == kScanPlanes>(A, X, ib, bs, j, nr.rin, relaxed != 0, st, &nr);
     const unsigned long long v[9] = {st.cand,     st.acc, st.read,  st.table,          st.cost_pos,
                                      st.cost_neg, st.bp,  st.edges + st.pulled, st.edges};
     const int which[9] = {PLL_ST_CAND,     PLL_ST_ACC, PLL_ST_READ,  PLL_ST_TABLE,      PLL_ST_COST_POS,
@@ -366,10 +371,10 @@ __device__ inline void check_push_body(const BuildArgs& A, const pll::Exec& X, u
 }
 
 // at most 128 VGPRs, i.e. 4 waves per SIMD, like the unfused check
-template <int WM, bool PACK, bool SMALLT>
+template <int WM, bool PACK, int SCAN>
 __global__ void __launch_bounds__(kBlock, 4) k_check_push(BuildArgs A, uint32_t ib, uint32_t bs, uint32_t j,
                                                           pll::NextRound nr, uint32_t relaxed) {
-    check_push_body<WM, false, PACK, SMALLT>(A, grid_exec(A), ib, bs, j, nr, relaxed);
+    check_push_body<WM, false, PACK, SCAN>(A, grid_exec(A), ib, bs, j, nr, relaxed);
 }
 
 // The blocks [b0, b0 + nb) of the grid run a phase on their own: queue
@@ -389,21 +394,21 @@ __device__ inline pll::Exec side_exec(const BuildArgs& A, uint32_t b0, uint32_t 
 
 // Directed graphs: both sides' fused rounds in one launch, blocks [0, nb0)
 // on the forward side and the rest on the backward side.
-template <int WM, bool SMALLT>
+template <int WM, int SCAN>
 __global__ void __launch_bounds__(kBlock, 4) k_check_push2(BuildArgs A0, pll::NextRound nr0, BuildArgs A1,
                                                            pll::NextRound nr1, uint32_t ib, uint32_t bs, uint32_t j,
                                                            uint32_t nb0) {
     if (blockIdx.x < nb0)
-        check_push_body<WM, false, false, SMALLT>(A0, side_exec(A0, 0, nb0), ib, bs, j, nr0, 0);
+        check_push_body<WM, false, false, SCAN>(A0, side_exec(A0, 0, nb0), ib, bs, j, nr0, 0);
     else
-        check_push_body<WM, false, false, SMALLT>(A1, side_exec(A1, nb0, gridDim.x - nb0), ib, bs, j, nr1, 0);
+        check_push_body<WM, false, false, SCAN>(A1, side_exec(A1, nb0, gridDim.x - nb0), ib, bs, j, nr1, 0);
 }
 
 // with bit-parallel labels (no register cap: it would spill)
-template <int WM>
+template <int WM, int SCAN>
 __global__ void __launch_bounds__(kBlock) k_check_push_bp(BuildArgs A, uint32_t ib, uint32_t bs, uint32_t j,
                                                           pll::NextRound nr, uint32_t relaxed) {
-    check_push_body<WM, true>(A, grid_exec(A), ib, bs, j, nr, relaxed);
+    check_push_body<WM, true, false, SCAN>(A, grid_exec(A), ib, bs, j, nr, relaxed);
 }
 
 // Pulled rounds: the (vertex, segment) items, once per build, and a round.
@@ -492,6 +497,7 @@ __global__ void k_check_weights(uint64_t nnz, const uint8_t* w, DevCounters* ctr
 
 // With `prep` set it also does k_batch_prep's reset for the next batch (the
 // batch end, which reads the touched counts, has finished by then).
+template <bool PLANES>
 __global__ void __launch_bounds__(kBlock) k_clear_table(BuildArgs A, uint32_t ib, uint32_t bs, DevCounters* prep) {
     if (prep && blockIdx.x == 0 && threadIdx.x < PLL_SHARDS) {
         Shard& sh = prep->sh[threadIdx.x];
@@ -499,7 +505,11 @@ __global__ void __launch_bounds__(kBlock) k_clear_table(BuildArgs A, uint32_t ib
         sh.hq[0] = sh.hq[1] = 0;
         sh.touched = 0;
     }
-    pll::phase_clear_table(A, grid_exec(A), ib, bs);
+    pll::phase_clear_table<PLANES>(A, grid_exec(A), ib, bs);
+}
+
+__global__ void __launch_bounds__(kBlock) k_table_fill(BuildArgs A, uint32_t ib, uint32_t bs) {
+    pll::phase_table_fill(A, grid_exec(A), ib, bs);
 }
 
 // ---- bit-parallel labels (Section 5.2) ------------------------------------------------------------
@@ -988,35 +998,43 @@ void dispatch_check(uint32_t blocks, hipStream_t s, const BuildArgs& A, uint32_t
 template <int WM>
 void launch_check_push(uint32_t blocks, hipStream_t s, const BuildArgs& A, uint32_t ib, uint32_t bs, uint32_t j,
                        const pll::NextRound& nr, uint32_t relaxed, bool pack) {
-    if (A.bp_t)
-        k_check_push_bp<WM><<<blocks, kBlock, 0, s>>>(A, ib, bs, j, nr, relaxed);
+    if (A.bp_t && A.P)
+        k_check_push_bp<WM, kScanPlanes><<<blocks, kBlock, 0, s>>>(A, ib, bs, j, nr, relaxed);
+    else if (A.bp_t)
+        k_check_push_bp<WM, kScanBytes><<<blocks, kBlock, 0, s>>>(A, ib, bs, j, nr, relaxed);
+    else if (A.P && pack)
+        k_check_push<WM, true, kScanPlanes><<<blocks, kBlock, 0, s>>>(A, ib, bs, j, nr, relaxed);
+    else if (A.P)
+        k_check_push<WM, false, kScanPlanes><<<blocks, kBlock, 0, s>>>(A, ib, bs, j, nr, relaxed);
     else if (pack)  // only in rounds j <= kSmallT
-        k_check_push<WM, true, true><<<blocks, kBlock, 0, s>>>(A, ib, bs, j, nr, relaxed);
+        k_check_push<WM, true, kScanSmall><<<blocks, kBlock, 0, s>>>(A, ib, bs, j, nr, relaxed);
     else if (j <= pll::kSmallT)
-        k_check_push<WM, false, true><<<blocks, kBlock, 0, s>>>(A, ib, bs, j, nr, relaxed);
+        k_check_push<WM, false, kScanSmall><<<blocks, kBlock, 0, s>>>(A, ib, bs, j, nr, relaxed);
     else
-        k_check_push<WM, false, false><<<blocks, kBlock, 0, s>>>(A, ib, bs, j, nr, relaxed);
+        k_check_push<WM, false, kScanBytes><<<blocks, kBlock, 0, s>>>(A, ib, bs, j, nr, relaxed);
 }
 
-template <bool SMALLT>
+template <int SCAN>
 void launch_check_push2(uint32_t nb0, uint32_t nb1, hipStream_t s, const BuildArgs& A0, const pll::NextRound& nr0,
                         const BuildArgs& A1, const pll::NextRound& nr1, uint32_t ib, uint32_t bs, uint32_t j) {
     const uint32_t g = nb0 + nb1;
     switch (words_class(A0.W)) {
-        case 1: k_check_push2<1, SMALLT><<<g, kBlock, 0, s>>>(A0, nr0, A1, nr1, ib, bs, j, nb0); break;
-        case 2: k_check_push2<2, SMALLT><<<g, kBlock, 0, s>>>(A0, nr0, A1, nr1, ib, bs, j, nb0); break;
-        case 4: k_check_push2<4, SMALLT><<<g, kBlock, 0, s>>>(A0, nr0, A1, nr1, ib, bs, j, nb0); break;
-        case 8: k_check_push2<8, SMALLT><<<g, kBlock, 0, s>>>(A0, nr0, A1, nr1, ib, bs, j, nb0); break;
-        default: k_check_push2<16, SMALLT><<<g, kBlock, 0, s>>>(A0, nr0, A1, nr1, ib, bs, j, nb0); break;
+        case 1: k_check_push2<1, SCAN><<<g, kBlock, 0, s>>>(A0, nr0, A1, nr1, ib, bs, j, nb0); break;
+        case 2: k_check_push2<2, SCAN><<<g, kBlock, 0, s>>>(A0, nr0, A1, nr1, ib, bs, j, nb0); break;
+        case 4: k_check_push2<4, SCAN><<<g, kBlock, 0, s>>>(A0, nr0, A1, nr1, ib, bs, j, nb0); break;
+        case 8: k_check_push2<8, SCAN><<<g, kBlock, 0, s>>>(A0, nr0, A1, nr1, ib, bs, j, nb0); break;
+        default: k_check_push2<16, SCAN><<<g, kBlock, 0, s>>>(A0, nr0, A1, nr1, ib, bs, j, nb0); break;
     }
 }
 
 void dispatch_check_push2(uint32_t nb0, uint32_t nb1, hipStream_t s, const BuildArgs& A0, const pll::NextRound& nr0,
                           const BuildArgs& A1, const pll::NextRound& nr1, uint32_t ib, uint32_t bs, uint32_t j) {
-    if (j <= pll::kSmallT)
-        launch_check_push2<true>(nb0, nb1, s, A0, nr0, A1, nr1, ib, bs, j);
+    if (A0.P)
+        launch_check_push2<kScanPlanes>(nb0, nb1, s, A0, nr0, A1, nr1, ib, bs, j);
+    else if (j <= pll::kSmallT)
+        launch_check_push2<kScanSmall>(nb0, nb1, s, A0, nr0, A1, nr1, ib, bs, j);
     else
-        launch_check_push2<false>(nb0, nb1, s, A0, nr0, A1, nr1, ib, bs, j);
+        launch_check_push2<kScanBytes>(nb0, nb1, s, A0, nr0, A1, nr1, ib, bs, j);
 }
 
 void dispatch_check_push(uint32_t blocks, hipStream_t s, const BuildArgs& A, uint32_t ib, uint32_t bs, uint32_t j,
@@ -1193,11 +1211,13 @@ int prepare_rank_csr(DevAllocs& M, DevCounters* ctr, DevCounters* h, uint32_t n,
 
 // Working buffers of the batch phases over the rank-space CSR (rrow, rcol);
 // the pruning checks read the build's own table until the caller says
-// otherwise.  The row masks of the first hot_rows table rows stay all ones.
+// otherwise.  With `planes` the table is kept as bit planes (BuildArgs::P)
+// and the byte table T stays null until planes_to_bytes.  The row masks of
+// the first hot_rows table rows stay all ones.
 // Returns the spare offsets array of the arena relayout.
 int init_state(DevAllocs& M, BuildArgs& A, uint32_t n, uint64_t nnz, uint32_t W, const uint64_t* rrow,
                const uint32_t* rcol, DevCounters* ctr, hipStream_t s, uint64_t** spare_off,
-               uint32_t hot_rows = kHotRows) {
+               bool planes, uint32_t hot_rows = kHotRows) {
     A = BuildArgs{};
     A.n = n;
     A.W = W;
@@ -1210,9 +1230,14 @@ int init_state(DevAllocs& M, BuildArgs& A, uint32_t n, uint64_t nnz, uint32_t W,
     A.lcap = M.get<uint32_t>(n);
     A.C = M.get<uint64_t>((size_t)n * W);
     A.msgs = M.get<uint64_t>((size_t)n * W);
-    A.T = M.get<uint8_t>((size_t)n * A.bstride);
+    static_assert(PLL_PLANES == 8, "the planes of a row take the bytes of a byte-table row");
+    if (planes)
+        A.P = M.get<uint64_t>((size_t)n * PLL_PLANES * W);
+    else
+        A.T = M.get<uint8_t>((size_t)n * A.bstride);
     A.rowmask = M.get<uint64_t>(n);
     A.Tchk = A.T;
+    A.Pchk = A.P;
     A.rmchk = A.rowmask;
     A.hq_seg = 2 * (nnz / pll::kHeavyItem) + 64;
     for (int q = 0; q < 2; ++q) {
@@ -1230,13 +1255,54 @@ int init_state(DevAllocs& M, BuildArgs& A, uint32_t n, uint64_t nnz, uint32_t W,
     TRY_HIP(hipMemsetAsync(A.llen, 0, sizeof(uint32_t) * n, s));
     TRY_HIP(hipMemsetAsync(A.C, 0, sizeof(uint64_t) * n * W, s));
     TRY_HIP(hipMemsetAsync(A.msgs, 0, sizeof(uint64_t) * n * W, s));
-    TRY_HIP(hipMemsetAsync(A.T, 0xFF, (size_t)n * A.bstride, s));
+    if (planes)
+        TRY_HIP(hipMemsetAsync(A.P, 0, (size_t)n * A.bstride, s));
+    else
+        TRY_HIP(hipMemsetAsync(A.T, 0xFF, (size_t)n * A.bstride, s));
     A.hot = std::min<uint32_t>(n, hot_rows);
     TRY_HIP(hipMemsetAsync(A.rowmask, 0xFF, sizeof(uint64_t) * A.hot, s));
     TRY_HIP(hipMemsetAsync(A.rowmask + A.hot, 0, sizeof(uint64_t) * (n - A.hot), s));
     TRY_HIP(hipMemsetAsync(A.recv_stamp, 0, sizeof(uint32_t) * n, s));
     TRY_HIP(hipMemsetAsync(A.touch_stamp, 0, sizeof(uint32_t) * n, s));
     return PLL_OK;
+}
+
+// A round past PLL_PLANES + 1 needs thresholds the planes do not hold: the
+// build goes on with the byte table, filled from the labels the batch's
+// roots hold now, for the rest of this batch and all later ones (a graph
+// that gets here once has long distances, and mostly would in every batch).
+// The planes' memory becomes the table's where nothing can be allocated.
+// The stream has drained.  The caller points Tchk at the table to check.
+int planes_to_bytes(DevAllocs& M, BuildArgs& A, uint32_t ib, uint32_t bs, hipStream_t s) {
+    const size_t bytes = (size_t)A.n * A.bstride;
+    if (M.fixed) {
+        A.T = reinterpret_cast<uint8_t*>(A.P);
+    } else {
+        M.drop(A.P);
+        A.T = M.get<uint8_t>(bytes);
+        if (M.err != hipSuccess) return status_of(M.err);
+    }
+    A.P = nullptr;
+    A.Pchk = nullptr;
+    A.Tchk = A.T;
+    TRY_HIP(hipMemsetAsync(A.T, 0xFF, bytes, s));
+    k_table_fill<<<blocks_for_waves(bs), kBlock, 0, s>>>(A, ib, bs);
+    TRY_HIP(hipGetLastError());
+    return PLL_OK;
+}
+
+void launch_batch_init(const BuildArgs& A, uint32_t ib, uint32_t bs, uint32_t bstamp, hipStream_t s) {
+    if (A.P)
+        k_batch_init<true><<<blocks_for_waves(bs), kBlock, 0, s>>>(A, ib, bs, bstamp);
+    else
+        k_batch_init<false><<<blocks_for_waves(bs), kBlock, 0, s>>>(A, ib, bs, bstamp);
+}
+
+void launch_clear_table(const BuildArgs& A, uint32_t ib, uint32_t bs, DevCounters* prep, hipStream_t s) {
+    if (A.P)
+        k_clear_table<true><<<blocks_for_waves(4ull * bs), kBlock, 0, s>>>(A, ib, bs, prep);
+    else
+        k_clear_table<false><<<blocks_for_waves(4ull * bs), kBlock, 0, s>>>(A, ib, bs, prep);
 }
 
 // Final label CSR of one build, by vertex id with hubs as ranks (a8):
@@ -1348,7 +1414,10 @@ int build_attempt(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, const uint3
     uint64_t* spare_off = nullptr;
     // bit-parallel roots take the top-ranked vertices out of the labels, which
     // leaves the top rows sparse: their masks are kept exact then
-    rc = init_state(M, A, n, nnz, W, RC.rrow, RC.rcol, ctr, s, &spare_off, bp_req ? 0u : kHotRows);
+    // the persistent loop and the recheck (testing: the byte table is their
+    // only form) keep the byte table throughout
+    const bool planes = !(flags & (PLL_FLAG_PERSISTENT | PLL_FLAG_RECHECK | PLL_FLAG_RELAXED));
+    rc = init_state(M, A, n, nnz, W, RC.rrow, RC.rcol, ctr, s, &spare_off, planes, bp_req ? 0u : kHotRows);
     if (rc) return rc;
     // the round-2 neighbour check needs every higher-ranked neighbour to be a
     // hub, which bit-parallel roots (taken out of the labels) break
@@ -1481,7 +1550,7 @@ int build_attempt(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, const uint3
         // table clear
         if (ib == 0) k_batch_prep<<<1, 64, 0, s>>>(ctr);
         if (A.bp_t) k_bp_batch_stage<<<blocks_for_threads((uint64_t)A.bp_t * bs), kBlock, 0, s>>>(A, ib, bs);
-        k_batch_init<<<blocks_for_waves(bs), kBlock, 0, s>>>(A, ib, bs, bstamp);
+        launch_batch_init(A, ib, bs, bstamp, s);
         P.span(PLL_PHASE_INIT, e0, P.mark(), (A.bp_t ? 2 : 1) + (ib == 0 ? 1 : 0));
         // round 1's push from the batch vertices (active list 0) into
         // receiver queue 0 and message buffer 1; afterwards every round j is
@@ -1499,6 +1568,10 @@ int build_attempt(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, const uint3
         uint64_t next_est = r1_est;
         for (uint32_t j = 1;; ++j) {
             ++rounds;
+            if (A.P && j > PLL_PLANES + 1) {
+                rc = planes_to_bytes(M, A, ib, bs, s);
+                if (rc) return rc;
+            }
             // the first round's receivers push the batch's densest deltas along
             // high-degree rows, so gathering pays off from fewer of them
             const uint32_t pull = pull_ok && next_est * (j == 1 ? kPullFrac1 : kPullFrac) >= n ? 1u : 0u;
@@ -1563,7 +1636,7 @@ int build_attempt(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, const uint3
         }
         hipEvent_t e1 = P.mark();
         dispatch_batch_end(blocks_for_waves(sum_touched(h)), s, A, ib, bs, recheck);
-        k_clear_table<<<blocks_for_waves(4ull * bs), kBlock, 0, s>>>(A, ib, bs, ctr);
+        launch_clear_table(A, ib, bs, ctr, s);
         P.span(PLL_PHASE_END, e1, P.mark(), 2);
         TRY_HIP(hipGetLastError());
         // compact the lists into a larger arena once a bump region is half used
@@ -1684,7 +1757,7 @@ int build_attempt_weighted(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, co
     if (rc) return rc;
     BuildArgs A{};
     uint64_t* spare_off = nullptr;
-    rc = init_state(M, A, n, nnz, W, RC.rrow, RC.rcol, ctr, s, &spare_off);
+    rc = init_state(M, A, n, nnz, W, RC.rrow, RC.rcol, ctr, s, &spare_off, false);
     if (rc) return rc;
     A.rw = RC.rw;
     A.D = M.get<uint8_t>((size_t)n * A.bstride);
@@ -1705,7 +1778,7 @@ int build_attempt_weighted(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, co
         ++batches;
         hipEvent_t e0 = P.mark();
         k_batch_prep<<<1, 64, 0, s>>>(ctr);
-        k_batch_init<<<blocks_for_waves(bs), kBlock, 0, s>>>(A, ib, bs, bstamp);
+        launch_batch_init(A, ib, bs, bstamp, s);
         P.span(PLL_PHASE_INIT, e0, P.mark(), 2);
         uint32_t p = 0, nact = bs;
         uint64_t heavy_waves = 1024;
@@ -1733,7 +1806,7 @@ int build_attempt_weighted(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, co
         }
         hipEvent_t e1 = P.mark();
         dispatch_batch_end_w(blocks_for_waves(sum_touched(h)), s, A, ib, bs);
-        k_clear_table<<<blocks_for_waves(4ull * bs), kBlock, 0, s>>>(A, ib, bs, nullptr);
+        launch_clear_table(A, ib, bs, nullptr, s);
         P.span(PLL_PHASE_END, e1, P.mark(), 2);
         TRY_HIP(hipGetLastError());
         if (!arena_fixed && ib + b < n && max_top(h) * 2 > A.region_cap) {
@@ -1850,12 +1923,14 @@ int build_attempt_directed(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, co
     // side 0: forward (L_in, out-arcs); side 1: backward (L_out, in-arcs)
     BuildArgs A[2];
     uint64_t* spare_off[2] = {nullptr, nullptr};
-    rc = init_state(M, A[0], n, nnz, W, RC.rrow, RC.rcol, ctr, s, &spare_off[0]);
+    const bool planes = !(flags & PLL_FLAG_RECHECK);
+    rc = init_state(M, A[0], n, nnz, W, RC.rrow, RC.rcol, ctr, s, &spare_off[0], planes);
     if (rc) return rc;
-    rc = init_state(M, A[1], n, nnz, W, irow, icol, ctr + 1, s, &spare_off[1]);
+    rc = init_state(M, A[1], n, nnz, W, irow, icol, ctr + 1, s, &spare_off[1], planes);
     if (rc) return rc;
     for (int d = 0; d < 2; ++d) {
         A[d].Tchk = A[d ^ 1].T;
+        A[d].Pchk = A[d ^ 1].P;
         A[d].rmchk = A[d ^ 1].rowmask;
     }
     // second message buffer and receiver list of each side's fused rounds
@@ -1892,7 +1967,7 @@ int build_attempt_directed(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, co
         hipEvent_t e0 = P.mark();
         for (int d = 0; d < 2; ++d) {
             k_batch_prep<<<1, 64, 0, s>>>(A[d].ctr);
-            k_batch_init<<<blocks_for_waves(bs), kBlock, 0, s>>>(A[d], ib, bs, bstamp);
+            launch_batch_init(A[d], ib, bs, bstamp, s);
         }
         P.span(PLL_PHASE_INIT, e0, P.mark(), 4);
         // fused rounds as in the undirected build, both sides in one launch
@@ -1909,6 +1984,13 @@ int build_attempt_directed(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, co
         bool live[2] = {true, true};
         for (uint32_t j = 1; live[0] || live[1]; ++j) {
             ++rounds;
+            if (A[0].P && j > PLL_PLANES + 1) {
+                for (int d = 0; d < 2; ++d) {
+                    rc = planes_to_bytes(M, A[d], ib, bs, s);
+                    if (rc) return rc;
+                }
+                for (int d = 0; d < 2; ++d) A[d].Tchk = A[d ^ 1].T;
+            }
             pll::NextRound nr[2];
             BuildArgs Aj[2];
             uint32_t nb[2] = {0, 0};
@@ -1951,7 +2033,7 @@ int build_attempt_directed(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, co
         // are cleared only after both
         hipEvent_t e1 = P.mark();
         for (int d = 0; d < 2; ++d) dispatch_batch_end(blocks_for_waves(sum_touched(h[d])), s, A[d], ib, bs, recheck);
-        for (int d = 0; d < 2; ++d) k_clear_table<<<blocks_for_waves(4ull * bs), kBlock, 0, s>>>(A[d], ib, bs, nullptr);
+        for (int d = 0; d < 2; ++d) launch_clear_table(A[d], ib, bs, nullptr, s);
         P.span(PLL_PHASE_END, e1, P.mark(), 4);
         TRY_HIP(hipGetLastError());
         for (int d = 0; d < 2; ++d) {

@@ -13,6 +13,7 @@
 #define PLL_WMAX (PLL_BMAX / 64)      // 64-bit words in a b-bit candidate bit-vector
 #define PLL_INF8 255u                 // "no entry" in the per-batch distance table
 #define PLL_MAX_N (1u << 24)          // hub ranks are packed in 24 bits
+#define PLL_PLANES 8u                 // distance planes per table row (BuildArgs::P)
 
 // Label entry: (hub rank << 8) | dist, so entries sort by hub rank.
 __host__ __device__ inline uint32_t pll_pack(uint32_t hub_rank, uint32_t d) { return (hub_rank << 8) | d; }
@@ -103,6 +104,15 @@ struct BuildArgs {
     // at v scans L_in(v) against the table of L_out(u_k), and vice versa)
     const uint8_t* Tchk;
     const uint64_t* rmchk;
+    // the same table as bit planes, used instead of T while every prune
+    // threshold of the round is at most PLL_PLANES (null: byte table only).
+    // Row h holds PLL_PLANES planes of W words at P + (h * PLL_PLANES + t - 1) * W;
+    // bit k of plane t is set when d(u_k, h) <= t for t = 1 and 2, and when
+    // d(u_k, h) == t for t >= 3 (self entries, at distance 0, are left out:
+    // they never prune).  Row n - 1 is always zero: the lowest-ranked vertex
+    // is a hub of nobody else.  Pchk is the table the checks read, as Tchk.
+    uint64_t* P;
+    const uint64_t* Pchk;
     // weighted graphs: D[v * bstride + k] = the smallest candidate distance
     // of u_k that reached v in this batch (255: none); it plays the part of
     // C(v), since a candidate may come back shorter in a later round

@@ -349,9 +349,25 @@ __device__ inline uint64_t rank_mask(uint32_t rel, uint32_t w) {
     return (1ull << (rel - lo)) - 1ull;
 }
 
+// Record d(u_k, h) = d (d >= 1) in the bit planes: plane 2 also holds the
+// distances of plane 1, so the thresholds 1 and 2 of rounds 2 and 3, which
+// carry nearly every check of a small-diameter graph, are one plane each;
+// the rare larger thresholds OR the exact planes 3..t on top.  Making planes
+// 3 and up cumulative too would cost a second atomic for nearly every entry
+// (90% of the R-MAT-20 label entries are at distance 2).
+__device__ inline void plane_set(const BuildArgs& A, uint32_t h, uint32_t d, uint32_t k) {
+    if (d > PLL_PLANES) return;
+    unsigned long long* row =
+        reinterpret_cast<unsigned long long*>(A.P) + (size_t)h * (PLL_PLANES * A.W) + (k >> 6);
+    const unsigned long long bit = 1ull << (k & 63u);
+    if (d == 1) atomicOr(row, bit);
+    atomicOr(row + (max(d, 2u) - 1u) * A.W, bit);
+}
+
 // Batch initialisation of Algorithm 4: delta L(u) = {(u,0)}, L(u) gets
 // (u,0), L(u) -> H(u).
 // The initial active list holds batch vertex u_k in slot k.
+template <bool PLANES = false>
 __device__ inline void phase_batch_init(const BuildArgs& A, const Exec& X, uint32_t ib, uint32_t bs, uint32_t bstamp) {
     const uint32_t lane = lane_id();
     for (uint32_t k = X.w; k < bs; k += X.nw) {
@@ -385,8 +401,10 @@ __device__ inline void phase_batch_init(const BuildArgs& A, const Exec& X, uint3
         if (lane == 0) {
             A.arena[off + len] = pll_pack(u, 0);
             A.llen[u] = len + 1;
-            A.T[(size_t)u * A.bstride + k] = 0;
-            if (u >= A.hot) atomicOr((unsigned long long*)&A.rowmask[u], kq);
+            if (!PLANES) {
+                A.T[(size_t)u * A.bstride + k] = 0;
+                if (u >= A.hot) atomicOr((unsigned long long*)&A.rowmask[u], kq);
+            }
         }
         // four chunks at a time: loaded before any is written out
         for (uint32_t i0 = 0; i0 < len; i0 += 256) {
@@ -401,8 +419,12 @@ __device__ inline void phase_batch_init(const BuildArgs& A, const Exec& X, uint3
             for (uint32_t c = 0; c < 4; ++c) {
                 if (i0 + 64u * c + lane < len) {
                     const uint32_t h = e[c] >> 8;
-                    A.T[(size_t)h * A.bstride + k] = (uint8_t)(e[c] & 255u);
-                    if (h >= A.hot) atomicOr((unsigned long long*)&A.rowmask[h], kq);
+                    if (PLANES) {
+                        plane_set(A, h, e[c] & 255u, k);
+                    } else {
+                        A.T[(size_t)h * A.bstride + k] = (uint8_t)(e[c] & 255u);
+                        if (h >= A.hot) atomicOr((unsigned long long*)&A.rowmask[h], kq);
+                    }
                 }
             }
         }
@@ -781,6 +803,140 @@ __device__ inline uint64_t bp_prune_words(const BuildArgs& A, uint32_t v, uint32
     return out;
 }
 
+// OR over each 16-lane row by DPP row rotations: every lane of a row gets
+// its row's OR (the whole wave must be active).
+__device__ inline uint32_t row_or32_dpp(uint32_t x) {
+    x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x121, 0xf, 0xf, false);  // row_ror:1
+    x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x122, 0xf, 0xf, false);  // row_ror:2
+    x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x124, 0xf, 0xf, false);  // row_ror:4
+    x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x128, 0xf, 0xf, false);  // row_ror:8
+    return x;
+}
+
+__device__ inline uint64_t row_or64_dpp(uint64_t x) {
+    return ((uint64_t)row_or32_dpp((uint32_t)(x >> 32)) << 32) | row_or32_dpp((uint32_t)x);
+}
+
+// Lane `src`'s x in every lane (the LDS crossbar; src may differ per lane).
+__device__ inline uint64_t shfl64(uint64_t x, uint32_t src) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(src * 4u), (int)(uint32_t)x);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(src * 4u), (int)(uint32_t)(x >> 32));
+    return ((uint64_t)hi << 32) | lo;
+}
+
+// x of the lane N below (mod 16) in each 16-lane row.
+template <int N>
+__device__ inline uint64_t row_ror64(uint64_t x) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)x, 0x120 + N, 0xf, 0xf, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(x >> 32), 0x120 + N, 0xf, 0xf, false);
+    return ((uint64_t)hi << 32) | lo;
+}
+
+// Lane e's x (e = 0..15, a constant) in every lane of its 16-lane row (DPP
+// row_newbcast; the whole wave must be active).
+template <int E>
+__device__ inline uint32_t row_bcast32(uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x150 + E, 0xf, 0xf, true);
+}
+
+// The word offsets of the table lines that a group's entries name, for the
+// lane's own slot: line i (< WM) is entry slot * WM + i of the row, where
+// slot = sub / WM (one slot, the whole row, at WM = 16).
+template <int WM, int I = 0>
+__device__ inline void plane_lines(uint32_t at, uint32_t first, uint32_t (&line)[WM]) {
+    if constexpr (I < WM) {
+        if constexpr (WM == 16)
+            line[I] = row_bcast32<I>(at);
+        else
+            line[I] = (uint32_t)__builtin_amdgcn_ds_bpermute((int)((first + I) * 4u), (int)at);
+        plane_lines<WM, I + 1>(at, first, line);
+    }
+}
+
+// The pruning test on the bit planes (BuildArgs::P), for rounds j <=
+// PLL_PLANES + 1.  The 16-lane group g takes 16 entries at a time: lane
+// 16g + i reads entry i, and the entry's plane line (W words, one 128-byte
+// line at W = 16) is then read by the group's lanes together, word w by the
+// lanes with sub % WM = w.  So an entry tests every candidate of the vertex
+// with one coalesced read and no compare or reduction, and the 16 lines of
+// a chunk are independent loads in flight at once: a chunk costs two
+// dependent accesses, where the byte table (prune_scan, prune_scan4) makes
+// a row-mask access and one pass of 64-byte segment reads, compares and
+// lane reductions per live candidate word (7.5 of them per entry in the
+// R-MAT-20 rounds 2 and 3).  Lanes whose word has no live candidate load
+// nothing.  For W < 16 the row's lanes hold 16 / WM lines side by side.
+//
+// SHARE: one receiver for the whole wave (its candidates in lanes w < W, and
+// group g takes entries 16g .. 16g + 15 of each 64); otherwise each group
+// has its own receiver, list and candidates (lane 16g + w).  The source is
+// L(v) or, with `nbr` in round 2, the neighbour row (see prune_scan_nbrs).
+// Returns the pruned candidates in the lanes that hold the words of cw.
+template <int WM, bool SHARE>
+__device__ inline uint64_t prune_planes(const BuildArgs& A, uint64_t off, uint32_t len, bool nbr, uint32_t lim,
+                                        uint32_t j, uint64_t cw, PhaseStats& st) {
+    constexpr uint32_t kStep = SHARE ? 64u : 16u;
+    const uint32_t lane = lane_id();
+    const uint32_t sub = lane & 15u;
+    const uint32_t gsh = lane & 48u;  // 16 * group
+    const uint32_t wd = sub & (uint32_t)(WM - 1);
+    const uint32_t first = gsh + sub - wd;  // first lane of this lane's slot
+    const uint32_t zero = (A.n - 1u) * (PLL_PLANES * A.W);
+    const uint32_t* src = (nbr ? A.rcol : A.arena) + off;
+    const uint64_t* words = A.Pchk + wd;
+    if (SHARE || WM < 16) cw = shfl64(cw, (SHARE ? 0u : gsh) + wd);
+    uint64_t pw = 0;
+    uint32_t idx = SHARE ? lane : sub;
+    uint32_t next = idx < len ? src[idx] : 0u;
+    for (uint32_t base = 0;; base += kStep, idx += kStep) {
+        const uint64_t live = cw & ~pw;
+        const uint64_t lb = ballot64(live != 0 && base < len);
+        if (!lb) break;
+        // this group still scans: candidates live and entries left
+        const bool on = ((lb >> gsh) & 0xFFFFull) != 0;
+        bool ok = on && idx < len;
+        st.read += ok;
+        const uint32_t ent = next;
+        next = on && idx + kStep < len ? src[idx + kStep] : 0u;
+        uint32_t h = ent, t = 1u;  // the neighbour row: T[h][k] <= 2 - 1
+        if (nbr) {
+            ok = ok && h < lim;
+        } else {
+            h = ent >> 8;
+            const uint32_t d = ent & 255u;
+            ok = ok && d != 0 && d < j;
+            t = j - d;
+        }
+        const uint32_t row = h * (PLL_PLANES * A.W);
+        uint64_t hit = 0;
+        // plane 1 or 2, then the exact planes 3..t
+        for (uint32_t p = 2;;) {
+            const uint64_t okb = ballot64(ok);
+            if (okb) {
+                uint32_t line[WM];
+                plane_lines<WM>(ok ? row + (min(t, p) - 1u) * A.W : zero, first, line);
+                if (live != 0 && on && ((okb >> gsh) & 0xFFFFull)) {
+#pragma unroll
+                    for (int i = 0; i < WM; ++i) hit |= words[line[i]];
+                    if (!(wd & 1u)) st.table += (uint32_t)__builtin_popcountll((okb >> first) & ((1ull << WM) - 1ull));
+                }
+            }
+            if (++p >= j) break;
+            ok = ok && t >= p;
+        }
+        // the lines of the row's slots, and of the wave's groups, together
+        if (WM <= 8) hit |= row_ror64<8>(hit);
+        if (WM <= 4) hit |= row_ror64<4>(hit);
+        if (WM <= 2) hit |= row_ror64<2>(hit);
+        if (WM <= 1) hit |= row_ror64<1>(hit);
+        if (SHARE) {
+            hit |= shfl64(hit, lane ^ 16u);
+            hit |= shfl64(hit, lane ^ 32u);
+        }
+        pw |= hit & live;
+    }
+    return pw;
+}
+
 // Gather phase of Algorithm 4 for round j: one wave per
 // receiver.  Receiver i (in shard order) becomes slot i of the next active
 // list (with an empty delta when nothing was accepted).
@@ -799,7 +955,7 @@ __device__ inline uint64_t bp_prune_words(const BuildArgs& A, uint32_t v, uint32
 // and nr->rclr, cleared here); active lists and heavy items use parity
 // nr->hout.
 
-template <int WM, bool BP = false, bool FUSE = false, bool QGATE = false, bool SMALLT = false>
+template <int WM, bool BP = false, bool FUSE = false, bool QGATE = false, bool SMALLT = false, bool PLANES = false>
 __device__ inline void phase_check(const BuildArgs& A, const Exec& X, uint32_t ib, uint32_t bs, uint32_t j, uint32_t p,
                                    bool relaxed, PhaseStats& st, const NextRound* nr = nullptr) {
     const uint32_t lane = lane_id();
@@ -840,7 +996,14 @@ __device__ inline void phase_check(const BuildArgs& A, const Exec& X, uint32_t i
         // i.e. with v a hub of u_k; but a candidate u_k only reaches vertices
         // ranked below it, and L(u_k) holds only hubs ranked above u_k.
         uint64_t pw = 0;
-        if (j == 2 && A.nbr_hubs && A.rrow[v + 1] - A.rrow[v] < len)
+        if (PLANES) {
+            if (j > 1) {
+                const uint64_t rb = A.rrow[v];
+                const uint32_t deg = (uint32_t)min(A.rrow[v + 1] - rb, (uint64_t)~0u);
+                const bool nbr = j == 2 && A.nbr_hubs && deg < len;
+                pw = prune_planes<WM, true>(A, nbr ? rb : off, nbr ? deg : len, nbr, min(v, ib + bs), j, scan, st);
+            }
+        } else if (j == 2 && A.nbr_hubs && A.rrow[v + 1] - A.rrow[v] < len)
             pw = prune_scan_nbrs<WM, QGATE, SMALLT>(A, v, min(v, relaxed ? ib : ib + bs), scan, st);
         else if (j > 1)
             pw = prune_scan<WM, QGATE, SMALLT>(A, off, len, j, scan, relaxed, ib, st);
@@ -878,9 +1041,13 @@ __device__ inline void phase_check(const BuildArgs& A, const Exec& X, uint32_t i
                 const uint32_t k = w * 64u + lane;
                 A.arena[off + len + pwos + __builtin_popcountll(aw & lt)] = pll_pack(ib + k, j);
                 if (in_batch) {
-                    A.T[(size_t)(ib + k) * A.bstride + (v - ib)] = (uint8_t)j;
-                    if (ib + k >= A.hot)
-                        atomicOr((unsigned long long*)&A.rowmask[ib + k], 1ull << ((v - ib) >> 4));
+                    if (PLANES) {
+                        plane_set(A, ib + k, j, v - ib);
+                    } else {
+                        A.T[(size_t)(ib + k) * A.bstride + (v - ib)] = (uint8_t)j;
+                        if (ib + k >= A.hot)
+                            atomicOr((unsigned long long*)&A.rowmask[ib + k], 1ull << ((v - ib) >> 4));
+                    }
                 }
             }
         }
@@ -901,27 +1068,6 @@ __device__ inline void phase_check(const BuildArgs& A, const Exec& X, uint32_t i
             enqueue_heavy(A, X, q, i, end - beg);
         }
     }
-}
-
-// OR over each 16-lane row by DPP row rotations: every lane of a row gets
-// its row's OR (the whole wave must be active).
-__device__ inline uint32_t row_or32_dpp(uint32_t x) {
-    x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x121, 0xf, 0xf, false);  // row_ror:1
-    x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x122, 0xf, 0xf, false);  // row_ror:2
-    x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x124, 0xf, 0xf, false);  // row_ror:4
-    x |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x128, 0xf, 0xf, false);  // row_ror:8
-    return x;
-}
-
-__device__ inline uint64_t row_or64_dpp(uint64_t x) {
-    return ((uint64_t)row_or32_dpp((uint32_t)(x >> 32)) << 32) | row_or32_dpp((uint32_t)x);
-}
-
-// Lane `src`'s x in every lane (the LDS crossbar; src may differ per lane).
-__device__ inline uint64_t shfl64(uint64_t x, uint32_t src) {
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(src * 4u), (int)(uint32_t)x);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(src * 4u), (int)(uint32_t)(x >> 32));
-    return ((uint64_t)hi << 32) | lo;
 }
 
 // The pruning scans of four receivers at once: group g = lane / 16 scans
@@ -1057,7 +1203,7 @@ __device__ inline void push_edges4(const BuildArgs& A, const Exec& X, const Next
 // receiver after another, and the next round's deliveries of all four go
 // out in one pass over their concatenated rows (push_edges4).  Active-list
 // slots, heavy rows, pulled rounds and statistics are phase_check's.
-template <int WM, bool SMALLT>
+template <int WM, bool SMALLT, bool PLANES = false>
 __device__ inline void phase_check4(const BuildArgs& A, const Exec& X, uint32_t ib, uint32_t bs, uint32_t j,
                                     bool relaxed, PhaseStats& st, const NextRound& nr) {
     const uint32_t lane = lane_id();
@@ -1108,7 +1254,10 @@ __device__ inline void phase_check4(const BuildArgs& A, const Exec& X, uint32_t 
                     lim = min(v, relaxed ? ib : ib + bs);
                 }
             }
-            pw = prune_scan4<WM, SMALLT>(A, soff, slen, nbr, lim, j, mine, relaxed, ib, st);
+            if (PLANES)
+                pw = prune_planes<WM, false>(A, soff, slen, nbr, lim, j, mine, st);
+            else
+                pw = prune_scan4<WM, SMALLT>(A, soff, slen, nbr, lim, j, mine, relaxed, ib, st);
         }
         const uint64_t acc4 = mine & ~pw;
         st.cand += __builtin_popcountll(mine);
@@ -1148,9 +1297,13 @@ __device__ inline void phase_check4(const BuildArgs& A, const Exec& X, uint32_t 
                     const uint32_t k = w * 64u + lane;
                     A.arena[og + lg + pwos + __builtin_popcountll(aw & lt)] = pll_pack(ib + k, j);
                     if (in_batch) {
-                        A.T[(size_t)(ib + k) * A.bstride + (vg - ib)] = (uint8_t)j;
-                        if (ib + k >= A.hot)
-                            atomicOr((unsigned long long*)&A.rowmask[ib + k], 1ull << ((vg - ib) >> 4));
+                        if (PLANES) {
+                            plane_set(A, ib + k, j, vg - ib);
+                        } else {
+                            A.T[(size_t)(ib + k) * A.bstride + (vg - ib)] = (uint8_t)j;
+                            if (ib + k >= A.hot)
+                                atomicOr((unsigned long long*)&A.rowmask[ib + k], 1ull << ((vg - ib) >> 4));
+                        }
                     }
                 }
             }
@@ -1552,7 +1705,24 @@ __device__ inline void phase_check_w(const BuildArgs& A, const Exec& X, uint32_t
     }
 }
 
-// Reset the distance table rows written during the batch.
+// The byte table from the labels the batch's roots hold now (one wave per
+// root): a build whose rounds outgrow the bit planes goes on with it.
+__device__ inline void phase_table_fill(const BuildArgs& A, const Exec& X, uint32_t ib, uint32_t bs) {
+    const uint32_t lane = lane_id();
+    for (uint32_t k = X.w; k < bs; k += X.nw) {
+        const uint32_t len = A.llen[ib + k];
+        const uint64_t off = A.loff[ib + k];
+        for (uint32_t i = lane; i < len; i += 64) {
+            const uint32_t e = A.arena[off + i];
+            const uint32_t h = e >> 8;
+            A.T[(size_t)h * A.bstride + k] = (uint8_t)(e & 255u);
+            if (h >= A.hot) atomicOr((unsigned long long*)&A.rowmask[h], 1ull << (k >> 4));
+        }
+    }
+}
+
+// Reset the distance table rows (or plane words) written during the batch.
+template <bool PLANES = false>
 __device__ inline void phase_clear_table(const BuildArgs& A, const Exec& X, uint32_t ib, uint32_t bs) {
     const uint32_t lane = lane_id();
     // four waves per root: task t clears the 64-entry chunks c, c + 4, ...
@@ -1563,11 +1733,19 @@ __device__ inline void phase_clear_table(const BuildArgs& A, const Exec& X, uint
         const uint32_t len = A.llen[u];
         const uint64_t off = A.loff[u];
         for (uint32_t i = 64u * c + lane; i < len; i += 256u) {
-            const uint32_t h = A.arena[off + i] >> 8;
-            A.T[(size_t)h * A.bstride + k] = (uint8_t)PLL_INF8;
-            if (h >= A.hot) A.rowmask[h] = 0;
+            const uint32_t e = A.arena[off + i];
+            const uint32_t h = e >> 8;
+            if (PLANES) {
+                const uint32_t d = e & 255u;
+                uint64_t* row = A.P + (size_t)h * (PLL_PLANES * A.W) + (k >> 6);
+                if (d == 1) row[0] = 0;
+                if (d != 0 && d <= PLL_PLANES) row[(max(d, 2u) - 1u) * A.W] = 0;
+            } else {
+                A.T[(size_t)h * A.bstride + k] = (uint8_t)PLL_INF8;
+                if (h >= A.hot) A.rowmask[h] = 0;
+            }
         }
-        if (c == 0 && lane == 0 && u >= A.hot) A.rowmask[u] = 0;
+        if (!PLANES && c == 0 && lane == 0 && u >= A.hot) A.rowmask[u] = 0;
     }
 }
 
