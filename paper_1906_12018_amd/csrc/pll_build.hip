@@ -322,9 +322,22 @@ __global__ void k_batch_prep(DevCounters* ctr) {
     }
 }
 
-template <bool PLANES>
 __global__ void __launch_bounds__(kBlock) k_batch_init(BuildArgs A, uint32_t ib, uint32_t bs, uint32_t bstamp) {
-    pll::phase_batch_init<PLANES>(A, grid_exec(A), ib, bs, bstamp);
+    pll::phase_batch_init(A, grid_exec(A), ib, bs, bstamp);
+}
+
+// The same for a build with bit planes, one wave per root.
+constexpr int kInitBlock = pll::kInitRoots * PLL_WAVE;
+
+__global__ void __launch_bounds__(kInitBlock) k_batch_init_planes(BuildArgs A, uint32_t ib, uint32_t bs,
+                                                                  uint32_t bstamp) {
+    __shared__ uint32_t s_hot[pll::kInitHot];
+    const uint32_t rows = ib + bs;
+    for (uint32_t h = threadIdx.x; h < min(rows, pll::kInitHot); h += kInitBlock) s_hot[h] = 0;
+    __syncthreads();
+    pll::phase_batch_init<true>(A, grid_exec(A), ib, bs, bstamp, s_hot);
+    __syncthreads();
+    pll::plane_flush(A, blockIdx.x * pll::kInitRoots, rows, s_hot);
 }
 
 __global__ void __launch_bounds__(kBlock) k_push(BuildArgs A, uint32_t ib, uint32_t p, uint32_t nact, uint32_t rstamp,
@@ -1293,9 +1306,9 @@ int planes_to_bytes(DevAllocs& M, BuildArgs& A, uint32_t ib, uint32_t bs, hipStr
 
 void launch_batch_init(const BuildArgs& A, uint32_t ib, uint32_t bs, uint32_t bstamp, hipStream_t s) {
     if (A.P)
-        k_batch_init<true><<<blocks_for_waves(bs), kBlock, 0, s>>>(A, ib, bs, bstamp);
+        k_batch_init_planes<<<(bs + pll::kInitRoots - 1) / pll::kInitRoots, kInitBlock, 0, s>>>(A, ib, bs, bstamp);
     else
-        k_batch_init<false><<<blocks_for_waves(bs), kBlock, 0, s>>>(A, ib, bs, bstamp);
+        k_batch_init<<<blocks_for_waves(bs), kBlock, 0, s>>>(A, ib, bs, bstamp);
 }
 
 void launch_clear_table(const BuildArgs& A, uint32_t ib, uint32_t bs, DevCounters* prep, hipStream_t s) {

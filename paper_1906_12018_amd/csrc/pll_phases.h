@@ -367,8 +367,17 @@ __device__ inline void plane_set(const BuildArgs& A, uint32_t h, uint32_t d, uin
 // Batch initialisation of Algorithm 4: delta L(u) = {(u,0)}, L(u) gets
 // (u,0), L(u) -> H(u).
 // The initial active list holds batch vertex u_k in slot k.
+//
+// With planes, a workgroup runs the kInitRoots consecutive roots of one
+// k / kInitRoots, one per wave, and collects the distances 1 and 2 of the
+// rows h < kInitHot in s_hot: bit k % kInitRoots of s_hot[h] is plane 1's
+// bit, bit 16 + k % kInitRoots plane 2's.  plane_flush then writes them out.
+constexpr uint32_t kInitHot = 4096;
+constexpr uint32_t kInitRoots = 16;
+
 template <bool PLANES = false>
-__device__ inline void phase_batch_init(const BuildArgs& A, const Exec& X, uint32_t ib, uint32_t bs, uint32_t bstamp) {
+__device__ inline void phase_batch_init(const BuildArgs& A, const Exec& X, uint32_t ib, uint32_t bs, uint32_t bstamp,
+                                        uint32_t* s_hot = nullptr) {
     const uint32_t lane = lane_id();
     for (uint32_t k = X.w; k < bs; k += X.nw) {
         const uint32_t u = ib + k;
@@ -420,7 +429,11 @@ __device__ inline void phase_batch_init(const BuildArgs& A, const Exec& X, uint3
                 if (i0 + 64u * c + lane < len) {
                     const uint32_t h = e[c] >> 8;
                     if (PLANES) {
-                        plane_set(A, h, e[c] & 255u, k);
+                        const uint32_t d = e[c] & 255u;
+                        if (d <= 2 && h < kInitHot)
+                            atomicOr(&s_hot[h], (d == 1 ? 0x10001u : 0x10000u) << (k % kInitRoots));
+                        else
+                            plane_set(A, h, d, k);
                     } else {
                         A.T[(size_t)h * A.bstride + k] = (uint8_t)(e[c] & 255u);
                         if (h >= A.hot) atomicOr((unsigned long long*)&A.rowmask[h], kq);
@@ -432,6 +445,22 @@ __device__ inline void phase_batch_init(const BuildArgs& A, const Exec& X, uint3
         if (lane == 0 && A.act_rng[0]) A.act_rng[0][k] = make_uint2(len, 1u);  // the self entry
         if (lane < A.W) A.act_delta[0][(size_t)k * A.W + lane] = (lane == (k >> 6)) ? (1ull << (k & 63)) : 0ull;
         enqueue_heavy(A, X, 0, k, deg);
+    }
+}
+
+// Write the workgroup's s_hot rows (below the batch's end: no other vertex is
+// a hub yet) into planes 1 and 2; k0 is its first root's index in the batch.
+// The top-ranked rows hold a bit of nearly every root, and atomics on one
+// address serialise: one atomic per row and 16 roots instead of one per
+// root.  R-MAT-20 batch init 17.8 -> 13.6 ms per build.
+__device__ inline void plane_flush(const BuildArgs& A, uint32_t k0, uint32_t rows, const uint32_t* s_hot) {
+    for (uint32_t h = threadIdx.x; h < min(rows, kInitHot); h += blockDim.x) {
+        const uint32_t x = s_hot[h];
+        if (!x) continue;
+        unsigned long long* row =
+            reinterpret_cast<unsigned long long*>(A.P) + (size_t)h * (PLL_PLANES * A.W) + (k0 >> 6);
+        if (x & 0xFFFFu) atomicOr(row, (unsigned long long)(x & 0xFFFFu) << (k0 & 63u));
+        atomicOr(row + A.W, (unsigned long long)(x >> 16) << (k0 & 63u));
     }
 }
 
