@@ -276,7 +276,9 @@ __device__ inline void block_add_stats(DevCounters* ctr, const unsigned long lon
     const uint32_t lane = lane_id(), wv = threadIdx.x >> 6;
 #pragma unroll
     for (int k = 0; k < N; ++k) {
-        const unsigned long long t = wave_sum64(v[k]);
+        // DPP adds: the shuffles of nine 64-bit sums (108 LDS accesses, in
+        // chains of twelve) ended every wave of every round
+        const unsigned long long t = ballot64(v[k] != 0) ? wave_sum64_dpp(v[k]) : 0ull;
         if (lane == 0) s_part[wv][k] = t;
     }
     __syncthreads();

@@ -209,6 +209,30 @@ __device__ inline uint32_t wave_or32_dpp(uint32_t x) {
     return readlane32(x, 63);
 }
 
+// Sum over the 64 lanes by DPP adds (the whole wave must be active);
+// wave-uniform.  Row shifts leave each 16-lane row's sum in its lane 15,
+// the row broadcasts add rows 0 and 1 and rows 2 and 3 up in lane 63.
+__device__ inline uint32_t wave_sum32_dpp(uint32_t x) {
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, true);  // row_shr:1
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, true);  // row_shr:2
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, true);  // row_shr:4
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, true);  // row_shr:8
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false); // row_bcast:15, rows 1, 3
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false); // row_bcast:31, rows 2, 3
+    return readlane32(x, 63);
+}
+
+// The same for 64-bit lanes: the low 26 bits, the next 26 and the top 12
+// are summed apart (64 lanes of 26 bits fit 32), the upper two only where a
+// lane has such bits.
+__device__ inline unsigned long long wave_sum64_dpp(unsigned long long x) {
+    const uint32_t mid = (uint32_t)(x >> 26) & 0x3FFFFFFu, top = (uint32_t)(x >> 52);
+    unsigned long long t = wave_sum32_dpp((uint32_t)x & 0x3FFFFFFu);
+    if (ballot64(mid != 0)) t += (unsigned long long)wave_sum32_dpp(mid) << 26;
+    if (ballot64(top != 0)) t += (unsigned long long)wave_sum32_dpp(top) << 52;
+    return t;
+}
+
 // Exclusive prefix sum over the 64 lanes.
 __device__ inline uint32_t wave_excl_scan32(uint32_t x) {
     const uint32_t l = lane_id();

@@ -29,7 +29,9 @@ struct Exec {
 
 // Per-lane statistics a phase accumulates (summed over lanes by the caller).
 struct PhaseStats {
-    unsigned long long cand = 0, acc = 0, edges = 0, read = 0, table = 0, removed = 0, bp = 0;
+    // one lane's share of a launch: a few per entry that this lane read
+    uint32_t cand = 0, acc = 0, read = 0, table = 0, removed = 0, bp = 0;
+    unsigned long long edges = 0;
     // cost of the positive / negative checks: |L(v)| at each check that
     // added / pruned a candidate (Section 4.3, Table 3)
     unsigned long long cost_pos = 0, cost_neg = 0;
@@ -268,13 +270,13 @@ __device__ inline uint64_t prune_scan_nbrs(const BuildArgs& A, uint32_t v, uint3
     return pw;
 }
 
-// Room for `need` more entries in the list of rank v (capacity doubling).
+// Room for `need` more entries in the list of rank v (capacity doubling;
+// cap is its capacity).
 // New blocks come from the bump region X.arena_sh of the arena, or from the
 // next region with room.  Wave-uniform; returns the list's offset, or ~0
 // when every region is exhausted.
 __device__ inline uint64_t wave_reserve(const BuildArgs& A, const Exec& X, uint32_t v, uint64_t off, uint32_t len,
-                                        uint32_t need) {
-    const uint32_t cap = A.lcap[v];
+                                        uint32_t cap, uint32_t need) {
     if (len + need <= cap) return off;
     uint32_t newcap = max(cap * 2u, (len + need + 15u) & ~15u);
     newcap = max(newcap, 16u);
@@ -383,6 +385,7 @@ __device__ inline void phase_batch_init(const BuildArgs& A, const Exec& X, uint3
         const uint32_t u = ib + k;
         const uint32_t len = A.llen[u];
         const uint64_t off0 = A.loff[u];
+        const uint32_t cap = A.lcap[u];
         // the first four chunks of L(u) and u's degree are loaded ahead of
         // the bookkeeping (a relocation by wave_reserve copies the same
         // entries, so they stay valid)
@@ -404,7 +407,7 @@ __device__ inline void phase_batch_init(const BuildArgs& A, const Exec& X, uint3
             if (lane < A.W) A.act_delta[0][(size_t)k * A.W + lane] = 0ull;
             continue;
         }
-        const uint64_t off = wave_reserve(A, X, u, off0, len, 1);
+        const uint64_t off = wave_reserve(A, X, u, off0, len, cap, 1);
         if (off == ~0ull) continue;
         const unsigned long long kq = 1ull << (k >> 4);
         if (lane == 0) {
@@ -464,6 +467,32 @@ __device__ inline void plane_flush(const BuildArgs& A, uint32_t k0, uint32_t row
     }
 }
 
+// The lanes with `enq` append r to receiver queue rq stored in recv, and of
+// them those with `first` (r's first touch in this batch) to the touched
+// list, with L(r)'s length tlen.  The whole wave calls it.  The two counters'
+// atomics are issued together, so a call waits for one round trip.
+__device__ inline void append_receivers(const BuildArgs& A, const Exec& X, uint32_t* recv, uint32_t rq, uint32_t r,
+                                        bool enq, bool first, uint32_t tlen) {
+    const uint64_t be = ballot64(enq), bf = ballot64(first);
+    if (!be) return;
+    const uint32_t lane = lane_id();
+    const uint32_t leader = (uint32_t)__builtin_ctzll(be);
+    uint32_t rb = 0, tb = 0;
+    if (lane == leader) {
+        rb = atomicAdd(&X.qs[X.my].recv[rq], (uint32_t)__builtin_popcountll(be));
+        if (bf) tb = atomicAdd(&X.qs[X.my].touched, (uint32_t)__builtin_popcountll(bf));
+    }
+    const size_t seg = (size_t)X.my * X.seg;
+    rb = readlane32(rb, leader);
+    tb = readlane32(tb, leader);
+    if (enq) recv[seg + rb + __builtin_popcountll(be & lanemask_lt())] = r;
+    if (first) {
+        const size_t tp = seg + tb + __builtin_popcountll(bf & lanemask_lt());
+        A.touched[tp] = r;
+        A.tstart[tp] = tlen;
+    }
+}
+
 // The lanes whose vertex r got a delivery (`any`) take r's receiver slot
 // of the next round (one per vertex and round, via its round stamp) into
 // queue rq stored in recv; the lane that wins the slot also records r's
@@ -471,21 +500,16 @@ __device__ inline void plane_flush(const BuildArgs& A, uint32_t k0, uint32_t row
 __device__ inline void enqueue_receivers(const BuildArgs& A, const Exec& X, uint32_t* recv, uint32_t rq,
                                          uint32_t rstamp, uint32_t bstamp, uint32_t r, bool any) {
     bool enq = false;
-    if (any && A.recv_stamp[r] != rstamp) enq = atomicExch(&A.recv_stamp[r], rstamp) != rstamp;
-    bool first = false;
-    if (enq && A.touch_stamp[r] != bstamp) {
-        A.touch_stamp[r] = bstamp;
-        first = true;
+    uint32_t ts = bstamp, tlen = 0;
+    if (any && A.recv_stamp[r] != rstamp) {
+        // the winner's other reads fly with the exchange
+        ts = A.touch_stamp[r];
+        tlen = A.llen[r];
+        enq = atomicExch(&A.recv_stamp[r], rstamp) != rstamp;
     }
-    if (ballot64(enq)) {
-        const uint32_t rp = shard_append(&X.qs[X.my].recv[rq], enq, (uint64_t)X.my * X.seg);
-        if (enq) recv[rp] = r;
-        const uint32_t tp = shard_append(&X.qs[X.my].touched, first, (uint64_t)X.my * X.seg);
-        if (first) {
-            A.touched[tp] = r;
-            A.tstart[tp] = A.llen[r];
-        }
-    }
+    const bool first = enq && ts != bstamp;
+    if (first) A.touch_stamp[r] = bstamp;
+    append_receivers(A, X, recv, rq, r, enq, first, tlen);
 }
 
 // Deliver to vertex r the words w[k] of a delta whose candidates ranked
@@ -513,13 +537,17 @@ __device__ inline bool deliver4(const BuildArgs& A, uint64_t* msgs, uint32_t r, 
 // Push delta L(a) (lane w < W holds word w in dl; nz marks the nonzero
 // words) along the CSR entries [beg, end) of the active vertex a, into the
 // message buffer msgs and receiver queue rq (counters) stored in recv.
+// The next 64 neighbours load while this step delivers; first0 is the first
+// step's, lane l's entry beg + l (0 past the end).
 __device__ inline void push_edges(const BuildArgs& A, const Exec& X, uint64_t* msgs, uint32_t* recv, uint32_t ib,
                                   uint32_t rq, uint32_t rstamp, uint32_t bstamp, uint64_t dl, uint64_t nz,
-                                  uint64_t beg, uint64_t end) {
+                                  uint64_t beg, uint64_t end, uint32_t first0) {
     const uint32_t lane = lane_id();
+    uint32_t next = first0;
     for (uint64_t e0 = beg; e0 < end; e0 += 64) {
         const uint64_t e = e0 + lane;
-        const uint32_t r = e < end ? A.rcol[e] : 0u;
+        const uint32_t r = next;
+        next = e + 64 < end ? A.rcol[e + 64] : 0u;
         const bool fwd = e < end && r > ib;
         const uint32_t rel = r - ib;
         bool any = false;
@@ -558,7 +586,8 @@ __device__ inline void phase_push_heavy(const BuildArgs& A, const Exec& X, uint3
         const uint64_t beg = A.rrow[a] + (uint64_t)item.y * kHeavyItem;
         const uint64_t end = min(A.rrow[a + 1], beg + kHeavyItem);
         if (lane == 0) st.edges += end - beg;
-        push_edges(A, X, msgs, recv, ib, rq, rstamp, bstamp, dl, nz, beg, end);
+        push_edges(A, X, msgs, recv, ib, rq, rstamp, bstamp, dl, nz, beg, end,
+                   beg + lane < end ? A.rcol[beg + lane] : 0u);
     }
 }
 
@@ -629,21 +658,7 @@ __device__ inline void phase_pull(const BuildArgs& A, const Exec& X, uint32_t ib
         }
         if (m) atomicOr((unsigned long long*)&nr.msgs[(size_t)r * W + lane], (unsigned long long)m);
         if (!ballot64(m != 0)) continue;
-        bool enq = false, first = false;
-        if (lane == 0) {
-            if (A.recv_stamp[r] != nr.rstamp) enq = atomicExch(&A.recv_stamp[r], nr.rstamp) != nr.rstamp;
-            if (enq && A.touch_stamp[r] != nr.bstamp) {
-                A.touch_stamp[r] = nr.bstamp;
-                first = true;
-            }
-        }
-        const uint32_t rp = shard_append(&X.qs[X.my].recv[nr.rout], enq, (uint64_t)X.my * X.seg);
-        if (enq) nr.recv[rp] = r;
-        const uint32_t tp = shard_append(&X.qs[X.my].touched, first, (uint64_t)X.my * X.seg);
-        if (first) {
-            A.touched[tp] = r;
-            A.tstart[tp] = A.llen[r];
-        }
+        enqueue_receivers(A, X, nr.recv, nr.rout, nr.rstamp, nr.bstamp, r, lane == 0);
     }
 }
 
@@ -696,21 +711,7 @@ __device__ inline void phase_pull4(const BuildArgs& A, const Exec& X, uint32_t i
         const uint64_t got = ballot64(m != 0);
         if (!got) continue;
         // one receiver slot per vertex and round, taken by lane 0 of the group
-        bool enq = false, first = false;
-        if (wd == 0 && ((got >> gsh) & 0xFFFFull)) {
-            if (A.recv_stamp[r] != nr.rstamp) enq = atomicExch(&A.recv_stamp[r], nr.rstamp) != nr.rstamp;
-            if (enq && A.touch_stamp[r] != nr.bstamp) {
-                A.touch_stamp[r] = nr.bstamp;
-                first = true;
-            }
-        }
-        const uint32_t rp = shard_append(&X.qs[X.my].recv[nr.rout], enq, (uint64_t)X.my * X.seg);
-        if (enq) nr.recv[rp] = r;
-        const uint32_t tp = shard_append(&X.qs[X.my].touched, first, (uint64_t)X.my * X.seg);
-        if (first) {
-            A.touched[tp] = r;
-            A.tstart[tp] = A.llen[r];
-        }
+        enqueue_receivers(A, X, nr.recv, nr.rout, nr.rstamp, nr.bstamp, r, wd == 0 && ((got >> gsh) & 0xFFFFull) != 0);
     }
 }
 
@@ -750,7 +751,8 @@ __device__ inline void phase_push(const BuildArgs& A, const Exec& X, uint32_t ib
         const uint64_t beg = A.rrow[a], end = A.rrow[a + 1];
         if (end - beg > kHeavy) continue;
         if (lane == 0) st.edges += end - beg;
-        push_edges(A, X, A.msgs, A.recv, ib, p, rstamp, bstamp, dl, nz, beg, end);
+        push_edges(A, X, A.msgs, A.recv, ib, p, rstamp, bstamp, dl, nz, beg, end,
+                   beg + lane < end ? A.rcol[beg + lane] : 0u);
     }
     phase_push_heavy(A, X, ib, p, p, A.msgs, A.recv, rstamp, bstamp, st);
 }
@@ -1014,6 +1016,12 @@ __device__ inline void phase_check(const BuildArgs& A, const Exec& X, uint32_t i
         }
         const uint32_t len = A.llen[v];
         uint64_t off = A.loff[v];
+        const uint32_t cap = A.lcap[v];
+        // the row is needed by the push and by round 2's scan; its first
+        // entries load beside the list's
+        const uint64_t rbeg = A.rrow[v], rend = A.rrow[v + 1];
+        uint32_t nb0 = 0;
+        if (FUSE && lane < rend - rbeg) nb0 = A.rcol[rbeg + lane];
         uint64_t scan = mine;
         if (BP) {
             const uint64_t bpp = bp_prune_words<WM>(A, v, ib, j, mine);
@@ -1027,12 +1035,11 @@ __device__ inline void phase_check(const BuildArgs& A, const Exec& X, uint32_t i
         uint64_t pw = 0;
         if (PLANES) {
             if (j > 1) {
-                const uint64_t rb = A.rrow[v];
-                const uint32_t deg = (uint32_t)min(A.rrow[v + 1] - rb, (uint64_t)~0u);
-                const bool nbr = j == 2 && A.nbr_hubs && deg < len;
-                pw = prune_planes<WM, true>(A, nbr ? rb : off, nbr ? deg : len, nbr, min(v, ib + bs), j, scan, st);
+                const bool nbr = j == 2 && A.nbr_hubs && rend - rbeg < len;
+                pw = prune_planes<WM, true>(A, nbr ? rbeg : off, nbr ? (uint32_t)(rend - rbeg) : len, nbr,
+                                            min(v, ib + bs), j, scan, st);
             }
-        } else if (j == 2 && A.nbr_hubs && A.rrow[v + 1] - A.rrow[v] < len)
+        } else if (j == 2 && A.nbr_hubs && rend - rbeg < len)
             pw = prune_scan_nbrs<WM, QGATE, SMALLT>(A, v, min(v, relaxed ? ib : ib + bs), scan, st);
         else if (j > 1)
             pw = prune_scan<WM, QGATE, SMALLT>(A, off, len, j, scan, relaxed, ib, st);
@@ -1055,7 +1062,7 @@ __device__ inline void phase_check(const BuildArgs& A, const Exec& X, uint32_t i
             if (lane == 0) atomicOr(&A.ctr->error, PLL_ERR_DIST);
             continue;
         }
-        off = wave_reserve(A, X, v, off, len, total);
+        off = wave_reserve(A, X, v, off, len, cap, total);
         if (off == ~0ull) continue;
         if (lane == 0) st.acc += total;
         const bool in_batch = v - ib < bs;
@@ -1084,17 +1091,16 @@ __device__ inline void phase_check(const BuildArgs& A, const Exec& X, uint32_t i
         if (FUSE && nr->pull) {  // the receivers gather: record where delta L(v) is
             if (lane == 0) {
                 A.act_at[v] = ((uint64_t)nr->rstamp << 32) | i;
-                st.pulled += A.rrow[v + 1] - A.rrow[v];
+                st.pulled += rend - rbeg;
             }
             continue;
         }
-        const uint64_t beg = A.rrow[v], end = A.rrow[v + 1];
-        if (FUSE && end - beg <= kHeavy) {
-            if (lane == 0) st.edges += end - beg;
-            push_edges(A, X, nr->msgs, nr->recv, ib, nr->rout, nr->rstamp, nr->bstamp, acc, ballot64(acc != 0), beg,
-                       end);
+        if (FUSE && rend - rbeg <= kHeavy) {
+            if (lane == 0) st.edges += rend - rbeg;
+            push_edges(A, X, nr->msgs, nr->recv, ib, nr->rout, nr->rstamp, nr->bstamp, acc, ballot64(acc != 0), rbeg,
+                       rend, nb0);
         } else {
-            enqueue_heavy(A, X, q, i, end - beg);
+            enqueue_heavy(A, X, q, i, rend - rbeg);
         }
     }
 }
@@ -1312,7 +1318,7 @@ __device__ inline void phase_check4(const BuildArgs& A, const Exec& X, uint32_t 
             const uint32_t vg = readlane32(v, 16u * gg);
             const uint32_t lg = readlane32(len, 16u * gg);
             const uint32_t total = readlane32(incl, 16u * gg + 15u);
-            const uint64_t og = wave_reserve(A, X, vg, readlane64(off, 16u * gg), lg, total);
+            const uint64_t og = wave_reserve(A, X, vg, readlane64(off, 16u * gg), lg, A.lcap[vg], total);
             if (og == ~0ull) continue;
             if (lane == 0) st.acc += total;
             const bool in_batch = vg - ib < bs;
@@ -1614,22 +1620,7 @@ __device__ inline void push_edges_w(const BuildArgs& A, const Exec& X, uint32_t 
             }
         }
         if (ballot64(over) && lane == 0) atomicOr(&A.ctr->error, PLL_ERR_DIST);
-        bool enq = false;
-        if (any && A.recv_stamp[r] != rstamp) enq = atomicExch(&A.recv_stamp[r], rstamp) != rstamp;
-        bool first = false;
-        if (enq && A.touch_stamp[r] != bstamp) {
-            A.touch_stamp[r] = bstamp;
-            first = true;
-        }
-        if (ballot64(enq)) {
-            const uint32_t rp = shard_append(&X.qs[X.my].recv[p], enq, (uint64_t)X.my * X.seg);
-            if (enq) A.recv[rp] = r;
-            const uint32_t tp = shard_append(&X.qs[X.my].touched, first, (uint64_t)X.my * X.seg);
-            if (first) {
-                A.touched[tp] = r;
-                A.tstart[tp] = A.llen[r];
-            }
-        }
+        enqueue_receivers(A, X, A.recv, p, rstamp, bstamp, r, any);
     }
 }
 
@@ -1703,7 +1694,7 @@ __device__ inline void phase_check_w(const BuildArgs& A, const Exec& X, uint32_t
             A.act_rng[q][i] = make_uint2(len, total);
         }
         if (total != 0) {
-            off = wave_reserve(A, X, v, off, len, total);
+            off = wave_reserve(A, X, v, off, len, A.lcap[v], total);
             if (off != ~0ull) {
                 if (lane == 0) st.acc += total;
                 const bool in_batch = v - ib < bs;
