@@ -1373,6 +1373,29 @@ __device__ inline void phase_check4(const BuildArgs& A, const Exec& X, uint32_t 
     }
 }
 
+// Write the batch entries (u_k, s_dist[k]) of the hubs k set in s_pres (W
+// words) to the arena from `at` on, in ascending hub rank; returns how many.
+__device__ inline uint32_t segment_emit(const BuildArgs& A, uint32_t ib, uint64_t at, const uint64_t* s_pres,
+                                        const uint8_t* s_dist) {
+    const uint32_t lane = lane_id();
+    const uint64_t pw = lane < A.W ? s_pres[lane] : 0ull;
+    const uint32_t cnt = (uint32_t)__builtin_popcountll(pw);
+    const uint32_t pos = wave_excl_scan32(cnt);
+    const uint32_t total = readlane32(pos + cnt, 63);
+    uint64_t todo = ballot64(pw != 0);
+    while (todo) {
+        const uint32_t w = (uint32_t)__builtin_ctzll(todo);
+        todo &= todo - 1;
+        const uint64_t aw = readlane64(pw, w);
+        const uint32_t base = readlane32(pos, w);
+        if ((aw >> lane) & 1ull) {
+            const uint32_t k = w * 64u + lane;
+            A.arena[at + base + __builtin_popcountll(aw & lanemask_lt())] = pll_pack(ib + k, s_dist[k]);
+        }
+    }
+    return total;
+}
+
 // Batch end, one wave per touched vertex v: clear C(v); sort the
 // entries this batch appended to L(v) by hub rank; with `recheck`, first
 // drop every such entry (u, d) that L(u) and L(v) already cover through
@@ -1466,24 +1489,78 @@ __device__ inline void phase_batch_end(const BuildArgs& A, const Exec& X, uint32
                 prev = mn;
             }
         }
-        // emit the batch segment in ascending hub rank
-        const uint64_t pw = lane < W ? s_pres[lane] : 0ull;
-        const uint32_t cnt = (uint32_t)__builtin_popcountll(pw);
-        const uint32_t pos = wave_excl_scan32(cnt);
-        const uint32_t total = readlane32(pos + cnt, 63);
-        uint64_t todo = ballot64(pw != 0);
-        while (todo) {
-            const uint32_t w = (uint32_t)__builtin_ctzll(todo);
-            todo &= todo - 1;
-            const uint64_t aw = readlane64(pw, w);
-            const uint32_t base = readlane32(pos, w);
-            if ((aw >> lane) & 1ull) {
-                const uint32_t k = w * 64u + lane;
-                A.arena[off + ts + base + __builtin_popcountll(aw & lanemask_lt())] = pll_pack(ib + k, s_dist[k]);
-            }
-        }
+        const uint32_t total = segment_emit(A, ib, off + ts, s_pres, s_dist);
         if (lane == 0 && total != tail) A.llen[v] = ts + total;
         wave_lds_sync();
+    }
+}
+
+// The position of this lane's x among its 16-lane row's (distinct) values.
+template <int N = 1>
+__device__ inline uint32_t row_rank32(uint32_t x) {
+    if constexpr (N < 16) {
+        const uint32_t y = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x120 + N, 0xf, 0xf, false);  // row_ror:N
+        return (y < x ? 1u : 0u) + row_rank32<N + 1>(x);
+    }
+    return 0u;
+}
+
+// The batch end of an unweighted build without the recheck, four touched
+// vertices per wave, one per 16-lane group: the batches of a large graph
+// touch hundreds of thousands of vertices and append fewer than 16 entries
+// to most, and one vertex per wave left 48 lanes idle behind a chain of
+// dependent reads.  A segment of up to 16 entries is sorted in registers
+// (each entry's position is the number of smaller ones in its row); longer
+// ones take the whole wave, one after another, through the presence bitmap
+// of phase_batch_end.
+__device__ inline void phase_batch_end4(const BuildArgs& A, const Exec& X, uint32_t ib, uint64_t* s_pres,
+                                        uint8_t* s_dist) {
+    const uint32_t lane = lane_id();
+    const uint32_t W = A.W;
+    const uint32_t sub = lane & 15u, g = lane >> 4;
+    uint32_t pre;
+    const uint32_t ntouched = shard_prefix(lane < X.nq ? X.qs[lane].touched : 0u, pre);
+    for (uint32_t i0 = 4u * X.w; i0 < ntouched; i0 += 4u * X.nw) {
+        const uint32_t ng = min(4u, ntouched - i0);
+        size_t at = 0;
+        for (uint32_t gg = 0; gg < ng; ++gg) {
+            const uint32_t sh = shard_of(X.nq, pre, i0 + gg);
+            const size_t x = (size_t)sh * X.seg + (i0 + gg - readlane32(pre, sh));
+            if (g == gg) at = x;
+        }
+        const bool has = g < ng;
+        const uint32_t v = has ? A.touched[at] : 0u;
+        const uint32_t ts = has ? A.tstart[at] : 0u;
+        const uint32_t len = has ? A.llen[v] : 0u;
+        const uint64_t seg = (has ? A.loff[v] : 0ull) + ts;
+        if (has && sub < W) A.C[(size_t)v * W + sub] = 0;
+        const uint32_t tail = len - ts;
+        const bool here = tail >= 2u && tail <= 16u && sub < tail;
+        const uint32_t e = here ? A.arena[seg + sub] : ~0u - sub;  // distinct, above every entry
+        const uint32_t pos = row_rank32(e);
+        if (here && pos != sub) A.arena[seg + pos] = e;
+        uint64_t longer = ballot64(sub == 0 && tail > 16u);
+        while (longer) {
+            const uint32_t l = (uint32_t)__builtin_ctzll(longer);
+            longer &= longer - 1;
+            const uint32_t tg = readlane32(tail, l);
+            const uint32_t* ent = A.arena + readlane64(seg, l);
+            if (tg <= 64) {  // one round's entries are in order already
+                const uint32_t x = lane < tg ? ent[lane] : ~0u;
+                const uint32_t nx = (uint32_t)__shfl_down((int)x, 1, 64);
+                if (!ballot64(lane + 1 < tg && x >= nx)) continue;
+            }
+            if (lane < W) s_pres[lane] = 0;
+            wave_lds_sync();
+            for (uint32_t x = lane; x < tg; x += 64) {
+                const uint32_t k = (ent[x] >> 8) - ib;
+                s_dist[k] = (uint8_t)(ent[x] & 255u);
+                atomicOr((unsigned long long*)&s_pres[k >> 6], 1ull << (k & 63));
+            }
+            wave_lds_sync();
+            segment_emit(A, ib, readlane64(seg, l), s_pres, s_dist);
+            wave_lds_sync();
+        }
     }
 }
 
