@@ -23,6 +23,7 @@
 // L_out(u) with L_in(v); the kernels take the two lists' arrays apart.
 // With bit-parallel labels (Section 5.2) the answer is the smaller of the
 // merge and the BP bound; the group's lanes split the BP roots.
+#include <algorithm>
 #include <atomic>
 
 #include "pll_internal.h"
@@ -31,15 +32,16 @@ namespace {
 
 constexpr int kBlock = 256;
 
-// Bit-parallel bound of (u, v) over BP roots i = first, first + step, ...
-// (Section 5.2): d_i(u) + d_i(v), minus 2 when the S^-1 sets meet, else
-// minus 1 when S^-1 of one meets S^0 of the other.
+// The smaller of `best` and the bit-parallel bound of (u, v) over BP roots
+// i = first, first + step, ... (Section 5.2): d_i(u) + d_i(v), minus 2 when
+// the S^-1 sets meet, else minus 1 when S^-1 of one meets S^0 of the other.
+// The sets are 32 of a root's 34 bytes and take off 2 at most, so a root
+// whose sum is not below best + 2 does not read them.
 __device__ inline uint32_t bp_bound(const uint8_t* __restrict__ bpd, const ulonglong2* __restrict__ bps, uint32_t t,
-                                    uint32_t u, uint32_t v, uint32_t first, uint32_t step) {
-    uint32_t best = PLL_DIST_INF;
+                                    uint32_t u, uint32_t v, uint32_t first, uint32_t step, uint32_t best) {
     for (uint32_t i = first; i < t; i += step) {
         const uint32_t du = bpd[(size_t)u * t + i], dv = bpd[(size_t)v * t + i];
-        if (du == PLL_INF8 || dv == PLL_INF8) continue;
+        if (du == PLL_INF8 || dv == PLL_INF8 || (best != PLL_DIST_INF && du + dv >= best + 2u)) continue;
         const ulonglong2 su = bps[(size_t)u * t + i], sv = bps[(size_t)v * t + i];
         uint32_t td = du + dv;
         if (su.x & sv.x) td -= 2;
@@ -88,7 +90,7 @@ __global__ void __launch_bounds__(kBlock) k_query_lane(const uint64_t* __restric
                 }
             }
         }
-        if (BP && u < n && v < n) best = min(best, bp_bound(bpd, bps, bpt, u, v, 0, 1));
+        if (BP && u < n && v < n) best = bp_bound(bpd, bps, bpt, u, v, 0, 1, best);
         out[i] = best;
     }
 }
@@ -254,7 +256,11 @@ __global__ void __launch_bounds__(kBlock) k_query_group(const uint64_t* __restri
                 if (b_hi > 0) load_window<kEntriesV>(wb, b_lo, b_hi, gl, kb);
             }
         }
-        if (BP && u < n && v < n) best = min(best, bp_bound(bpd, bps, bpt, u, v, gl, G));
+        if (BP) {
+#pragma unroll
+            for (int s = G / 2; s >= 1; s >>= 1) best = min(best, (uint32_t)__shfl_xor((int)best, s, G));
+            if (u < n && v < n) best = bp_bound(bpd, bps, bpt, u, v, gl, G, best);
+        }
 #pragma unroll
         for (int s = G / 2; s >= 1; s >>= 1) best = min(best, (uint32_t)__shfl_xor((int)best, s, G));
         if (gl == 0) out[p] = best;
@@ -412,7 +418,7 @@ __global__ void __launch_bounds__(kBlock) k_query_wave(const uint64_t* __restric
                                                        const uint64_t* __restrict__ offv,
                                                        const uint32_t* __restrict__ entv,
                                                        const uint2* __restrict__ lbv, uint32_t n, uint64_t count,
-                                                       const uint32_t* __restrict__ qu,
+                                                       uint32_t per, const uint32_t* __restrict__ qu,
                                                        const uint32_t* __restrict__ qv, uint32_t* __restrict__ out,
                                                        const uint8_t* __restrict__ bpd,
                                                        const ulonglong2* __restrict__ bps, uint32_t bpt) {
@@ -423,16 +429,16 @@ __global__ void __launch_bounds__(kBlock) k_query_wave(const uint64_t* __restric
     const uint32_t oA = wv * 2 * kWinWords, oB = oA + kWinWords;  // the wave's windows, in words
     uint32_t* sa = s_win + oA;
     uint32_t* sb = s_win + oB;
-    // A wave takes groups of 64 consecutive pairs.  Lane l first gathers pair
-    // l's ids, list bounds and list offsets, so these dependent loads are in
-    // flight for all 64 pairs at once; the wave then merges the pairs one by
-    // one, reading their bounds from lane registers, and stores the 64
-    // answers together.
-    const uint64_t groups = (count + 63) / 64;
+    // A wave takes groups of `per` (up to 64) consecutive pairs.  Lane l first
+    // gathers pair l's ids, list bounds and list offsets, so these dependent
+    // loads are in flight for all pairs at once; the wave then merges the
+    // pairs one by one, reading their bounds from lane registers, and stores
+    // the answers together.
+    const uint64_t groups = (count + per - 1) / per;
     const uint64_t gstride = (uint64_t)gridDim.x * kWavesPerBlock;
     for (uint64_t g = blockIdx.x * kWavesPerBlock + wv; g < groups; g += gstride) {
-        const uint64_t p0 = g * 64;
-        const uint32_t np = (uint32_t)min<uint64_t>(64, count - p0);
+        const uint64_t p0 = g * per;
+        const uint32_t np = (uint32_t)min<uint64_t>(per, count - p0);
         const uint64_t pl = p0 + lane;
         uint32_t ul = 0, vl = 0;
         if (lane < np) {
@@ -523,7 +529,7 @@ __global__ void __launch_bounds__(kBlock) k_query_wave(const uint64_t* __restric
             }
             if (BP) {
                 const uint32_t u = readlane32(ul, k), v = readlane32(vl, k);
-                best = min(best, bp_bound(bpd, bps, bpt, u, v, lane, 64));
+                best = bp_bound(bpd, bps, bpt, u, v, lane, 64, best);
             }
             best = wave_min32_dpp(best);
             res = lane == k ? best : res;
@@ -532,14 +538,16 @@ __global__ void __launch_bounds__(kBlock) k_query_wave(const uint64_t* __restric
     }
 }
 
-// One pair at a time per wave, in groups of 64 pairs; waves loop over
-// groups.  Grid: 8x the workgroups that fit on the device at once (measured
+// One pair at a time per wave, in groups of up to 64 pairs; waves loop over
+// groups.  A call of few pairs is cut into groups of fewer, so that it has
+// four times the waves that fit at once (R-MAT-16, 1,000 pairs: 55 us in
+// groups of 64, below 9 us one by one; R-MAT-20, 300,000 pairs: 171 us at
+// once, 134 at four times, 143 at eight times the resident waves).  Grid: 8x the workgroups that fit on the device at once (measured
 // on a 2^20-vertex R-MAT index with 10^7 pairs: 8x 4.18 ms, 32x 4.22 ms,
 // 128x 4.28 ms).
 void launch_wave(const pll_index* idx, uint64_t count, const uint32_t* d_u, const uint32_t* d_v, uint32_t* d_out,
                  hipStream_t stream) {
     static std::atomic<uint64_t> cap_cache[64];
-    uint64_t blocks = ((count + 63) / 64 + kWavesPerBlock - 1) / kWavesPerBlock;
     const int dev = idx->device;
     uint64_t cap = dev >= 0 && dev < 64 ? cap_cache[dev].load(std::memory_order_relaxed) : 0;
     if (cap == 0) {
@@ -553,17 +561,20 @@ void launch_wave(const pll_index* idx, uint64_t count, const uint32_t* d_u, cons
         cap = (uint64_t)per_cu * cus * 8;
         if (dev >= 0 && dev < 64) cap_cache[dev].store(cap, std::memory_order_relaxed);
     }
+    const uint64_t waves = cap / 8 * kWavesPerBlock * 4;
+    const uint32_t per = (uint32_t)std::min<uint64_t>(64, (count + waves - 1) / waves);
+    uint64_t blocks = ((count + per - 1) / per + kWavesPerBlock - 1) / kWavesPerBlock;
     if (blocks > cap) blocks = cap;
     const uint64_t* offu = idx->directed ? idx->d_off_out : idx->d_off;
     const uint32_t* entu = idx->directed ? idx->d_ent_out : idx->d_ent;
     const uint2* lbu = idx->directed ? idx->d_lb_out : idx->d_lb;
     if (idx->info.bp_roots)
         k_query_wave<true><<<(uint32_t)blocks, kBlock, 0, stream>>>(offu, entu, lbu, idx->d_off, idx->d_ent, idx->d_lb,
-                                                                    idx->n, count, d_u, d_v, d_out, idx->d_bp_dist,
+                                                                    idx->n, count, per, d_u, d_v, d_out, idx->d_bp_dist,
                                                                     idx->d_bp_sets, idx->info.bp_roots);
     else
         k_query_wave<false><<<(uint32_t)blocks, kBlock, 0, stream>>>(offu, entu, lbu, idx->d_off, idx->d_ent,
-                                                                     idx->d_lb, idx->n, count, d_u, d_v, d_out,
+                                                                     idx->d_lb, idx->n, count, per, d_u, d_v, d_out,
                                                                      nullptr, nullptr, 0);
 }
 
@@ -604,6 +615,13 @@ void launch_group(const pll_index* idx, uint64_t count, const uint32_t* d_u, con
                                                                           count, d_u, d_v, d_out, nullptr, nullptr, 0);
 }
 
+// Calls of up to this many pairs take a wave per pair whatever the mean label
+// (when the index leaves the lanes open): they do not fill the device, so the
+// longest pair's chain of windows decides.  Mean labels of 4 to 43 entries,
+// 8,000 pairs: 8.4-9.0 us, 14-44 us with groups; 30,000 pairs: 14-26 us
+// against 18-30; from 100,000 pairs on the groups win.
+constexpr uint64_t kSmallCall = 32768;
+
 // Lanes per pair when the index leaves it open: the window (4 entries per
 // lane) should hold about one average label.
 uint32_t query_lanes_auto(const pll_index* idx) {
@@ -611,8 +629,14 @@ uint32_t query_lanes_auto(const pll_index* idx) {
     // a whole wave per pair from a mean label of 32 entries on (measured on
     // R-MAT indexes of 2^14..2^20 vertices, mean labels of 44..241 entries:
     // the wave kernel was fastest at every size); smaller groups below
-    if (mean >= 32) return 64;
-    uint32_t g = 4;
+    // With bit-parallel roots every pair has the bound to compute, for which
+    // a wave has more lanes than roots: groups win up to twice that mean
+    // (1,000,000 pairs, mean 38: 254 us with 16 lanes, 307 with 64; mean 43:
+    // 343 and 446), and from 16 roots on 8 lanes share them (mean 17, 16
+    // roots: 157 us, 172 with 4 lanes; mean 4.8, 64 roots: 234 and 391).
+    const bool bp = idx->info.bp_roots != 0;
+    if (mean >= (bp ? 64u : 32u)) return 64;
+    uint32_t g = idx->info.bp_roots >= 16 ? 8 : 4;
     while (g < 32 && 4ull * g < mean) g *= 2;
     return g;
 }
@@ -626,7 +650,8 @@ uint32_t pll_query_lanes(const pll_index* idx) {
 int pll_query_launch(const pll_index* idx, uint64_t count, const uint32_t* d_u, const uint32_t* d_v,
                      uint32_t* d_out, hipStream_t stream) {
     if (count == 0) return PLL_OK;
-    const uint32_t g = pll_query_lanes(idx);
+    uint32_t g = pll_query_lanes(idx);
+    if (idx->query_lanes == 0 && count <= kSmallCall) g = 64;
     switch (g) {
         case 1: {
             uint64_t blocks = (count + kBlock - 1) / kBlock;
