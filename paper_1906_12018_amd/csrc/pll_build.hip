@@ -355,7 +355,7 @@ __device__ inline void batch_init_planes(const BuildArgs& A, const pll::Exec& X,
     const uint32_t rows = ib + bs;
     for (uint32_t h = threadIdx.x; h < min(rows, pll::kInitHot); h += kInitBlock) s_hot[h] = 0;
     __syncthreads();
-    pll::phase_batch_init<true>(A, X, ib, bs, bstamp, s_hot);
+    pll::phase_batch_init<true, true>(A, X, ib, bs, bstamp, s_hot);
     __syncthreads();
     pll::plane_flush(A, k0, rows, s_hot);
 }
@@ -368,7 +368,7 @@ __global__ void __launch_bounds__(kInitBlock) k_batch_init_planes(BuildArgs A, u
 __global__ void __launch_bounds__(kBlock) k_push(BuildArgs A, uint32_t ib, uint32_t p, uint32_t nact, uint32_t rstamp,
                                                  uint32_t bstamp) {
     PhaseStats st;
-    pll::phase_push(A, grid_exec(A), ib, p, nact, rstamp, bstamp, st);
+    pll::phase_push(A, grid_exec(A), A.msgs, A.recv, ib, p, nact, rstamp, bstamp, st);
     const unsigned long long v[1] = {st.edges};
     const int which[1] = {PLL_ST_EDGES};
     block_add_stats<1>(A.ctr, v, which);
@@ -389,7 +389,7 @@ __global__ void __launch_bounds__(kBlock) k_push2(BuildArgs A0, BuildArgs A1, ui
     const uint32_t nb = gridDim.x / 2, side = blockIdx.x >= nb ? 1u : 0u;
     const BuildArgs& A = side ? A1 : A0;
     PhaseStats st;
-    pll::phase_push(A, side_exec(A, side * nb, nb), ib, 0, nact, rstamp, bstamp, st);
+    pll::phase_push(A, side_exec(A, side * nb, nb), A.msgs, A.recv, ib, 0, nact, rstamp, bstamp, st);
     const unsigned long long v[1] = {st.edges};
     const int which[1] = {PLL_ST_EDGES};
     block_add_stats<1>(A.ctr, v, which);
@@ -1642,18 +1642,15 @@ int build_attempt(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, const uint3
             // the first round's receivers push the batch's densest deltas along
             // high-degree rows, so gathering pays off from fewer of them
             const uint32_t pull = pull_ok && next_est * (j == 1 ? kPullFrac1 : kPullFrac) >= n ? 1u : 0u;
-            const pll::NextRound nr{mbuf[(j + 1) & 1u], rbuf[(j + 1) & 1u], (j - 1) % 3, j % 3, (j + 1) % 3, j & 1u,
+            const pll::NextRound nr{mbuf[j & 1u], rbuf[j & 1u], mbuf[(j + 1) & 1u], rbuf[(j + 1) & 1u], (j - 1) % 3, j % 3, (j + 1) % 3, j & 1u,
                                     rstamp + 1, bstamp, pull};
             ++rstamp;
-            BuildArgs Aj = A;
-            Aj.msgs = mbuf[j & 1u];
-            Aj.recv = rbuf[j & 1u];
             if (P.on) k_delay<<<1, 1, 0, s>>>(delay_ticks);
             hipEvent_t r1 = P.mark();
             // rounds with many receivers check four per wave (phase_check4)
             const bool pack = ((flags & PLL_FLAG_PACK4) || next_est >= kPackMin) && j <= pll::kSmallT;
             const uint64_t waves = pack ? next_est / 4 + 512 : next_est + 2048;
-            dispatch_check_push(blocks_for_waves(std::min<uint64_t>(n, waves)), s, Aj, ib, bs, j, nr, relaxed, pack);
+            dispatch_check_push(blocks_for_waves(std::min<uint64_t>(n, waves)), s, A, ib, bs, j, nr, relaxed, pack);
             P.span(PLL_PHASE_CHECK, r1, P.mark(), 1);
             TRY_HIP(hipGetLastError());
             if (pull) {
@@ -2063,19 +2060,15 @@ int build_attempt_directed(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, co
                 for (int d = 0; d < 2; ++d) A[d].Tchk = A[d ^ 1].T;
             }
             pll::NextRound nr[2];
-            BuildArgs Aj[2];
             uint32_t nb[2] = {0, 0};
             for (int d = 0; d < 2; ++d) {
-                nr[d] = pll::NextRound{mbuf[d][(j + 1) & 1u], rbuf[d][(j + 1) & 1u], (j - 1) % 3, j % 3, (j + 1) % 3,
+                nr[d] = pll::NextRound{mbuf[d][j & 1u], rbuf[d][j & 1u], mbuf[d][(j + 1) & 1u], rbuf[d][(j + 1) & 1u], (j - 1) % 3, j % 3, (j + 1) % 3,
                                        j & 1u, rstamp + 1, bstamp};
-                Aj[d] = A[d];
-                Aj[d].msgs = mbuf[d][j & 1u];
-                Aj[d].recv = rbuf[d][j & 1u];
                 if (live[d]) nb[d] = blocks_for_waves(std::min<uint64_t>(n, next_est[d] + 2048));
             }
             ++rstamp;
             hipEvent_t r1 = P.mark();
-            dispatch_check_push2(nb[0], nb[1], s, Aj[0], nr[0], Aj[1], nr[1], ib, bs, j);
+            dispatch_check_push2(nb[0], nb[1], s, A[0], nr[0], A[1], nr[1], ib, bs, j);
             P.span(PLL_PHASE_CHECK, r1, P.mark(), 1);
             TRY_HIP(hipGetLastError());
             rc = read_both();

@@ -34,10 +34,13 @@ constexpr uint32_t kMaxGang = 16;
 struct alignas(128) GangCtl {
     uint32_t bar_count, bar_gen;
     uint32_t err[2];        // sticky error words, one per barrier parity
-    uint32_t round_acc[2];  // entries accepted in the current round, by round parity
-    uint32_t pad0[2];
+    // entries accepted and heavy items queued in round j, in slot j % 3: the
+    // words are read after the round's only barrier, so member 0 may clear a
+    // slot no sooner than two barriers later (in the phase of round j + 2)
+    uint32_t round_acc[3];
+    uint32_t round_heavy[3];
     unsigned long long out_base;
-    uint32_t pad1[22];
+    uint32_t pad1[20];
     Shard shards[kMaxGang];
 };
 static_assert(sizeof(GangCtl) == 128 * (kMaxGang + 1), "layout");
@@ -53,6 +56,10 @@ struct GraphJob {
     uint2* out_lb;      // [n] list bounds by vertex id (first and last hub rank; see pll_index)
     GangCtl* gc;
     uint32_t gang;      // workgroups building this graph
+    // the second message buffer and receiver list of the fused rounds (round
+    // j's live in buffer j & 1; A.msgs and A.recv are buffer 0)
+    uint64_t* msgs1;
+    uint32_t* recv1;
 };
 
 struct GraphResult {
@@ -266,6 +273,9 @@ __global__ void __launch_bounds__(kMultiBlock) k_multi_build(const GraphJob* __r
         uint32_t rstamp = 0, bstamp = 0;
         unsigned long long batches = 0, rounds = 0;
         bool failed = false;
+        // bit planes until a round outgrows them; the recheck's only form is
+        // the byte table
+        bool planes = !recheck;
         for (uint32_t ib = 0; ib < n && !failed; ib += b) {
             const uint32_t bs = min(b, n - ib);
             ++bstamp;
@@ -273,37 +283,66 @@ __global__ void __launch_bounds__(kMultiBlock) k_multi_build(const GraphJob* __r
             if (r == 0) {
                 if (tid < G) {
                     Shard& q = gc->shards[tid];
-                    q.recv[0] = q.recv[1] = 0;
+                    q.recv[0] = q.recv[1] = q.recv[2] = 0;
                     q.hq[0] = q.hq[1] = 0;
                     q.touched = 0;
                 }
-                if (tid == 0) gc->round_acc[0] = gc->round_acc[1] = 0;
+                if (tid < 3) gc->round_acc[tid] = gc->round_heavy[tid] = 0;
             }
             if (gang_sync(gc, G, k, ctr, spin_limit, &s_flag)) { failed = true; break; }
-            pll::phase_batch_init(A, X, ib, bs, bstamp);
+            if (planes)
+                pll::phase_batch_init<true>(A, X, ib, bs, bstamp);
+            else
+                pll::phase_batch_init(A, X, ib, bs, bstamp);
             if (gang_sync(gc, G, k, ctr, spin_limit, &s_flag)) { failed = true; break; }
-            uint32_t p = 0, nact = bs;
+            ++rstamp;
+            pll::phase_push(A, X, J.msgs1, J.recv1, ib, 0, bs, rstamp, bstamp, st);
+            if (gang_sync(gc, G, k, ctr, spin_limit, &s_flag)) { failed = true; break; }
+            // fused rounds (see phase_check4): the check of round j delivers
+            // round j+1 as well, so a round has one barrier
             for (uint32_t j = 1;; ++j) {
-                ++rstamp;
                 ++rounds;
-                pll::phase_push(A, X, ib, p, nact, rstamp, bstamp, st);
+                if (planes && j > PLL_PLANES + 1) {
+                    // the planes' memory becomes the byte table (planes_to_bytes)
+                    planes = false;
+                    uint4* t = reinterpret_cast<uint4*>(A.T);
+                    const size_t words = (size_t)n * A.bstride / sizeof(uint4);
+                    for (size_t i = X.w * 64u + lane; i < words; i += X.nw * 64u) t[i] = make_uint4(~0u, ~0u, ~0u, ~0u);
+                    if (gang_sync(gc, G, k, ctr, spin_limit, &s_flag)) { failed = true; break; }
+                    pll::phase_table_fill(A, X, ib, bs);
+                    if (gang_sync(gc, G, k, ctr, spin_limit, &s_flag)) { failed = true; break; }
+                }
+                const pll::NextRound nr{j & 1u ? J.msgs1 : A.msgs, j & 1u ? J.recv1 : A.recv,
+                                        j & 1u ? A.msgs : J.msgs1, j & 1u ? A.recv : J.recv1,
+                                        (j - 1) % 3, j % 3, (j + 1) % 3, j & 1u, rstamp + 1, bstamp, 0u};
+                ++rstamp;
+                // round j+1's slot was last read after round j-2's barrier
+                if (r == 0 && tid == 0) gc->round_acc[(j + 1) % 3] = gc->round_heavy[(j + 1) % 3] = 0;
+                const uint32_t acc0 = st.acc;
+                if (planes)
+                    pll::phase_check4<WM, false, true>(A, X, ib, bs, j, false, st, nr);
+                else
+                    pll::phase_check4<WM, false, false>(A, X, ib, bs, j, relaxed, st, nr);
+                if (lane == 0 && st.acc != acc0) atomicAdd(&gc->round_acc[j % 3], st.acc - acc0);
+                __syncthreads();
+                if (tid == 0 && load_agent(&gc->shards[r].hq[nr.hout])) atomicOr(&gc->round_heavy[j % 3], 1u);
                 if (gang_sync(gc, G, k, ctr, spin_limit, &s_flag)) { failed = true; break; }
-                // the counter of round j+1 was last read after round j-1
-                if (r == 0 && tid == 0) gc->round_acc[(j + 1) & 1u] = 0;
-                const unsigned long long acc0 = st.acc;
-                pll::phase_check<WM, false, false, true>(A, X, ib, bs, j, p, relaxed, st);
-                if (lane == 0 && st.acc != acc0) atomicAdd(&gc->round_acc[j & 1u], (uint32_t)(st.acc - acc0));
-                if (gang_sync(gc, G, k, ctr, spin_limit, &s_flag)) { failed = true; break; }
-                if (load_agent(&gc->round_acc[j & 1u]) == 0) break;
-                uint32_t cnt = 0;
-                for (uint32_t s = 0; s < G; ++s) cnt += load_agent(&gc->shards[s].recv[p]);
-                nact = cnt;
-                p ^= 1u;
+                if (load_agent(&gc->round_acc[j % 3]) == 0) break;
+                if (load_agent(&gc->round_heavy[j % 3])) {
+                    pll::phase_push_heavy(A, X, ib, nr.hout, nr.rout, nr.msgs, nr.recv, nr.rstamp, bstamp, st);
+                    if (gang_sync(gc, G, k, ctr, spin_limit, &s_flag)) { failed = true; break; }
+                }
             }
             if (failed) break;
-            pll::phase_batch_end<WM>(A, X, ib, bs, recheck, s_pres[wv], s_dist[wv], nullptr, st);
+            if (recheck)
+                pll::phase_batch_end<WM>(A, X, ib, bs, true, s_pres[wv], s_dist[wv], nullptr, st);
+            else
+                pll::phase_batch_end4(A, X, ib, s_pres[wv], s_dist[wv]);
             if (gang_sync(gc, G, k, ctr, spin_limit, &s_flag)) { failed = true; break; }
-            pll::phase_clear_table(A, X, ib, bs);
+            if (planes)
+                pll::phase_clear_table<true>(A, X, ib, bs);
+            else
+                pll::phase_clear_table(A, X, ib, bs);
             if (gang_sync(gc, G, k, ctr, spin_limit, &s_flag)) { failed = true; break; }
         }
         if (failed) continue;
@@ -438,10 +477,13 @@ hipError_t dispatch_multi(uint32_t W, uint32_t grid, hipStream_t s, const GraphJ
     }
 }
 
-double work_estimate(const pll_graph_desc& d) { return (double)d.nnz * std::log2(d.n + 2.0) + d.n; }
+// Fitted to graphs built by one workgroup alone: n = 20,000 with 320,000 and
+// 80,000 CSR entries 200 and 79 ms, 10,000 with 100,000 48 ms, 5,000 with
+// 50,000 14.6 ms.  (CSR entries times log n, the former estimate, gave the
+// large graphs too few workgroups: 256 graphs 77 ms, 52 ms with this one.)
+double work_estimate(const pll_graph_desc& d) { return d.n * (std::pow((double)d.nnz, 2.0 / 3.0) + 1.0); }
 
-// Gang sizes: a graph's share of the estimated work (CSR entries times
-// log n, plus n) times the resident workgroups, times gang_scale percent,
+// Gang sizes: a graph's share of the estimated work times the resident workgroups, times gang_scale percent,
 // clamped to [1, min(kMaxGang, resident, max_gang)].
 std::vector<uint32_t> gang_sizes(uint32_t count, const pll_graph_desc* graphs, uint32_t resident, uint32_t scale_pct,
                                  uint32_t max_gang) {
@@ -502,8 +544,8 @@ int multi_attempt(uint32_t count, const pll_graph_desc* graphs, uint32_t b, uint
         return at;
     };
     struct Off {
-        uint64_t gc, loff, llen, lcap, C, msgs, rowmask, recv_stamp, touch_stamp, T;
-        uint64_t rank, rrow, rcol, act_v0, act_v1, ad0, ad1, hq0, hq1, recv, touched, tstart;
+        uint64_t gc, loff, llen, lcap, C, msgs, msgs1, rowmask, recv_stamp, touch_stamp, T;
+        uint64_t rank, rrow, rcol, act_v0, act_v1, ad0, ad1, hq0, hq1, recv, recv1, touched, tstart;
     };
     std::vector<Off> off(count);
     for (uint32_t g = 0; g < count; ++g) {
@@ -516,6 +558,7 @@ int multi_attempt(uint32_t count, const pll_graph_desc* graphs, uint32_t b, uint
         o.lcap = take(zb, 4 * n);
         o.C = take(zb, 8 * n * W);
         o.msgs = take(zb, 8 * n * W);
+        o.msgs1 = take(zb, 8 * n * W);
         o.rowmask = take(zb, 8 * n);
         o.recv_stamp = take(zb, 4 * n);
         o.touch_stamp = take(zb, 4 * (n + 1));
@@ -530,6 +573,7 @@ int multi_attempt(uint32_t count, const pll_graph_desc* graphs, uint32_t b, uint
         o.hq0 = take(ob, 8 * hq_seg * gs);
         o.hq1 = take(ob, 8 * hq_seg * gs);
         o.recv = take(ob, 4 * n * gs);
+        o.recv1 = take(ob, 4 * n * gs);
         o.touched = take(ob, 4 * n * gs);
         o.tstart = take(ob, 4 * n * gs);
         jobs[g] = GraphJob{};
@@ -614,6 +658,10 @@ int multi_attempt(uint32_t count, const pll_graph_desc* graphs, uint32_t b, uint
         A.touch_stamp = (uint32_t*)(zp + o.touch_stamp);
         A.T = (uint8_t*)(tp + o.T);
         A.Tchk = A.T;
+        A.P = (uint64_t*)A.T;  // bit planes in the same memory (planes_to_bytes)
+        A.Pchk = A.P;
+        J.msgs1 = (uint64_t*)(zp + o.msgs1);
+        J.recv1 = (uint32_t*)(op + o.recv1);
         A.rmchk = A.rowmask;
         A.rw = nullptr;  // unweighted, no bit-parallel labels
         A.D = nullptr;
@@ -662,7 +710,7 @@ int multi_attempt(uint32_t count, const pll_graph_desc* graphs, uint32_t b, uint
             break;
         }
         k_fill32<<<2048, 256, 0, s>>>((uint32_t*)Z.p, zb / 4, 0u);
-        k_fill32<<<2048, 256, 0, s>>>((uint32_t*)TT.p, tb / 4, 0xFFFFFFFFu);
+        k_fill32<<<2048, 256, 0, s>>>((uint32_t*)TT.p, tb / 4, flags & PLL_FLAG_RECHECK ? 0xFFFFFFFFu : 0u);
         k_fill32<<<64, 256, 0, s>>>((uint32_t*)DC.p, sizeof(DevCounters) / 4, 0u);
         k_fill32<<<64, 256, 0, s>>>((uint32_t*)RS.p, sizeof(GraphResult) * count / 4, 0u);
         hipError_t le = dispatch_multi(W, grid, s, (const GraphJob*)JB.p, (const uint2*)SL.p, (uint32_t)slots.size(),

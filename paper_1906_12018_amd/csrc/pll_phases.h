@@ -370,14 +370,14 @@ __device__ inline void plane_set(const BuildArgs& A, uint32_t h, uint32_t d, uin
 // (u,0), L(u) -> H(u).
 // The initial active list holds batch vertex u_k in slot k.
 //
-// With planes, a workgroup runs the kInitRoots consecutive roots of one
+// With planes and HOT, a workgroup runs the kInitRoots consecutive roots of one
 // k / kInitRoots, one per wave, and collects the distances 1 and 2 of the
 // rows h < kInitHot in s_hot: bit k % kInitRoots of s_hot[h] is plane 1's
 // bit, bit 16 + k % kInitRoots plane 2's.  plane_flush then writes them out.
 constexpr uint32_t kInitHot = 4096;
 constexpr uint32_t kInitRoots = 16;
 
-template <bool PLANES = false>
+template <bool PLANES = false, bool HOT = false>
 __device__ inline void phase_batch_init(const BuildArgs& A, const Exec& X, uint32_t ib, uint32_t bs, uint32_t bstamp,
                                         uint32_t* s_hot = nullptr) {
     const uint32_t lane = lane_id();
@@ -433,7 +433,7 @@ __device__ inline void phase_batch_init(const BuildArgs& A, const Exec& X, uint3
                     const uint32_t h = e[c] >> 8;
                     if (PLANES) {
                         const uint32_t d = e[c] & 255u;
-                        if (d <= 2 && h < kInitHot)
+                        if (HOT && d <= 2 && h < kInitHot)
                             atomicOr(&s_hot[h], (d == 1 ? 0x10001u : 0x10000u) << (k % kInitRoots));
                         else
                             plane_set(A, h, d, k);
@@ -591,9 +591,12 @@ __device__ inline void phase_push_heavy(const BuildArgs& A, const Exec& X, uint3
     }
 }
 
-// Where a fused check delivers the next round: its message buffer, receiver
-// queue and counters, the round stamps, and whether that round is pulled.
+// Where a fused check takes its round from (message buffer and receiver
+// list) and delivers the next one: that round's message buffer, receiver
+// queue and counters, the round stamps, and whether it is pulled.
 struct NextRound {
+    uint64_t* msgs_in;
+    uint32_t* recv_in;
     uint64_t* msgs;
     uint32_t* recv;
     uint32_t rin, rout, rclr, hout;
@@ -732,13 +735,14 @@ __device__ inline void phase_pull_items(const BuildArgs& A, const Exec& X, uint2
     }
 }
 
-// Scatter phase of Algorithm 4 over active list p (nact slots).
+// Scatter phase of Algorithm 4 over active list p (nact slots) into msgs and
+// receiver queue p stored in recv.
 // Batch vertex u_k may be sent to v only when u_k outranks v (rank ib + k
 // < v) and C(v) does not hold it yet.  Slots whose delta is empty are
 // skipped; rows longer than kHeavy were queued as items and are spread over
 // every wave after the per-slot pass.
-__device__ inline void phase_push(const BuildArgs& A, const Exec& X, uint32_t ib, uint32_t p, uint32_t nact,
-                                  uint32_t rstamp, uint32_t bstamp, PhaseStats& st) {
+__device__ inline void phase_push(const BuildArgs& A, const Exec& X, uint64_t* msgs, uint32_t* recv, uint32_t ib,
+                                  uint32_t p, uint32_t nact, uint32_t rstamp, uint32_t bstamp, PhaseStats& st) {
     const uint32_t lane = lane_id();
     if (X.zero_i < X.nq) X.qs[X.zero_i].hq[p ^ 1u] = 0;
     const uint32_t* act_v = A.act_v[p];
@@ -751,10 +755,10 @@ __device__ inline void phase_push(const BuildArgs& A, const Exec& X, uint32_t ib
         const uint64_t beg = A.rrow[a], end = A.rrow[a + 1];
         if (end - beg > kHeavy) continue;
         if (lane == 0) st.edges += end - beg;
-        push_edges(A, X, A.msgs, A.recv, ib, p, rstamp, bstamp, dl, nz, beg, end,
+        push_edges(A, X, msgs, recv, ib, p, rstamp, bstamp, dl, nz, beg, end,
                    beg + lane < end ? A.rcol[beg + lane] : 0u);
     }
-    phase_push_heavy(A, X, ib, p, p, A.msgs, A.recv, rstamp, bstamp, st);
+    phase_push_heavy(A, X, ib, p, p, msgs, recv, rstamp, bstamp, st);
 }
 
 // Bit-parallel bound (Section 5.2) of every candidate in `mine` at v for
@@ -979,7 +983,7 @@ __device__ inline uint64_t prune_planes(const BuildArgs& A, uint64_t off, uint32
 // delta L for round j+1 right away (rows up to kHeavy; longer rows become
 // heavy items for a separate launch), into the other message buffer nr->msgs
 // and receiver queue nr->rout, whose entries go to nr->recv (this round's
-// receivers are read from A.recv, so the two lists never share storage).
+// receivers are read from nr->recv_in, so the two lists never share storage).
 // C(r) of a neighbour may not hold this round's arrivals yet when the push
 // reads it, so the check filters its messages by C(v) itself.  Receiver
 // counters rotate over three (this round's nr->rin = p, the next round's,
@@ -992,6 +996,8 @@ __device__ inline void phase_check(const BuildArgs& A, const Exec& X, uint32_t i
     const uint32_t lane = lane_id();
     const uint32_t W = A.W;
     const uint32_t q = FUSE ? nr->hout : p ^ 1u;
+    uint64_t* const msgs = FUSE ? nr->msgs_in : A.msgs;
+    const uint32_t* const recv = FUSE ? nr->recv_in : A.recv;
     uint32_t pre;
     const uint32_t nrecv = shard_prefix(lane < X.nq ? X.qs[lane].recv[p] : 0u, pre);
     // clear the counts the next launch appends to
@@ -1005,12 +1011,12 @@ __device__ inline void phase_check(const BuildArgs& A, const Exec& X, uint32_t i
     }
     for (uint32_t i = X.w; i < nrecv; i += X.nw) {
         const uint32_t s = shard_of(X.nq, pre, i);
-        const uint32_t v = A.recv[(size_t)s * X.seg + (i - readlane32(pre, s))];
+        const uint32_t v = recv[(size_t)s * X.seg + (i - readlane32(pre, s))];
         uint64_t mine = 0;
         if (lane < W) {
             const size_t at = (size_t)v * W + lane;
-            mine = A.msgs[at];
-            A.msgs[at] = 0;
+            mine = msgs[at];
+            msgs[at] = 0;
             if (FUSE) mine &= ~A.C[at];
             A.C[at] |= mine;
         }
@@ -1262,12 +1268,12 @@ __device__ inline void phase_check4(const BuildArgs& A, const Exec& X, uint32_t 
         }
         const bool has = g < ng;
         const uint32_t i = i0 + g;
-        const uint32_t v = has ? A.recv[slot] : 0u;
+        const uint32_t v = has ? nr.recv_in[slot] : 0u;
         uint64_t mine = 0;
         if (has && sub < W) {
             const size_t at = (size_t)v * W + sub;
-            mine = A.msgs[at];
-            A.msgs[at] = 0;
+            mine = nr.msgs_in[at];
+            nr.msgs_in[at] = 0;
             mine &= ~A.C[at];
             A.C[at] |= mine;
         }

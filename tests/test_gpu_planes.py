@@ -74,3 +74,21 @@ def test_noalloc_rounds_around_the_last_plane(length, b):
     assert np.array_equal(off.cpu().numpy().view(np.uint64), want.offsets)
     assert np.array_equal(hubs.cpu().numpy().view(np.uint32), want.hubs_as_ids(order))
     assert np.array_equal(dists.cpu().numpy(), want.dist)
+
+
+@pytest.mark.parametrize("flags", [0, pll.FLAG_RECHECK])
+@pytest.mark.parametrize("b,max_gang", [(64, 1), (190, 3), (1024, 16)])
+def test_many_graphs_around_the_last_plane(b, max_gang, flags):
+    # graphs that stay on the planes beside graphs that leave them, and rows
+    # long enough to be pushed as items of their own
+    graphs = [tailed(k) for k in (1, PLANES, PLANES + 1, PLANES + 2, 40)] + [
+        synth.path_graph(200), synth.star_graph(3000), synth.ba_graph(2500, 4, 3), synth.disjoint_union(
+            synth.star_graph(2100), synth.path_graph(30))]
+    orders = [synth.degree_order(g) for g in graphs]
+    idxs = pll.build_labels_batched([to_dev(g, o) for g, o in zip(graphs, orders)], batch_size=b, flags=flags,
+                                    gang_scale=1000, max_gang=max_gang)
+    for g, o, idx in zip(graphs, orders, idxs):
+        want = oracle.pll_labels(g, o)
+        assert_labels_equal(idx, want, o)
+        check_counters(idx, g, o, b, want)
+        idx.free()
