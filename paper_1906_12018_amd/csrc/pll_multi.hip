@@ -1,10 +1,11 @@
 // Many independent graphs in one persistent-kernel launch (captured in a
 // hipGraph).  Every graph is built by a gang of G workgroups (G = 1 for
 // small graphs, more for large ones, in proportion to the graph's share of
-// the estimated work).  Workgroups take (graph, member) slots from one list
-// ordered by decreasing graph size, so a gang's members join in order and a
-// gang always completes: the kernel is launched with no more workgroups than
-// can be resident and no gang is larger than that.  Inside a gang the phases
+// the estimated work).  Workgroups take (graph, member) slots from lists (one
+// per XCD in large launches) ordered by decreasing graph size, so a gang's
+// members join in order and a gang always completes: the kernel is launched
+// with no more workgroups than can be resident and no gang is larger than
+// that.  Inside a gang the phases
 // of pll_phases.h run over all G x 16 waves, with queue counters in per-graph
 // global shards (one per member) and a gang barrier between phases; a gang of
 // one only uses __syncthreads.  Member 0 also checks the input, relabels to
@@ -68,13 +69,25 @@ struct GraphResult {
     unsigned long long batches, rounds, cand, acc, edges, read, table, removed, cost_pos, cost_neg;
 };
 
+// The slots are cut into queues (queue q holds slots [qbeg[q], qbeg[q + 1])).
+constexpr uint32_t kQueues = 8;  // one per XCD
+
 struct MultiCtl {
-    uint32_t next_slot;
-    uint32_t spin_limit;
-    uint32_t pad[30];
     unsigned long long out_top;
     unsigned long long out_cap;
+    uint32_t spin_limit;
+    uint32_t queues;  // 1 or kQueues
+    uint32_t qbeg[kQueues + 1];
+    uint32_t pad[17];
+    struct alignas(128) {
+        uint32_t taken;
+    } q[kQueues];
 };
+
+// The XCD this wave runs on (hardware register XCC_ID).
+__device__ inline uint32_t xcd_id() {
+    return __builtin_amdgcn_s_getreg((31 << 11) | 20) % kQueues;
+}
 
 // Exclusive prefix sums of in[0..n) into out[0..n] by one workgroup.
 __device__ void wg_scan(const uint32_t* in, uint32_t n, uint64_t* out, uint64_t* s_wsum, uint64_t* s_carry) {
@@ -173,8 +186,24 @@ __global__ void __launch_bounds__(kMultiBlock) k_multi_build(const GraphJob* __r
     const bool relaxed = (flags & PLL_FLAG_RELAXED) != 0;
     const uint32_t spin_limit = ctl->spin_limit;
 
+    const uint32_t queues = ctl->queues;
+    const uint32_t home = queues > 1 ? xcd_id() : 0u;
+
     for (;;) {
-        if (tid == 0) s_slot = atomicAdd(&ctl->next_slot, 1u);
+        if (tid == 0) {
+            // the next slot of the own XCD's queue, then of the others
+            s_slot = nslots;
+            for (uint32_t i = 0; i < queues; ++i) {
+                const uint32_t q = (home + i) % queues;
+                const uint32_t beg = ctl->qbeg[q], cnt = ctl->qbeg[q + 1] - beg;
+                if (load_agent(&ctl->q[q].taken) >= cnt) continue;
+                const uint32_t at = atomicAdd(&ctl->q[q].taken, 1u);
+                if (at < cnt) {
+                    s_slot = beg + at;
+                    break;
+                }
+            }
+        }
         __syncthreads();
         const uint32_t si = s_slot;
         __syncthreads();
@@ -592,9 +621,29 @@ int multi_attempt(uint32_t count, const pll_graph_desc* graphs, uint32_t b, uint
     std::iota(gorder.begin(), gorder.end(), 0u);
     std::stable_sort(gorder.begin(), gorder.end(),
                      [&](uint32_t a, uint32_t c) { return work_estimate(graphs[a]) > work_estimate(graphs[c]); });
+    // One queue per XCD when the launch is large enough: a gang's members
+    // then share an L2, and its message words and counters do not move
+    // between XCDs.  A queue's workgroups finish it, then help the others.
+    // In each queue at most one gang is partly joined, so at most
+    // kQueues * (largest gang - 1) workgroups wait for members; with more in
+    // the launch one is always free to join, whatever XCDs they run on.
+    const uint32_t grid = std::min<uint32_t>(std::accumulate(G.begin(), G.end(), 0u), (uint32_t)resident);
+    const uint32_t max_g = *std::max_element(G.begin(), G.end());
+    MultiCtl hctl{};
+    hctl.queues = grid >= kQueues * max_g ? kQueues : 1u;
+    std::vector<std::vector<uint2>> queue(hctl.queues);
+    std::vector<double> load(hctl.queues, 0.0);
+    for (uint32_t g : gorder) {  // the least loaded queue takes the next largest graph
+        const uint32_t q = (uint32_t)(std::min_element(load.begin(), load.end()) - load.begin());
+        load[q] += work_estimate(graphs[g]);
+        for (uint32_t m = 0; m < G[g]; ++m) queue[q].push_back(make_uint2(g, m));
+    }
     std::vector<uint2> slots;
-    for (uint32_t g : gorder)
-        for (uint32_t m = 0; m < G[g]; ++m) slots.push_back(make_uint2(g, m));
+    for (uint32_t q = 0; q < kQueues; ++q) {
+        hctl.qbeg[q] = (uint32_t)slots.size();
+        if (q < hctl.queues) slots.insert(slots.end(), queue[q].begin(), queue[q].end());
+    }
+    hctl.qbeg[kQueues] = (uint32_t)slots.size();
 
     Buf Z, TT, O, JB, SL, RS, CT, DC, AR;
     for (Buf* bf : {&Z, &TT, &O, &JB, &SL, &RS, &CT, &DC, &AR}) bf->s = &SG.s;
@@ -688,7 +737,6 @@ int multi_attempt(uint32_t count, const pll_graph_desc* graphs, uint32_t b, uint
         J.out_off = out_offs[g];
         J.out_lb = out_lbs[g];
     }
-    MultiCtl hctl{};
     hctl.out_cap = out_cap;
     hctl.spin_limit = 1u << 22;  // a few seconds at most per barrier
     int rc = PLL_OK;
@@ -704,7 +752,6 @@ int multi_attempt(uint32_t count, const pll_graph_desc* graphs, uint32_t b, uint
         }
         // every workgroup resident at once, so a partially joined gang is
         // always completed by workgroups that finish other graphs
-        const uint32_t grid = std::min<uint32_t>((uint32_t)slots.size(), (uint32_t)resident);
         if (hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal) != hipSuccess) {
             rc = PLL_EDEVICE;
             break;
