@@ -330,6 +330,61 @@ __global__ void __launch_bounds__(kBlock) k_compact(uint32_t n, const uint64_t* 
     }
 }
 
+// ---- batches queued ahead of the host (run_ahead below) ----
+//
+// A launch of a queued batch runs only while nothing has halted the queue; a
+// step that the host has to see to first (a round more than were queued, rows
+// long enough for a launch of their own) halts it with its code.  Every
+// condition is unchanged while the launch that tests it runs, so all of its
+// workgroups decide alike.
+__device__ inline bool ahead_halted(const BuildArgs& A, uint32_t ahead) { return ahead && A.ctr->halt != 0; }
+
+__device__ inline bool any_shard(const DevCounters* ctr, uint32_t p, uint32_t hp, bool recv) {
+    const uint32_t lane = lane_id();
+    uint32_t x = 0;
+    if (lane < PLL_SHARDS) x = (recv ? ctr->sh[lane].recv[p] : 0u) | ctr->sh[lane].hq[hp];
+    return ballot64(x != 0) != 0;
+}
+
+// Before the check of round j: whether it is not to run.  Counts the round
+// (round 1, and every round after one that accepted something) and records
+// its receivers.
+__device__ inline bool ahead_check_stops(const BuildArgs& A, const pll::Exec& X, uint32_t ahead, uint32_t j,
+                                         uint32_t rin) {
+    if (!ahead) return false;
+    DevCounters* c = A.ctr;
+    const uint32_t halt = c->halt;
+    const bool heavy = j > 1 && any_shard(c, 0, (j - 1) & 1u, false);
+    if (halt || heavy) {
+        if (!halt && X.zero_i == 0) c->halt = ahead;
+        return true;
+    }
+    if (X.zero_i < PLL_WAVE) {
+        const uint32_t lane = lane_id();
+        const uint32_t total = wave_sum32(lane < PLL_SHARDS ? c->sh[lane].recv[rin] : 0u);
+        if (lane == 0) {
+            c->rrecv[j] = total;
+            if (j == 1 || c->racc[j - 1]) ++c->ahead_rounds;
+        }
+    }
+    return false;
+}
+
+// Before the batch end after `k` queued rounds: whether the batch goes on.
+__device__ inline bool ahead_end_stops(const BuildArgs& A, const pll::Exec& X, uint32_t ahead, uint32_t k) {
+    if (!ahead) return false;
+    DevCounters* c = A.ctr;
+    const uint32_t halt = c->halt, acc = c->racc[k];
+    const bool more = acc != 0 && any_shard(c, k % 3, k & 1u, true);
+    if (halt || more) {
+        if (!halt && X.zero_i == 0) c->halt = ahead;
+        return true;
+    }
+    // round k accepted something that nobody receives: the empty round k + 1
+    if (acc && X.zero_i == 0) ++c->ahead_rounds;
+    return false;
+}
+
 __device__ inline void reset_shard(Shard& sh) {
     sh.recv[0] = sh.recv[1] = sh.recv[2] = 0;
     sh.hq[0] = sh.hq[1] = 0;
@@ -338,7 +393,11 @@ __device__ inline void reset_shard(Shard& sh) {
 
 __global__ void k_batch_prep(DevCounters* ctr) {
     if (threadIdx.x < PLL_SHARDS) reset_shard(ctr->sh[threadIdx.x]);
+    if (threadIdx.x < PLL_PLANES + 2) ctr->racc[threadIdx.x] = 0;
 }
+
+// The host has taken over from a halted queue.
+__global__ void k_unhalt(DevCounters* ctr) { ctr->halt = 0; }
 
 __global__ void __launch_bounds__(kBlock) k_batch_init(BuildArgs A, uint32_t ib, uint32_t bs, uint32_t bstamp) {
     pll::phase_batch_init(A, grid_exec(A), ib, bs, bstamp);
@@ -361,12 +420,14 @@ __device__ inline void batch_init_planes(const BuildArgs& A, const pll::Exec& X,
 }
 
 __global__ void __launch_bounds__(kInitBlock) k_batch_init_planes(BuildArgs A, uint32_t ib, uint32_t bs,
-                                                                  uint32_t bstamp) {
+                                                                  uint32_t bstamp, uint32_t ahead) {
+    if (ahead_halted(A, ahead)) return;
     batch_init_planes(A, grid_exec(A), ib, bs, bstamp, blockIdx.x * pll::kInitRoots);
 }
 
 __global__ void __launch_bounds__(kBlock) k_push(BuildArgs A, uint32_t ib, uint32_t p, uint32_t nact, uint32_t rstamp,
-                                                 uint32_t bstamp) {
+                                                 uint32_t bstamp, uint32_t ahead) {
+    if (ahead_halted(A, ahead)) return;
     PhaseStats st;
     pll::phase_push(A, grid_exec(A), A.msgs, A.recv, ib, p, nact, rstamp, bstamp, st);
     const unsigned long long v[1] = {st.edges};
@@ -426,7 +487,8 @@ enum { kScanBytes, kScanSmall, kScanPlanes };
 // Round j's check fused with round j+1's push (NextRound in pll_phases.h).
 template <int WM, bool BP, bool PACK = false, int SCAN = kScanBytes>
 __device__ inline void check_push_body(const BuildArgs& A, const pll::Exec& X, uint32_t ib, uint32_t bs, uint32_t j,
-                                       const pll::NextRound& nr, uint32_t relaxed) {
+                                       const pll::NextRound& nr, uint32_t relaxed, uint32_t ahead) {
+    if (ahead_check_stops(A, X, ahead, j, nr.rin)) return;
     PhaseStats st;
     if (PACK && !BP)
         pll::phase_check4<WM, SCAN == kScanSmall, SCAN == kScanPlanes>(A, X, ib, bs, j, relaxed != 0, st, nr);
@@ -437,13 +499,16 @@ __device__ inline void check_push_body(const BuildArgs& A, const pll::Exec& X, u
     const int which[9] = {PLL_ST_CAND,     PLL_ST_ACC, PLL_ST_READ,  PLL_ST_TABLE,      PLL_ST_COST_POS,
                           PLL_ST_COST_NEG, PLL_ST_BP,  PLL_ST_EDGES, PLL_ST_FUSED_EDGES};
     block_add_stats<9>(A.ctr, v, which);
+    // a queued batch tells by it which round was its last (every workgroup
+    // that accepted something stores the same value)
+    if (ahead && ballot64(st.acc != 0) && lane_id() == 0) A.ctr->racc[j] = 1;
 }
 
 // at most 128 VGPRs, i.e. 4 waves per SIMD, like the unfused check
 template <int WM, bool PACK, int SCAN>
 __global__ void __launch_bounds__(kBlock, 4) k_check_push(BuildArgs A, uint32_t ib, uint32_t bs, uint32_t j,
-                                                          pll::NextRound nr, uint32_t relaxed) {
-    check_push_body<WM, false, PACK, SCAN>(A, grid_exec(A), ib, bs, j, nr, relaxed);
+                                                          pll::NextRound nr, uint32_t relaxed, uint32_t ahead) {
+    check_push_body<WM, false, PACK, SCAN>(A, grid_exec(A), ib, bs, j, nr, relaxed, ahead);
 }
 
 // Directed graphs: both sides' fused rounds in one launch, blocks [0, nb0)
@@ -453,16 +518,16 @@ __global__ void __launch_bounds__(kBlock, 4) k_check_push2(BuildArgs A0, pll::Ne
                                                            pll::NextRound nr1, uint32_t ib, uint32_t bs, uint32_t j,
                                                            uint32_t nb0) {
     if (blockIdx.x < nb0)
-        check_push_body<WM, false, false, SCAN>(A0, side_exec(A0, 0, nb0), ib, bs, j, nr0, 0);
+        check_push_body<WM, false, false, SCAN>(A0, side_exec(A0, 0, nb0), ib, bs, j, nr0, 0, 0);
     else
-        check_push_body<WM, false, false, SCAN>(A1, side_exec(A1, nb0, gridDim.x - nb0), ib, bs, j, nr1, 0);
+        check_push_body<WM, false, false, SCAN>(A1, side_exec(A1, nb0, gridDim.x - nb0), ib, bs, j, nr1, 0, 0);
 }
 
 // with bit-parallel labels (no register cap: it would spill)
 template <int WM, int SCAN>
 __global__ void __launch_bounds__(kBlock) k_check_push_bp(BuildArgs A, uint32_t ib, uint32_t bs, uint32_t j,
-                                                          pll::NextRound nr, uint32_t relaxed) {
-    check_push_body<WM, true, false, SCAN>(A, grid_exec(A), ib, bs, j, nr, relaxed);
+                                                          pll::NextRound nr, uint32_t relaxed, uint32_t ahead) {
+    check_push_body<WM, true, false, SCAN>(A, grid_exec(A), ib, bs, j, nr, relaxed, ahead);
 }
 
 // Pulled rounds: the (vertex, segment) items, once per build, and a round.
@@ -486,7 +551,8 @@ __global__ void __launch_bounds__(kBlock) k_push_heavy(BuildArgs A, uint32_t ib,
     block_add_stats<1>(A.ctr, v, which);
 }
 
-__global__ void __launch_bounds__(kBlock) k_batch_end4(BuildArgs A, uint32_t ib) {
+__global__ void __launch_bounds__(kBlock) k_batch_end4(BuildArgs A, uint32_t ib, uint32_t ahead, uint32_t rounds) {
+    if (ahead_end_stops(A, grid_exec(A), ahead, rounds)) return;
     __shared__ uint64_t s_pres[kWavesPerBlock][PLL_WMAX];
     __shared__ uint8_t s_dist[kWavesPerBlock][PLL_BMAX];
     const uint32_t wv = threadIdx.x >> 6;
@@ -560,8 +626,11 @@ __global__ void k_check_weights(uint64_t nnz, const uint8_t* w, DevCounters* ctr
 // With `prep` set it also does k_batch_prep's reset for the next batch (the
 // batch end, which reads the touched counts, has finished by then).
 template <bool PLANES>
-__global__ void __launch_bounds__(kBlock) k_clear_table(BuildArgs A, uint32_t ib, uint32_t bs, DevCounters* prep) {
+__global__ void __launch_bounds__(kBlock) k_clear_table(BuildArgs A, uint32_t ib, uint32_t bs, DevCounters* prep,
+                                                        uint32_t ahead) {
+    if (ahead_halted(A, ahead)) return;
     if (prep && blockIdx.x == 0 && threadIdx.x < PLL_SHARDS) reset_shard(prep->sh[threadIdx.x]);
+    if (prep && blockIdx.x == 0 && threadIdx.x < PLL_PLANES + 2) prep->racc[threadIdx.x] = 0;
     pll::phase_clear_table<PLANES>(A, grid_exec(A), ib, bs);
 }
 
@@ -774,7 +843,8 @@ __global__ void __launch_bounds__(kBlock) k_bp_sibling(uint32_t n, uint32_t t, u
 
 // Transposed copy of the batch vertices' BP data (root-major, so that the
 // check's lanes over batch vertices read consecutive addresses).
-__global__ void k_bp_batch_stage(BuildArgs A, uint32_t ib, uint32_t bs) {
+__global__ void k_bp_batch_stage(BuildArgs A, uint32_t ib, uint32_t bs, uint32_t ahead) {
+    if (ahead_halted(A, ahead)) return;
     const uint32_t t = A.bp_t;
     for (uint32_t x = blockIdx.x * blockDim.x + threadIdx.x; x < t * bs; x += gridDim.x * blockDim.x) {
         const uint32_t i = x / bs, k = x % bs;
@@ -1059,21 +1129,21 @@ void dispatch_check(uint32_t blocks, hipStream_t s, const BuildArgs& A, uint32_t
 
 template <int WM>
 void launch_check_push(uint32_t blocks, hipStream_t s, const BuildArgs& A, uint32_t ib, uint32_t bs, uint32_t j,
-                       const pll::NextRound& nr, uint32_t relaxed, bool pack) {
+                       const pll::NextRound& nr, uint32_t relaxed, bool pack, uint32_t ahead) {
     if (A.bp_t && A.P)
-        k_check_push_bp<WM, kScanPlanes><<<blocks, kBlock, 0, s>>>(A, ib, bs, j, nr, relaxed);
+        k_check_push_bp<WM, kScanPlanes><<<blocks, kBlock, 0, s>>>(A, ib, bs, j, nr, relaxed, ahead);
     else if (A.bp_t)
-        k_check_push_bp<WM, kScanBytes><<<blocks, kBlock, 0, s>>>(A, ib, bs, j, nr, relaxed);
+        k_check_push_bp<WM, kScanBytes><<<blocks, kBlock, 0, s>>>(A, ib, bs, j, nr, relaxed, ahead);
     else if (A.P && pack)
-        k_check_push<WM, true, kScanPlanes><<<blocks, kBlock, 0, s>>>(A, ib, bs, j, nr, relaxed);
+        k_check_push<WM, true, kScanPlanes><<<blocks, kBlock, 0, s>>>(A, ib, bs, j, nr, relaxed, ahead);
     else if (A.P)
-        k_check_push<WM, false, kScanPlanes><<<blocks, kBlock, 0, s>>>(A, ib, bs, j, nr, relaxed);
+        k_check_push<WM, false, kScanPlanes><<<blocks, kBlock, 0, s>>>(A, ib, bs, j, nr, relaxed, ahead);
     else if (pack)  // only in rounds j <= kSmallT
-        k_check_push<WM, true, kScanSmall><<<blocks, kBlock, 0, s>>>(A, ib, bs, j, nr, relaxed);
+        k_check_push<WM, true, kScanSmall><<<blocks, kBlock, 0, s>>>(A, ib, bs, j, nr, relaxed, ahead);
     else if (j <= pll::kSmallT)
-        k_check_push<WM, false, kScanSmall><<<blocks, kBlock, 0, s>>>(A, ib, bs, j, nr, relaxed);
+        k_check_push<WM, false, kScanSmall><<<blocks, kBlock, 0, s>>>(A, ib, bs, j, nr, relaxed, ahead);
     else
-        k_check_push<WM, false, kScanBytes><<<blocks, kBlock, 0, s>>>(A, ib, bs, j, nr, relaxed);
+        k_check_push<WM, false, kScanBytes><<<blocks, kBlock, 0, s>>>(A, ib, bs, j, nr, relaxed, ahead);
 }
 
 template <int SCAN>
@@ -1100,20 +1170,20 @@ void dispatch_check_push2(uint32_t nb0, uint32_t nb1, hipStream_t s, const Build
 }
 
 void dispatch_check_push(uint32_t blocks, hipStream_t s, const BuildArgs& A, uint32_t ib, uint32_t bs, uint32_t j,
-                         const pll::NextRound& nr, uint32_t relaxed, bool pack) {
+                         const pll::NextRound& nr, uint32_t relaxed, bool pack, uint32_t ahead) {
     switch (words_class(A.W)) {
-        case 1: launch_check_push<1>(blocks, s, A, ib, bs, j, nr, relaxed, pack); break;
-        case 2: launch_check_push<2>(blocks, s, A, ib, bs, j, nr, relaxed, pack); break;
-        case 4: launch_check_push<4>(blocks, s, A, ib, bs, j, nr, relaxed, pack); break;
-        case 8: launch_check_push<8>(blocks, s, A, ib, bs, j, nr, relaxed, pack); break;
-        default: launch_check_push<16>(blocks, s, A, ib, bs, j, nr, relaxed, pack); break;
+        case 1: launch_check_push<1>(blocks, s, A, ib, bs, j, nr, relaxed, pack, ahead); break;
+        case 2: launch_check_push<2>(blocks, s, A, ib, bs, j, nr, relaxed, pack, ahead); break;
+        case 4: launch_check_push<4>(blocks, s, A, ib, bs, j, nr, relaxed, pack, ahead); break;
+        case 8: launch_check_push<8>(blocks, s, A, ib, bs, j, nr, relaxed, pack, ahead); break;
+        default: launch_check_push<16>(blocks, s, A, ib, bs, j, nr, relaxed, pack, ahead); break;
     }
 }
 
 void dispatch_batch_end(uint64_t touched, hipStream_t s, const BuildArgs& A, uint32_t ib, uint32_t bs,
-                        uint32_t recheck) {
+                        uint32_t recheck, uint32_t ahead = 0, uint32_t rounds = 0) {
     if (!recheck) {
-        k_batch_end4<<<blocks_for_waves((touched + 3) / 4), kBlock, 0, s>>>(A, ib);
+        k_batch_end4<<<blocks_for_waves((touched + 3) / 4), kBlock, 0, s>>>(A, ib, ahead, rounds);
         return;
     }
     const uint32_t blocks = blocks_for_waves(touched);
@@ -1358,18 +1428,20 @@ int planes_to_bytes(DevAllocs& M, BuildArgs& A, uint32_t ib, uint32_t bs, hipStr
     return PLL_OK;
 }
 
-void launch_batch_init(const BuildArgs& A, uint32_t ib, uint32_t bs, uint32_t bstamp, hipStream_t s) {
+void launch_batch_init(const BuildArgs& A, uint32_t ib, uint32_t bs, uint32_t bstamp, hipStream_t s,
+                       uint32_t ahead = 0) {
     if (A.P)
-        k_batch_init_planes<<<init_blocks(bs), kInitBlock, 0, s>>>(A, ib, bs, bstamp);
+        k_batch_init_planes<<<init_blocks(bs), kInitBlock, 0, s>>>(A, ib, bs, bstamp, ahead);
     else
         k_batch_init<<<blocks_for_waves(bs), kBlock, 0, s>>>(A, ib, bs, bstamp);
 }
 
-void launch_clear_table(const BuildArgs& A, uint32_t ib, uint32_t bs, DevCounters* prep, hipStream_t s) {
+void launch_clear_table(const BuildArgs& A, uint32_t ib, uint32_t bs, DevCounters* prep, hipStream_t s,
+                        uint32_t ahead = 0) {
     if (A.P)
-        k_clear_table<true><<<blocks_for_waves(4ull * bs), kBlock, 0, s>>>(A, ib, bs, prep);
+        k_clear_table<true><<<blocks_for_waves(4ull * bs), kBlock, 0, s>>>(A, ib, bs, prep, ahead);
     else
-        k_clear_table<false><<<blocks_for_waves(4ull * bs), kBlock, 0, s>>>(A, ib, bs, prep);
+        k_clear_table<false><<<blocks_for_waves(4ull * bs), kBlock, 0, s>>>(A, ib, bs, prep, 0);
 }
 
 // Final label CSR of one build, by vertex id with hubs as ranks (a8):
@@ -1444,6 +1516,77 @@ int build_bp(DevAllocs& M, uint32_t n, uint32_t t_req, const uint64_t* rrow, con
     TRY_HIP(hipMemsetAsync(&ctr->sh[0].recv[0], 0, sizeof(uint32_t), s));
     return PLL_OK;
 }
+
+// Batches queued ahead of the host.  A round of a few thousand receivers
+// runs 10 us, and reading its counters back and launching the next one costs
+// as much again.  Once the rounds of a batch fall below kPackMin receivers
+// (so none is packed or pulled), whole batches are queued: init, push, as
+// many checks as the last batches needed, end and clear, for up to kAheadMax
+// batches, with grids sized by the last receiver counts, and one read-back at
+// the end.  A batch that needs more rounds, or that meets rows long enough
+// for a launch of their own, halts the queue on the device (ahead_check_stops,
+// ahead_end_stops): what was queued behind it does nothing, and the host
+// finishes that batch round by round.
+struct Ahead {
+    static constexpr uint32_t kAheadMax = 8;
+    bool on = false;
+    uint32_t rounds = 0;  // checks to queue per batch; 0: no batch seen yet
+    uint32_t depth = 1;   // batches to queue; doubles while nothing halts
+    uint32_t quiet = 0;   // queues whose last batch did not need its last check
+    bool heavy = false;   // the last batch met heavy rows
+    uint64_t recv[PLL_PLANES + 2] = {};
+    unsigned long long top = 0;     // arena top at the last look
+    unsigned long long growth = 0;  // per batch since then
+    bool fits = false;              // every round of the last batch could be queued
+
+    void look(const DevCounters* h, uint32_t batches_run) {
+        const unsigned long long t = max_top(h);
+        growth = t >= top ? (t - top) / std::max(batches_run, 1u) : t;
+        top = t;
+    }
+    // Batches to queue now, of the `left` ones to run (0: none).
+    uint32_t ready(const BuildArgs& A, const DevCounters* h, uint32_t left) {
+        if (!on || !A.P || rounds == 0 || !fits || heavy) return 0;
+        for (uint32_t j = 1; j <= rounds; ++j)
+            if (recv[j] >= kPackMin) return 0;
+        // room for four times the recent growth in the bump regions
+        const unsigned long long room = A.region_cap - std::min<unsigned long long>(max_top(h), A.region_cap);
+        uint32_t d = std::min(depth, left);
+        while (d && 4 * growth * d > room) d /= 2;
+        return d;
+    }
+    // A batch the host runs: its first round, and each round after its check.
+    void begin(uint32_t resume_j) {
+        if (resume_j) return;
+        fits = true;
+        heavy = false;
+    }
+    void round(uint32_t j, uint64_t receivers, bool heavy_rows) {
+        heavy = heavy || heavy_rows;
+        if (j > PLL_PLANES + 1) {
+            fits = false;
+            return;
+        }
+        recv[j] = receivers;
+        rounds = std::max(rounds, j);
+    }
+    void after(const DevCounters* h, uint32_t queued, uint32_t done, uint32_t k) {
+        look(h, done + 1);
+        for (uint32_t j = 1; j <= k; ++j) recv[j] = h->rrecv[j];
+        if (done < queued) {
+            depth = 1;
+            quiet = 0;
+            return;
+        }
+        depth = std::min(2 * depth, kAheadMax);
+        // drop the last check once several queues did not need it
+        quiet = h->rrecv[k] == 0 ? quiet + 1 : 0;
+        if (quiet >= 2 && rounds > 1) {
+            --rounds;
+            quiet = 0;
+        }
+    }
+};
 
 int build_attempt(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, const uint32_t* col, const uint32_t* order,
                   uint32_t b, uint32_t flags, uint64_t arena_hint, bool arena_fixed, uint32_t max_workgroups,
@@ -1602,6 +1745,9 @@ int build_attempt(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, const uint3
     // which falls from batch to batch in rank order (a grid-stride loop
     // covers any excess)
     uint64_t r1_est = n;
+    Ahead Q;
+    Q.on = A.P && !P.on && !trace && !(flags & PLL_FLAG_PACK4);
+    uint32_t resume_j = 0;  // the queue began this batch; the host goes on at this round
     for (uint32_t ib = 0; !(flags & PLL_FLAG_PERSISTENT) && ib < n; ib += b) {
         if (ib >= skip_from) {
             const uint64_t left = (n - ib + b - 1) / b;
@@ -1609,31 +1755,94 @@ int build_attempt(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, const uint3
             rounds += left;
             break;
         }
+        if (const uint32_t depth = skip_known ? Q.ready(A, h, (skip_from - ib + b - 1) / b) : 0) {
+            // batches queued without a read-back between them (struct Ahead)
+            const uint32_t bstamp0 = bstamp, rstamp0 = rstamp, K = Q.rounds;
+            uint64_t touched = b;
+            for (uint32_t j = 1; j <= K; ++j) touched += Q.recv[j];
+            for (uint32_t d = 0; d < depth; ++d) {
+                const uint32_t ibd = ib + d * b, bsd = std::min(b, n - ibd), code = 1 + 16 * d;
+                ++bstamp;
+                if (A.bp_t)
+                    k_bp_batch_stage<<<blocks_for_threads((uint64_t)A.bp_t * bsd), kBlock, 0, s>>>(A, ibd, bsd, 1);
+                launch_batch_init(A, ibd, bsd, bstamp, s, 1);
+                ++rstamp;
+                BuildArgs A1 = A;
+                A1.msgs = mbuf[1];
+                A1.recv = rbuf[1];
+                k_push<<<blocks_for_waves((uint64_t)bsd + 1024), kBlock, 0, s>>>(A1, ibd, 0, bsd, rstamp, bstamp, 1);
+                for (uint32_t j = 1; j <= K; ++j, ++rstamp) {
+                    const pll::NextRound nr{mbuf[j & 1u], rbuf[j & 1u], mbuf[(j + 1) & 1u], rbuf[(j + 1) & 1u],
+                                            (j - 1) % 3, j % 3, (j + 1) % 3, j & 1u, rstamp + 1, bstamp, 0u};
+                    dispatch_check_push(blocks_for_waves(std::min<uint64_t>(n, Q.recv[j] + Q.recv[j] / 4 + 512)), s, A,
+                                        ibd, bsd, j, nr, 0, false, code + j);
+                }
+                dispatch_batch_end(touched, s, A, ibd, bsd, 0, code + K + 1, K);
+                launch_clear_table(A, ibd, bsd, ctr, s, 1);
+            }
+            TRY_HIP(hipGetLastError());
+            rc = read_counters(ctr, h, s);
+            if (rc) return rc;
+            if (h->error) return device_error_status(h->error);
+            accepted_seen = sum_stat(h, PLL_ST_ACC);
+            const uint32_t done = h->halt ? (h->halt - 1) / 16 : depth;
+            batches += done;
+            Q.after(h, depth, done, K);
+            if (!h->halt) {
+                r1_est = std::max<uint64_t>(b, h->rrecv[1]);
+                ib += (depth - 1) * b;
+                if (!arena_fixed && ib + b < n && max_top(h) * 2 > A.region_cap) {
+                    rc = relayout_arena(M, A, spare_off, tmp32, scan_scratch, false, A.region_cap * 2, 0, s);
+                    if (rc) return rc;
+                }
+                continue;
+            }
+            // the host finishes batch `done` from round resume_j on, with the
+            // stamps the queue gave it (the later batches have not begun)
+            resume_j = (h->halt - 1) % 16;
+            ib += done * b;
+            bstamp = bstamp0 + done;
+            rstamp = rstamp0 + done * (K + 1) + resume_j - 1;
+            k_unhalt<<<1, 1, 0, s>>>(ctr);
+        }
         const uint32_t bs = std::min(b, n - ib);
         ++bstamp;
         ++batches;
-        hipEvent_t e0 = P.mark();
-        // later batches have the counters reset by the previous batch's
-        // table clear
-        if (ib == 0) k_batch_prep<<<1, 64, 0, s>>>(ctr);
-        if (A.bp_t) k_bp_batch_stage<<<blocks_for_threads((uint64_t)A.bp_t * bs), kBlock, 0, s>>>(A, ib, bs);
-        launch_batch_init(A, ib, bs, bstamp, s);
-        P.span(PLL_PHASE_INIT, e0, P.mark(), (A.bp_t ? 2 : 1) + (ib == 0 ? 1 : 0));
-        // round 1's push from the batch vertices (active list 0) into
-        // receiver queue 0 and message buffer 1; afterwards every round j is
-        // one fused launch (check of round j, push of round j+1 into buffer
-        // (j+1) & 1), plus a launch for heavy rows when there are any
-        ++rstamp;
-        {
-            BuildArgs A1 = A;
-            A1.msgs = mbuf[1];
-            A1.recv = rbuf[1];
-            hipEvent_t r0 = P.mark();
-            k_push<<<blocks_for_waves((uint64_t)bs + 1024), kBlock, 0, s>>>(A1, ib, 0, bs, rstamp, bstamp);
-            P.span(PLL_PHASE_PUSH, r0, P.mark(), 1);
-        }
         uint64_t next_est = r1_est;
-        for (uint32_t j = 1;; ++j) {
+        if (!resume_j) {
+            hipEvent_t e0 = P.mark();
+            // later batches have the counters reset by the previous batch's
+            // table clear
+            if (ib == 0) k_batch_prep<<<1, 64, 0, s>>>(ctr);
+            if (A.bp_t) k_bp_batch_stage<<<blocks_for_threads((uint64_t)A.bp_t * bs), kBlock, 0, s>>>(A, ib, bs, 0);
+            launch_batch_init(A, ib, bs, bstamp, s);
+            P.span(PLL_PHASE_INIT, e0, P.mark(), (A.bp_t ? 2 : 1) + (ib == 0 ? 1 : 0));
+            // round 1's push from the batch vertices (active list 0) into
+            // receiver queue 0 and message buffer 1; afterwards every round j is
+            // one fused launch (check of round j, push of round j+1 into buffer
+            // (j+1) & 1), plus a launch for heavy rows when there are any
+            ++rstamp;
+            {
+                BuildArgs A1 = A;
+                A1.msgs = mbuf[1];
+                A1.recv = rbuf[1];
+                hipEvent_t r0 = P.mark();
+                k_push<<<blocks_for_waves((uint64_t)bs + 1024), kBlock, 0, s>>>(A1, ib, 0, bs, rstamp, bstamp, 0);
+                P.span(PLL_PHASE_PUSH, r0, P.mark(), 1);
+            }
+        } else {
+            // the heavy rows of round resume_j - 1 that halted the queue
+            const uint32_t j = resume_j, nh = sum_hq(h, (j - 1) & 1u);
+            ++rstamp;
+            if (nh) {
+                Q.heavy = true;
+                k_push_heavy<<<blocks_for_waves(nh), kBlock, 0, s>>>(A, ib, (j - 1) & 1u, (j - 1) % 3, mbuf[j & 1u],
+                                                                     rbuf[j & 1u], rstamp, bstamp);
+            }
+            next_est = (uint64_t)sum_recv(h, (j - 1) % 3) + 1024ull * nh;
+        }
+        Q.begin(resume_j);
+        for (uint32_t j = resume_j ? resume_j : 1;; ++j) {
             ++rounds;
             if (A.P && j > PLL_PLANES + 1) {
                 rc = planes_to_bytes(M, A, ib, bs, s);
@@ -1650,7 +1859,7 @@ int build_attempt(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, const uint3
             // rounds with many receivers check four per wave (phase_check4)
             const bool pack = ((flags & PLL_FLAG_PACK4) || next_est >= kPackMin) && j <= pll::kSmallT;
             const uint64_t waves = pack ? next_est / 4 + 512 : next_est + 2048;
-            dispatch_check_push(blocks_for_waves(std::min<uint64_t>(n, waves)), s, A, ib, bs, j, nr, relaxed, pack);
+            dispatch_check_push(blocks_for_waves(std::min<uint64_t>(n, waves)), s, A, ib, bs, j, nr, relaxed, pack, 0);
             P.span(PLL_PHASE_CHECK, r1, P.mark(), 1);
             TRY_HIP(hipGetLastError());
             if (pull) {
@@ -1670,6 +1879,7 @@ int build_attempt(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, const uint3
             }
             const unsigned long long acc_now = sum_stat(h, PLL_ST_ACC);
             if (j == 1) r1_est = std::max<uint64_t>(bs, sum_recv(h, nr.rin));
+            Q.round(j, sum_recv(h, nr.rin), sum_hq(h, nr.hout) != 0);
             if (trace) {
                 unsigned long long cur[PLL_NUM_ST];
                 for (int k = 0; k < PLL_NUM_ST; ++k) cur[k] = sum_stat(h, k);
@@ -1698,11 +1908,13 @@ int build_attempt(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, const uint3
                 break;
             }
         }
+        resume_j = 0;
         hipEvent_t e1 = P.mark();
         dispatch_batch_end(sum_touched(h), s, A, ib, bs, recheck);
         launch_clear_table(A, ib, bs, ctr, s);
         P.span(PLL_PHASE_END, e1, P.mark(), 2);
         TRY_HIP(hipGetLastError());
+        Q.look(h, 1);
         // compact the lists into a larger arena once a bump region is half used
         if (!arena_fixed && ib + b < n && max_top(h) * 2 > A.region_cap) {
             rc = relayout_arena(M, A, spare_off, tmp32, scan_scratch, false, A.region_cap * 2, 0, s);
@@ -1769,7 +1981,7 @@ int build_attempt(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, const uint3
     I.max_dist = h->max_dist;
     I.max_label = h->max_label;
     I.batches = batches;
-    I.rounds = rounds;
+    I.rounds = rounds + h->ahead_rounds;
     I.candidates = sum_stat(h, PLL_ST_CAND);
     I.accepted = sum_stat(h, PLL_ST_ACC);
     I.edges_scanned = sum_stat(h, PLL_ST_EDGES);

@@ -65,7 +65,14 @@ struct DevCounters {
     uint32_t max_dist;
     uint32_t max_label;
     uint32_t edge_end;  // 1 + the highest rank with an edge (0: the graph has no edges)
-    uint32_t pad[28];
+    // batches queued ahead of the host (see run_ahead in pll_build.hip): where
+    // the queue stopped (0: it did not), whether round j of the current batch
+    // accepted anything, its receivers in the last batch, and the rounds run
+    uint32_t halt;
+    uint32_t racc[PLL_PLANES + 2];
+    uint32_t rrecv[PLL_PLANES + 2];
+    uint32_t pad[5];
+    unsigned long long ahead_rounds;
     Shard sh[PLL_SHARDS];
 };
 
