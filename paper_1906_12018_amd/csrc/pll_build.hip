@@ -385,6 +385,45 @@ __device__ inline bool ahead_end_stops(const BuildArgs& A, const pll::Exec& X, u
     return false;
 }
 
+// The same for the two sides of a directed build, whose rounds go in lockstep
+// and whose queue halts together (on side 0's word); b1 is the first block of
+// side 1.
+__device__ inline bool ahead_check_stops2(const BuildArgs& A0, const BuildArgs& A1, uint32_t ahead, uint32_t j,
+                                          uint32_t rin, uint32_t b1) {
+    if (!ahead) return false;
+    DevCounters *c0 = A0.ctr, *c1 = A1.ctr;
+    const uint32_t halt = c0->halt, hp = (j - 1) & 1u;
+    const bool h0 = j > 1 && any_shard(c0, 0, hp, false), h1 = j > 1 && any_shard(c1, 0, hp, false);
+    if (halt || h0 || h1) {
+        if (!halt && blockIdx.x == 0 && threadIdx.x == 0) c0->halt = ahead;
+        return true;
+    }
+    if ((blockIdx.x == 0 || blockIdx.x == b1) && threadIdx.x < PLL_WAVE) {
+        DevCounters* c = blockIdx.x == 0 ? c0 : c1;
+        const uint32_t lane = lane_id();
+        const uint32_t total = wave_sum32(lane < PLL_SHARDS ? c->sh[lane].recv[rin] : 0u);
+        if (lane == 0) {
+            c->rrecv[j] = total;
+            if (blockIdx.x == 0 && (j == 1 || c0->racc[j - 1] || c1->racc[j - 1])) ++c0->ahead_rounds;
+        }
+    }
+    return false;
+}
+
+__device__ inline bool ahead_end_stops2(const BuildArgs& A0, const BuildArgs& A1, uint32_t ahead, uint32_t k) {
+    if (!ahead) return false;
+    DevCounters *c0 = A0.ctr, *c1 = A1.ctr;
+    const uint32_t halt = c0->halt, acc = c0->racc[k] | c1->racc[k];
+    const bool m0 = any_shard(c0, k % 3, k & 1u, true), m1 = any_shard(c1, k % 3, k & 1u, true);
+    const bool first = blockIdx.x == 0 && threadIdx.x == 0;
+    if (halt || (acc && (m0 || m1))) {
+        if (!halt && first) c0->halt = ahead;
+        return true;
+    }
+    if (acc && first) ++c0->ahead_rounds;
+    return false;
+}
+
 __device__ inline void reset_shard(Shard& sh) {
     sh.recv[0] = sh.recv[1] = sh.recv[2] = 0;
     sh.hq[0] = sh.hq[1] = 0;
@@ -439,14 +478,16 @@ __global__ void __launch_bounds__(kBlock) k_push(BuildArgs A, uint32_t ib, uint3
 // half of the blocks on each (a launch of one side leaves most of the chip
 // idle and is bound by its chain of accesses).
 __global__ void __launch_bounds__(kInitBlock) k_batch_init_planes2(BuildArgs A0, BuildArgs A1, uint32_t ib,
-                                                                   uint32_t bs, uint32_t bstamp) {
+                                                                   uint32_t bs, uint32_t bstamp, uint32_t ahead) {
+    if (ahead_halted(A0, ahead)) return;
     const uint32_t nb = gridDim.x / 2, side = blockIdx.x >= nb ? 1u : 0u;
     const BuildArgs& A = side ? A1 : A0;
     batch_init_planes(A, side_exec(A, side * nb, nb), ib, bs, bstamp, (blockIdx.x - side * nb) * pll::kInitRoots);
 }
 
 __global__ void __launch_bounds__(kBlock) k_push2(BuildArgs A0, BuildArgs A1, uint32_t ib, uint32_t nact,
-                                                  uint32_t rstamp, uint32_t bstamp) {
+                                                  uint32_t rstamp, uint32_t bstamp, uint32_t ahead) {
+    if (ahead_halted(A0, ahead)) return;
     const uint32_t nb = gridDim.x / 2, side = blockIdx.x >= nb ? 1u : 0u;
     const BuildArgs& A = side ? A1 : A0;
     PhaseStats st;
@@ -456,7 +497,9 @@ __global__ void __launch_bounds__(kBlock) k_push2(BuildArgs A0, BuildArgs A1, ui
     block_add_stats<1>(A.ctr, v, which);
 }
 
-__global__ void __launch_bounds__(kBlock) k_batch_end4_2(BuildArgs A0, BuildArgs A1, uint32_t ib, uint32_t nb0) {
+__global__ void __launch_bounds__(kBlock) k_batch_end4_2(BuildArgs A0, BuildArgs A1, uint32_t ib, uint32_t nb0,
+                                                         uint32_t ahead, uint32_t rounds) {
+    if (ahead_end_stops2(A0, A1, ahead, rounds)) return;
     __shared__ uint64_t s_pres[kWavesPerBlock][PLL_WMAX];
     __shared__ uint8_t s_dist[kWavesPerBlock][PLL_BMAX];
     const uint32_t wv = threadIdx.x >> 6;
@@ -488,7 +531,6 @@ enum { kScanBytes, kScanSmall, kScanPlanes };
 template <int WM, bool BP, bool PACK = false, int SCAN = kScanBytes>
 __device__ inline void check_push_body(const BuildArgs& A, const pll::Exec& X, uint32_t ib, uint32_t bs, uint32_t j,
                                        const pll::NextRound& nr, uint32_t relaxed, uint32_t ahead) {
-    if (ahead_check_stops(A, X, ahead, j, nr.rin)) return;
     PhaseStats st;
     if (PACK && !BP)
         pll::phase_check4<WM, SCAN == kScanSmall, SCAN == kScanPlanes>(A, X, ib, bs, j, relaxed != 0, st, nr);
@@ -508,6 +550,7 @@ __device__ inline void check_push_body(const BuildArgs& A, const pll::Exec& X, u
 template <int WM, bool PACK, int SCAN>
 __global__ void __launch_bounds__(kBlock, 4) k_check_push(BuildArgs A, uint32_t ib, uint32_t bs, uint32_t j,
                                                           pll::NextRound nr, uint32_t relaxed, uint32_t ahead) {
+    if (ahead_check_stops(A, grid_exec(A), ahead, j, nr.rin)) return;
     check_push_body<WM, false, PACK, SCAN>(A, grid_exec(A), ib, bs, j, nr, relaxed, ahead);
 }
 
@@ -516,17 +559,19 @@ __global__ void __launch_bounds__(kBlock, 4) k_check_push(BuildArgs A, uint32_t 
 template <int WM, int SCAN>
 __global__ void __launch_bounds__(kBlock, 4) k_check_push2(BuildArgs A0, pll::NextRound nr0, BuildArgs A1,
                                                            pll::NextRound nr1, uint32_t ib, uint32_t bs, uint32_t j,
-                                                           uint32_t nb0) {
+                                                           uint32_t nb0, uint32_t ahead) {
+    if (ahead_check_stops2(A0, A1, ahead, j, nr0.rin, nb0)) return;
     if (blockIdx.x < nb0)
-        check_push_body<WM, false, false, SCAN>(A0, side_exec(A0, 0, nb0), ib, bs, j, nr0, 0, 0);
+        check_push_body<WM, false, false, SCAN>(A0, side_exec(A0, 0, nb0), ib, bs, j, nr0, 0, ahead);
     else
-        check_push_body<WM, false, false, SCAN>(A1, side_exec(A1, nb0, gridDim.x - nb0), ib, bs, j, nr1, 0, 0);
+        check_push_body<WM, false, false, SCAN>(A1, side_exec(A1, nb0, gridDim.x - nb0), ib, bs, j, nr1, 0, ahead);
 }
 
 // with bit-parallel labels (no register cap: it would spill)
 template <int WM, int SCAN>
 __global__ void __launch_bounds__(kBlock) k_check_push_bp(BuildArgs A, uint32_t ib, uint32_t bs, uint32_t j,
                                                           pll::NextRound nr, uint32_t relaxed, uint32_t ahead) {
+    if (ahead_check_stops(A, grid_exec(A), ahead, j, nr.rin)) return;
     check_push_body<WM, true, false, SCAN>(A, grid_exec(A), ib, bs, j, nr, relaxed, ahead);
 }
 
@@ -636,11 +681,14 @@ __global__ void __launch_bounds__(kBlock) k_clear_table(BuildArgs A, uint32_t ib
 
 // Both sides of a directed build, and the counters' reset.
 template <bool PLANES>
-__global__ void __launch_bounds__(kBlock) k_clear_table2(BuildArgs A0, BuildArgs A1, uint32_t ib, uint32_t bs) {
+__global__ void __launch_bounds__(kBlock) k_clear_table2(BuildArgs A0, BuildArgs A1, uint32_t ib, uint32_t bs,
+                                                         uint32_t ahead) {
+    if (ahead_halted(A0, ahead)) return;
     const uint32_t nb = gridDim.x / 2, side = blockIdx.x >= nb ? 1u : 0u;
     const BuildArgs& A = side ? A1 : A0;
     const pll::Exec X = side_exec(A, side * nb, nb);
     if (X.zero_i < PLL_SHARDS) reset_shard(A.ctr->sh[X.zero_i]);
+    if (X.zero_i < PLL_PLANES + 2) A.ctr->racc[X.zero_i] = 0;
     pll::phase_clear_table<PLANES>(A, X, ib, bs);
 }
 
@@ -1148,25 +1196,25 @@ void launch_check_push(uint32_t blocks, hipStream_t s, const BuildArgs& A, uint3
 
 template <int SCAN>
 void launch_check_push2(uint32_t nb0, uint32_t nb1, hipStream_t s, const BuildArgs& A0, const pll::NextRound& nr0,
-                        const BuildArgs& A1, const pll::NextRound& nr1, uint32_t ib, uint32_t bs, uint32_t j) {
+                        const BuildArgs& A1, const pll::NextRound& nr1, uint32_t ib, uint32_t bs, uint32_t j, uint32_t ahead) {
     const uint32_t g = nb0 + nb1;
     switch (words_class(A0.W)) {
-        case 1: k_check_push2<1, SCAN><<<g, kBlock, 0, s>>>(A0, nr0, A1, nr1, ib, bs, j, nb0); break;
-        case 2: k_check_push2<2, SCAN><<<g, kBlock, 0, s>>>(A0, nr0, A1, nr1, ib, bs, j, nb0); break;
-        case 4: k_check_push2<4, SCAN><<<g, kBlock, 0, s>>>(A0, nr0, A1, nr1, ib, bs, j, nb0); break;
-        case 8: k_check_push2<8, SCAN><<<g, kBlock, 0, s>>>(A0, nr0, A1, nr1, ib, bs, j, nb0); break;
-        default: k_check_push2<16, SCAN><<<g, kBlock, 0, s>>>(A0, nr0, A1, nr1, ib, bs, j, nb0); break;
+        case 1: k_check_push2<1, SCAN><<<g, kBlock, 0, s>>>(A0, nr0, A1, nr1, ib, bs, j, nb0, ahead); break;
+        case 2: k_check_push2<2, SCAN><<<g, kBlock, 0, s>>>(A0, nr0, A1, nr1, ib, bs, j, nb0, ahead); break;
+        case 4: k_check_push2<4, SCAN><<<g, kBlock, 0, s>>>(A0, nr0, A1, nr1, ib, bs, j, nb0, ahead); break;
+        case 8: k_check_push2<8, SCAN><<<g, kBlock, 0, s>>>(A0, nr0, A1, nr1, ib, bs, j, nb0, ahead); break;
+        default: k_check_push2<16, SCAN><<<g, kBlock, 0, s>>>(A0, nr0, A1, nr1, ib, bs, j, nb0, ahead); break;
     }
 }
 
 void dispatch_check_push2(uint32_t nb0, uint32_t nb1, hipStream_t s, const BuildArgs& A0, const pll::NextRound& nr0,
-                          const BuildArgs& A1, const pll::NextRound& nr1, uint32_t ib, uint32_t bs, uint32_t j) {
+                          const BuildArgs& A1, const pll::NextRound& nr1, uint32_t ib, uint32_t bs, uint32_t j, uint32_t ahead) {
     if (A0.P)
-        launch_check_push2<kScanPlanes>(nb0, nb1, s, A0, nr0, A1, nr1, ib, bs, j);
+        launch_check_push2<kScanPlanes>(nb0, nb1, s, A0, nr0, A1, nr1, ib, bs, j, ahead);
     else if (j <= pll::kSmallT)
-        launch_check_push2<kScanSmall>(nb0, nb1, s, A0, nr0, A1, nr1, ib, bs, j);
+        launch_check_push2<kScanSmall>(nb0, nb1, s, A0, nr0, A1, nr1, ib, bs, j, ahead);
     else
-        launch_check_push2<kScanBytes>(nb0, nb1, s, A0, nr0, A1, nr1, ib, bs, j);
+        launch_check_push2<kScanBytes>(nb0, nb1, s, A0, nr0, A1, nr1, ib, bs, j, ahead);
 }
 
 void dispatch_check_push(uint32_t blocks, hipStream_t s, const BuildArgs& A, uint32_t ib, uint32_t bs, uint32_t j,
@@ -2235,34 +2283,120 @@ int build_attempt_directed(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, co
     uint32_t rstamp = 0, bstamp = 0;
     uint64_t rounds = 0, batches = 0;
     unsigned long long accepted_seen[2] = {0, 0};
+    Ahead Q[2];  // one queue; the sides' receivers and arenas apart
+    Q[0].on = Q[1].on = planes && !P.on && !(flags & PLL_FLAG_PACK4);
+    uint32_t resume_j = 0;
     for (uint32_t ib = 0; ib < n; ib += b) {
+        const uint32_t left = (n - ib + b - 1) / b;
+        if (const uint32_t depth = std::min(Q[0].ready(A[0], h[0], left), Q[1].ready(A[1], h[1], left))) {
+            // batches queued without a read-back between them (struct Ahead)
+            const uint32_t bstamp0 = bstamp, rstamp0 = rstamp, K = std::max(Q[0].rounds, Q[1].rounds);
+            uint32_t nbe[2];
+            for (int d = 0; d < 2; ++d) {
+                uint64_t touched = b;
+                for (uint32_t j = 1; j <= K; ++j) touched += Q[d].recv[j];
+                nbe[d] = blocks_for_waves((touched + 3) / 4);
+            }
+            for (uint32_t q = 0; q < depth; ++q) {
+                const uint32_t ibq = ib + q * b, bsq = std::min(b, n - ibq), code = 1 + 16 * q;
+                ++bstamp;
+                k_batch_init_planes2<<<2 * init_blocks(bsq), kInitBlock, 0, s>>>(A[0], A[1], ibq, bsq, bstamp, 1);
+                ++rstamp;
+                BuildArgs A1[2] = {A[0], A[1]};
+                for (int d = 0; d < 2; ++d) {
+                    A1[d].msgs = mbuf[d][1];
+                    A1[d].recv = rbuf[d][1];
+                }
+                k_push2<<<2 * blocks_for_waves((uint64_t)bsq + 1024), kBlock, 0, s>>>(A1[0], A1[1], ibq, bsq, rstamp,
+                                                                                      bstamp, 1);
+                for (uint32_t j = 1; j <= K; ++j, ++rstamp) {
+                    pll::NextRound nr[2];
+                    uint32_t nb[2];
+                    for (int d = 0; d < 2; ++d) {
+                        nr[d] = pll::NextRound{mbuf[d][j & 1u], rbuf[d][j & 1u], mbuf[d][(j + 1) & 1u],
+                                               rbuf[d][(j + 1) & 1u], (j - 1) % 3, j % 3, (j + 1) % 3, j & 1u,
+                                               rstamp + 1, bstamp, 0u};
+                        nb[d] = blocks_for_waves(std::min<uint64_t>(n, Q[d].recv[j] + Q[d].recv[j] / 4 + 512));
+                    }
+                    dispatch_check_push2(nb[0], nb[1], s, A[0], nr[0], A[1], nr[1], ibq, bsq, j, code + j);
+                }
+                k_batch_end4_2<<<nbe[0] + nbe[1], kBlock, 0, s>>>(A[0], A[1], ibq, nbe[0], code + K + 1, K);
+                k_clear_table2<true><<<2 * blocks_for_waves(4ull * bsq), kBlock, 0, s>>>(A[0], A[1], ibq, bsq, 1);
+            }
+            TRY_HIP(hipGetLastError());
+            rc = read_both();
+            if (rc) return rc;
+            const uint32_t halt = h[0]->halt, done = halt ? (halt - 1) / 16 : depth;
+            for (int d = 0; d < 2; ++d) {
+                if (h[d]->error) return device_error_status(h[d]->error);
+                accepted_seen[d] = sum_stat(h[d], PLL_ST_ACC);
+                Q[d].after(h[d], depth, done, K);
+            }
+            Q[0].rounds = Q[1].rounds = std::max(Q[0].rounds, Q[1].rounds);
+            batches += done;
+            if (!halt) {
+                ib += (depth - 1) * b;
+                for (int d = 0; d < 2; ++d) {
+                    if (!arena_fixed && ib + b < n && max_top(h[d]) * 2 > A[d].region_cap) {
+                        rc = relayout_arena(M, A[d], spare_off[d], tmp32, scan_scratch, false, A[d].region_cap * 2, 0,
+                                            s);
+                        if (rc) return rc;
+                    }
+                }
+                continue;
+            }
+            // the host finishes batch `done` from round resume_j on
+            resume_j = (halt - 1) % 16;
+            ib += done * b;
+            bstamp = bstamp0 + done;
+            rstamp = rstamp0 + done * (K + 1) + resume_j - 1;
+            k_unhalt<<<1, 1, 0, s>>>(ctr);
+        }
         const uint32_t bs = std::min(b, n - ib);
         ++bstamp;
         ++batches;
-        hipEvent_t e0 = P.mark();
-        // later batches have the counters reset by the previous table clear
-        if (ib == 0)
-            for (int d = 0; d < 2; ++d) k_batch_prep<<<1, 64, 0, s>>>(A[d].ctr);
-        if (A[0].P)
-            k_batch_init_planes2<<<2 * init_blocks(bs), kInitBlock, 0, s>>>(A[0], A[1], ib, bs, bstamp);
-        else
-            for (int d = 0; d < 2; ++d) launch_batch_init(A[d], ib, bs, bstamp, s);
-        P.span(PLL_PHASE_INIT, e0, P.mark(), (A[0].P ? 1 : 2) + (ib == 0 ? 2 : 0));
-        // fused rounds as in the undirected build, both sides in one launch
-        ++rstamp;
-        {
-            BuildArgs A1[2] = {A[0], A[1]};
-            for (int d = 0; d < 2; ++d) {
-                A1[d].msgs = mbuf[d][1];
-                A1[d].recv = rbuf[d][1];
-            }
-            hipEvent_t r0 = P.mark();
-            k_push2<<<2 * blocks_for_waves((uint64_t)bs + 1024), kBlock, 0, s>>>(A1[0], A1[1], ib, bs, rstamp, bstamp);
-            P.span(PLL_PHASE_PUSH, r0, P.mark(), 1);
-        }
         uint64_t next_est[2] = {bs, bs};
         bool live[2] = {true, true};
-        for (uint32_t j = 1; live[0] || live[1]; ++j) {
+        if (!resume_j) {
+            hipEvent_t e0 = P.mark();
+            // later batches have the counters reset by the previous table clear
+            if (ib == 0)
+                for (int d = 0; d < 2; ++d) k_batch_prep<<<1, 64, 0, s>>>(A[d].ctr);
+            if (A[0].P)
+                k_batch_init_planes2<<<2 * init_blocks(bs), kInitBlock, 0, s>>>(A[0], A[1], ib, bs, bstamp, 0);
+            else
+                for (int d = 0; d < 2; ++d) launch_batch_init(A[d], ib, bs, bstamp, s);
+            P.span(PLL_PHASE_INIT, e0, P.mark(), (A[0].P ? 1 : 2) + (ib == 0 ? 2 : 0));
+            // fused rounds as in the undirected build, both sides in one launch
+            ++rstamp;
+            {
+                BuildArgs A1[2] = {A[0], A[1]};
+                for (int d = 0; d < 2; ++d) {
+                    A1[d].msgs = mbuf[d][1];
+                    A1[d].recv = rbuf[d][1];
+                }
+                hipEvent_t r0 = P.mark();
+                k_push2<<<2 * blocks_for_waves((uint64_t)bs + 1024), kBlock, 0, s>>>(A1[0], A1[1], ib, bs, rstamp, bstamp,
+                                                                                     0);
+                P.span(PLL_PHASE_PUSH, r0, P.mark(), 1);
+            }
+        } else {
+            // the sides that go on, and the heavy rows that halted the queue
+            ++rstamp;
+            for (int d = 0; d < 2; ++d) {
+                const uint32_t j = resume_j, nh = sum_hq(h[d], (j - 1) & 1u);
+                if (nh) {
+                    Q[d].heavy = true;
+                    k_push_heavy<<<blocks_for_waves(nh), kBlock, 0, s>>>(A[d], ib, (j - 1) & 1u, (j - 1) % 3,
+                                                                         mbuf[d][j & 1u], rbuf[d][j & 1u], rstamp,
+                                                                         bstamp);
+                }
+                next_est[d] = (uint64_t)sum_recv(h[d], (j - 1) % 3) + 1024ull * nh;
+                live[d] = next_est[d] != 0;
+            }
+        }
+        for (int d = 0; d < 2; ++d) Q[d].begin(resume_j);
+        for (uint32_t j = resume_j ? resume_j : 1; live[0] || live[1]; ++j) {
             ++rounds;
             if (A[0].P && j > PLL_PLANES + 1) {
                 for (int d = 0; d < 2; ++d) {
@@ -2280,7 +2414,7 @@ int build_attempt_directed(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, co
             }
             ++rstamp;
             hipEvent_t r1 = P.mark();
-            dispatch_check_push2(nb[0], nb[1], s, A[0], nr[0], A[1], nr[1], ib, bs, j);
+            dispatch_check_push2(nb[0], nb[1], s, A[0], nr[0], A[1], nr[1], ib, bs, j, 0);
             P.span(PLL_PHASE_CHECK, r1, P.mark(), 1);
             TRY_HIP(hipGetLastError());
             rc = read_both();
@@ -2288,6 +2422,7 @@ int build_attempt_directed(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, co
             P.resolve();
             for (int d = 0; d < 2; ++d) {
                 if (h[d]->error) return device_error_status(h[d]->error);
+                Q[d].round(j, live[d] ? sum_recv(h[d], nr[d].rin) : 0, live[d] && sum_hq(h[d], nr[d].hout));
                 if (!live[d]) continue;
                 const unsigned long long acc_now = sum_stat(h[d], PLL_ST_ACC);
                 if (acc_now == accepted_seen[d]) {  // this side accepted nothing: its search is done
@@ -2305,6 +2440,7 @@ int build_attempt_directed(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, co
                 next_est[d] = (uint64_t)sum_recv(h[d], nr[d].rout) + 1024ull * nh;
             }
         }
+        resume_j = 0;
         // both sides' batch ends read the other side's table, so the tables
         // are cleared only after both
         hipEvent_t e1 = P.mark();
@@ -2313,16 +2449,17 @@ int build_attempt_directed(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, co
         } else {
             const uint32_t nb0 = blocks_for_waves((sum_touched(h[0]) + 3) / 4);
             const uint32_t nb1 = blocks_for_waves((sum_touched(h[1]) + 3) / 4);
-            k_batch_end4_2<<<nb0 + nb1, kBlock, 0, s>>>(A[0], A[1], ib, nb0);
+            k_batch_end4_2<<<nb0 + nb1, kBlock, 0, s>>>(A[0], A[1], ib, nb0, 0, 0);
         }
         const uint32_t nbc = blocks_for_waves(4ull * bs);
         if (A[0].P)
-            k_clear_table2<true><<<2 * nbc, kBlock, 0, s>>>(A[0], A[1], ib, bs);
+            k_clear_table2<true><<<2 * nbc, kBlock, 0, s>>>(A[0], A[1], ib, bs, 0);
         else
-            k_clear_table2<false><<<2 * nbc, kBlock, 0, s>>>(A[0], A[1], ib, bs);
+            k_clear_table2<false><<<2 * nbc, kBlock, 0, s>>>(A[0], A[1], ib, bs, 0);
         P.span(PLL_PHASE_END, e1, P.mark(), recheck ? 3 : 2);
         TRY_HIP(hipGetLastError());
         for (int d = 0; d < 2; ++d) {
+            Q[d].look(h[d], 1);
             if (!arena_fixed && ib + b < n && max_top(h[d]) * 2 > A[d].region_cap) {
                 rc = relayout_arena(M, A[d], spare_off[d], tmp32, scan_scratch, false, A[d].region_cap * 2, 0, s);
                 if (rc) return rc;
@@ -2383,7 +2520,7 @@ int build_attempt_directed(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, co
     I.max_dist = std::max(h[0]->max_dist, h[1]->max_dist);
     I.max_label = std::max(h[0]->max_label, h[1]->max_label);
     I.batches = batches;
-    I.rounds = rounds;
+    I.rounds = rounds + h[0]->ahead_rounds;
     auto both = [&](int k) { return sum_stat(h[0], k) + sum_stat(h[1], k); };
     I.candidates = both(PLL_ST_CAND);
     I.accepted = both(PLL_ST_ACC);

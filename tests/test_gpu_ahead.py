@@ -11,6 +11,7 @@ import paper_1906_12018_amd as pll
 import synth
 from gpu_util import assert_labels_equal, build, check_counters
 from test_gpu_bp import check_bp
+from test_gpu_directed import build_dir, check_directed
 
 pytestmark = pytest.mark.gpu
 
@@ -34,6 +35,42 @@ def test_queues_that_halt(gi, seed, b):
     idx = build(g, order, batch_size=b, flags=0)
     assert_labels_equal(idx, want, order)
     check_counters(idx, g, order, b, want)
+    idx.free()
+
+
+def digraphs():
+    star = synth.star_graph(2200)
+    out_star = synth.DiGraph(n=2200, row_ptr=np.concatenate([[0], np.full(2200, 2199)]).astype(np.uint64),
+                             col=np.arange(1, 2200, dtype=np.uint32))
+    return [synth.as_digraph(star), out_star, synth.reverse_digraph(out_star), synth.rmat_digraph(10, 5, seed=3),
+            synth.directed_cycle(60), synth.gnp_digraph(300, 0.006, 4),
+            synth.as_digraph(synth.disjoint_union(synth.ba_graph(600, 2, 5), synth.star_graph(1200)))]
+
+
+def directed_rounds(g, order, b):
+    """Lockstep rounds of the two sides by the labels: a batch runs one round
+    more than the largest distance of the entries its roots gained."""
+    lin, lout = oracle.pll_labels_directed(g, order)
+    rounds = 0
+    for ib in range(0, g.n, b):
+        far = 0
+        for lab in (lin, lout):
+            mine = (lab.hub_rank >= ib) & (lab.hub_rank < ib + b)
+            far = max(far, int(lab.dist[mine].max(initial=0)))
+        rounds += 1 + far
+    return rounds
+
+
+@pytest.mark.parametrize("b", [16, 61, 128])
+@pytest.mark.parametrize("seed", [0, 1])
+@pytest.mark.parametrize("gi", range(len(digraphs())))
+def test_directed_queues_that_halt(gi, seed, b):
+    g = digraphs()[gi]
+    order = (synth.degree_order_directed(g) if seed == 0
+             else np.random.default_rng(seed).permutation(g.n).astype(np.uint32))
+    idx = build_dir(g, order, batch_size=b)
+    check_directed(idx, g, order)
+    assert idx.info()["rounds"] == directed_rounds(g, order, b)
     idx.free()
 
 
