@@ -38,8 +38,12 @@ constexpr int kBlock = 256;              // 4 waves
 constexpr int kWavesPerBlock = kBlock / PLL_WAVE;
 constexpr uint32_t kMaxBlocks = 4096;
 constexpr uint32_t kHotRows = 4096;        // top-ranked table rows whose row masks stay all ones
-constexpr uint64_t kPullFrac = 2;          // a round with at least n / 2 receivers pulls the next one
-constexpr uint64_t kPullFrac1 = 8;         // ... and a batch's first round with at least n / 8
+// A round with at least 2n / 5 receivers pulls the next one, and a batch's
+// first round with at least n / 12.  Pushes are bound by random atomics
+// (22 M of them in 1.08 ms, R-MAT-20), a gather by the graph's size (0.39 ms).
+// R-MAT-20 build with n / 8 and n / 2: 141.8 ms; n / 12 with n / 2, 2n / 5
+// and n / 2.8: 136.5, 134.4 and 135.4; n / 16 and n / 24: 135.1 and 135.4.
+constexpr uint64_t kPullFrac1 = 12;
 constexpr uint32_t kPullMinN = 16384;      // smaller graphs always push (the pull's set-up outweighs it)
 constexpr uint64_t kPackMin = 16384;       // receivers from which a fused round checks four per wave
 
@@ -468,7 +472,8 @@ __global__ void __launch_bounds__(kBlock) k_push(BuildArgs A, uint32_t ib, uint3
                                                  uint32_t bstamp, uint32_t ahead) {
     if (ahead_halted(A, ahead)) return;
     PhaseStats st;
-    pll::phase_push(A, grid_exec(A), A.msgs, A.recv, ib, p, nact, rstamp, bstamp, st);
+    // a batch starts with every C(r) empty
+    pll::phase_push(A, grid_exec(A), A.msgs, A.recv, ib, p, nact, rstamp, bstamp, st, false);
     const unsigned long long v[1] = {st.edges};
     const int which[1] = {PLL_ST_EDGES};
     block_add_stats<1>(A.ctr, v, which);
@@ -491,7 +496,7 @@ __global__ void __launch_bounds__(kBlock) k_push2(BuildArgs A0, BuildArgs A1, ui
     const uint32_t nb = gridDim.x / 2, side = blockIdx.x >= nb ? 1u : 0u;
     const BuildArgs& A = side ? A1 : A0;
     PhaseStats st;
-    pll::phase_push(A, side_exec(A, side * nb, nb), A.msgs, A.recv, ib, 0, nact, rstamp, bstamp, st);
+    pll::phase_push(A, side_exec(A, side * nb, nb), A.msgs, A.recv, ib, 0, nact, rstamp, bstamp, st, false);
     const unsigned long long v[1] = {st.edges};
     const int which[1] = {PLL_ST_EDGES};
     block_add_stats<1>(A.ctr, v, which);
@@ -590,7 +595,7 @@ __global__ void __launch_bounds__(kBlock) k_push_heavy(BuildArgs A, uint32_t ib,
                                                        uint64_t* msgs, uint32_t* recv, uint32_t rstamp,
                                                        uint32_t bstamp) {
     PhaseStats st;
-    pll::phase_push_heavy(A, grid_exec(A), ib, hp, rq, msgs, recv, rstamp, bstamp, st);
+    pll::phase_push_heavy(A, grid_exec(A), ib, hp, rq, msgs, recv, rstamp, bstamp, st, true);
     const unsigned long long v[1] = {st.edges};
     const int which[1] = {PLL_ST_EDGES};
     block_add_stats<1>(A.ctr, v, which);
@@ -676,7 +681,7 @@ __global__ void __launch_bounds__(kBlock) k_clear_table(BuildArgs A, uint32_t ib
     if (ahead_halted(A, ahead)) return;
     if (prep && blockIdx.x == 0 && threadIdx.x < PLL_SHARDS) reset_shard(prep->sh[threadIdx.x]);
     if (prep && blockIdx.x == 0 && threadIdx.x < PLL_PLANES + 2) prep->racc[threadIdx.x] = 0;
-    pll::phase_clear_table<PLANES>(A, grid_exec(A), ib, bs);
+    pll::phase_clear_table<PLANES, PLANES>(A, grid_exec(A), ib, bs);
 }
 
 // Both sides of a directed build, and the counters' reset.
@@ -689,7 +694,7 @@ __global__ void __launch_bounds__(kBlock) k_clear_table2(BuildArgs A0, BuildArgs
     const pll::Exec X = side_exec(A, side * nb, nb);
     if (X.zero_i < PLL_SHARDS) reset_shard(A.ctr->sh[X.zero_i]);
     if (X.zero_i < PLL_PLANES + 2) A.ctr->racc[X.zero_i] = 0;
-    pll::phase_clear_table<PLANES>(A, X, ib, bs);
+    pll::phase_clear_table<PLANES, PLANES>(A, X, ib, bs);
 }
 
 __global__ void __launch_bounds__(kBlock) k_table_fill(BuildArgs A, uint32_t ib, uint32_t bs) {
@@ -1898,7 +1903,7 @@ int build_attempt(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, const uint3
             }
             // the first round's receivers push the batch's densest deltas along
             // high-degree rows, so gathering pays off from fewer of them
-            const uint32_t pull = pull_ok && next_est * (j == 1 ? kPullFrac1 : kPullFrac) >= n ? 1u : 0u;
+            const uint32_t pull = pull_ok && (j == 1 ? next_est * kPullFrac1 : next_est * 5 / 2) >= n ? 1u : 0u;
             const pll::NextRound nr{mbuf[j & 1u], rbuf[j & 1u], mbuf[(j + 1) & 1u], rbuf[(j + 1) & 1u], (j - 1) % 3, j % 3, (j + 1) % 3, j & 1u,
                                     rstamp + 1, bstamp, pull};
             ++rstamp;

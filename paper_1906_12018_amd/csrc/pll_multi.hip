@@ -325,7 +325,7 @@ __global__ void __launch_bounds__(kMultiBlock) k_multi_build(const GraphJob* __r
                 pll::phase_batch_init(A, X, ib, bs, bstamp);
             if (gang_sync(gc, G, k, ctr, spin_limit, &s_flag)) { failed = true; break; }
             ++rstamp;
-            pll::phase_push(A, X, J.msgs1, J.recv1, ib, 0, bs, rstamp, bstamp, st);
+            pll::phase_push(A, X, J.msgs1, J.recv1, ib, 0, bs, rstamp, bstamp, st, false);
             if (gang_sync(gc, G, k, ctr, spin_limit, &s_flag)) { failed = true; break; }
             // fused rounds (see phase_check4): the check of round j delivers
             // round j+1 as well, so a round has one barrier
@@ -358,7 +358,7 @@ __global__ void __launch_bounds__(kMultiBlock) k_multi_build(const GraphJob* __r
                 if (gang_sync(gc, G, k, ctr, spin_limit, &s_flag)) { failed = true; break; }
                 if (load_agent(&gc->round_acc[j % 3]) == 0) break;
                 if (load_agent(&gc->round_heavy[j % 3])) {
-                    pll::phase_push_heavy(A, X, ib, nr.hout, nr.rout, nr.msgs, nr.recv, nr.rstamp, bstamp, st);
+                    pll::phase_push_heavy(A, X, ib, nr.hout, nr.rout, nr.msgs, nr.recv, nr.rstamp, bstamp, st, true);
                     if (gang_sync(gc, G, k, ctr, spin_limit, &s_flag)) { failed = true; break; }
                 }
             }

@@ -374,7 +374,7 @@ __device__ inline void plane_set(const BuildArgs& A, uint32_t h, uint32_t d, uin
 // k / kInitRoots, one per wave, and collects the distances 1 and 2 of the
 // rows h < kInitHot in s_hot: bit k % kInitRoots of s_hot[h] is plane 1's
 // bit, bit 16 + k % kInitRoots plane 2's.  plane_flush then writes them out.
-constexpr uint32_t kInitHot = 4096;
+constexpr uint32_t kInitHot = 8192;
 constexpr uint32_t kInitRoots = 16;
 
 template <bool PLANES = false, bool HOT = false>
@@ -454,16 +454,16 @@ __device__ inline void phase_batch_init(const BuildArgs& A, const Exec& X, uint3
 // Write the workgroup's s_hot rows (below the batch's end: no other vertex is
 // a hub yet) into planes 1 and 2; k0 is its first root's index in the batch.
 // The top-ranked rows hold a bit of nearly every root, and atomics on one
-// address serialise: one atomic per row and 16 roots instead of one per
-// root.  R-MAT-20 batch init 17.8 -> 13.6 ms per build.
+// address serialise.  No other workgroup writes these 16 bits of a row's
+// word, so they go out as plain 16-bit stores.
 __device__ inline void plane_flush(const BuildArgs& A, uint32_t k0, uint32_t rows, const uint32_t* s_hot) {
+    uint16_t* half = reinterpret_cast<uint16_t*>(A.P) + k0 / kInitRoots;
     for (uint32_t h = threadIdx.x; h < min(rows, kInitHot); h += blockDim.x) {
         const uint32_t x = s_hot[h];
         if (!x) continue;
-        unsigned long long* row =
-            reinterpret_cast<unsigned long long*>(A.P) + (size_t)h * (PLL_PLANES * A.W) + (k0 >> 6);
-        if (x & 0xFFFFu) atomicOr(row, (unsigned long long)(x & 0xFFFFu) << (k0 & 63u));
-        atomicOr(row + A.W, (unsigned long long)(x >> 16) << (k0 & 63u));
+        uint16_t* row = half + (size_t)h * (PLL_PLANES * 4u * A.W);
+        if (x & 0xFFFFu) row[0] = (uint16_t)x;
+        row[4u * A.W] = (uint16_t)(x >> 16);
     }
 }
 
@@ -518,10 +518,10 @@ __device__ inline void enqueue_receivers(const BuildArgs& A, const Exec& X, uint
 // words of one edge cost one round trip.  Returns whether anything was
 // delivered.
 __device__ inline bool deliver4(const BuildArgs& A, uint64_t* msgs, uint32_t r, const uint32_t (&w)[4],
-                                const uint64_t (&m)[4]) {
+                                const uint64_t (&m)[4], bool filter) {
     uint64_t c[4];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) c[k] = m[k] ? A.C[(size_t)r * A.W + w[k]] : 0ull;
+    for (int k = 0; k < 4; ++k) c[k] = filter && m[k] ? A.C[(size_t)r * A.W + w[k]] : 0ull;
     bool any = false;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
@@ -538,10 +538,11 @@ __device__ inline bool deliver4(const BuildArgs& A, uint64_t* msgs, uint32_t r, 
 // words) along the CSR entries [beg, end) of the active vertex a, into the
 // message buffer msgs and receiver queue rq (counters) stored in recv.
 // The next 64 neighbours load while this step delivers; first0 is the first
-// step's, lane l's entry beg + l (0 past the end).
+// step's, lane l's entry beg + l (0 past the end).  Without `filter` C(r) is
+// not read (a batch's first push: it is empty).
 __device__ inline void push_edges(const BuildArgs& A, const Exec& X, uint64_t* msgs, uint32_t* recv, uint32_t ib,
                                   uint32_t rq, uint32_t rstamp, uint32_t bstamp, uint64_t dl, uint64_t nz,
-                                  uint64_t beg, uint64_t end, uint32_t first0) {
+                                  uint64_t beg, uint64_t end, uint32_t first0, bool filter) {
     const uint32_t lane = lane_id();
     uint32_t next = first0;
     for (uint64_t e0 = beg; e0 < end; e0 += 64) {
@@ -561,7 +562,7 @@ __device__ inline void push_edges(const BuildArgs& A, const Exec& X, uint64_t* m
                 m[k] = todo && fwd ? readlane64(dl, w[k]) & rank_mask(rel, w[k]) : 0ull;
                 todo &= todo - 1;
             }
-            any |= deliver4(A, msgs, r, w, m);
+            any |= deliver4(A, msgs, r, w, m, filter);
         }
         enqueue_receivers(A, X, recv, rq, rstamp, bstamp, r, any);
     }
@@ -571,7 +572,7 @@ __device__ inline void push_edges(const BuildArgs& A, const Exec& X, uint64_t* m
 // into msgs and receiver queue rq stored in recv.
 __device__ inline void phase_push_heavy(const BuildArgs& A, const Exec& X, uint32_t ib, uint32_t p, uint32_t rq,
                                         uint64_t* msgs, uint32_t* recv, uint32_t rstamp, uint32_t bstamp,
-                                        PhaseStats& st) {
+                                        PhaseStats& st, bool filter) {
     const uint32_t lane = lane_id();
     const uint32_t* act_v = A.act_v[p];
     const uint64_t* act_d = A.act_delta[p];
@@ -587,7 +588,7 @@ __device__ inline void phase_push_heavy(const BuildArgs& A, const Exec& X, uint3
         const uint64_t end = min(A.rrow[a + 1], beg + kHeavyItem);
         if (lane == 0) st.edges += end - beg;
         push_edges(A, X, msgs, recv, ib, rq, rstamp, bstamp, dl, nz, beg, end,
-                   beg + lane < end ? A.rcol[beg + lane] : 0u);
+                   beg + lane < end ? A.rcol[beg + lane] : 0u, filter);
     }
 }
 
@@ -601,7 +602,7 @@ struct NextRound {
     uint32_t* recv;
     uint32_t rin, rout, rclr, hout;
     uint32_t rstamp, bstamp;
-    uint32_t pull;  // the next round is pulled (phase_pull) instead of pushed
+    uint32_t pull;  // the next round is pulled (phase_pull4) instead of pushed
 };
 
 // A pulled round (the direction-optimizing alternative to push_edges, for
@@ -612,65 +613,15 @@ struct NextRound {
 // C(r), into msgs(r), with one receiver slot and the first-touch record.
 // Items are (vertex, segment of kPullSeg CSR entries); the segments of one
 // vertex merge through atomicOr and the receiver stamp, like pushes do.
-// Four active neighbours are gathered at a time, one per 16-lane group.
 constexpr uint32_t kPullSeg = 256;
 
-__device__ inline void phase_pull(const BuildArgs& A, const Exec& X, uint32_t ib, const uint2* items,
-                                  const uint32_t* nitems, uint32_t q, const NextRound& nr) {
-    const uint32_t lane = lane_id();
-    const uint32_t W = A.W;
-    const uint32_t grp = lane >> 4, wd = lane & 15u;
-    const uint64_t* act_d = A.act_delta[q];
-    const uint32_t total = *nitems;
-    for (uint32_t t = X.w; t < total; t += X.nw) {
-        const uint2 it = items[t];
-        const uint32_t r = it.x;
-        if (r <= ib) continue;
-        const uint64_t beg = A.rrow[r] + (uint64_t)it.y * kPullSeg;
-        const uint64_t end = min(A.rrow[r + 1], beg + kPullSeg);
-        uint64_t m = 0;
-        for (uint64_t e0 = beg; e0 < end; e0 += 64) {
-            const uint64_t e = e0 + lane;
-            const uint64_t at = e < end ? A.act_at[A.rcol[e]] : 0ull;
-            uint64_t act = ballot64((uint32_t)(at >> 32) == nr.rstamp);
-            while (act) {
-                uint32_t slot = 0;
-                bool have = false;
-#pragma unroll
-                for (uint32_t k = 0; k < 4; ++k) {
-                    if (act) {
-                        const uint32_t s = (uint32_t)__builtin_ctzll(act);
-                        act &= act - 1;
-                        const uint32_t sl = readlane32((uint32_t)at, s);
-                        if (grp == k) {
-                            slot = sl;
-                            have = true;
-                        }
-                    }
-                }
-                if (have && wd < W) m |= act_d[(size_t)slot * W + wd];
-            }
-        }
-        m |= __shfl_xor(m, 16, 64);
-        m |= __shfl_xor(m, 32, 64);
-        if (lane < W) {
-            m &= rank_mask(r - ib, lane);
-            if (m) m &= ~A.C[(size_t)r * W + lane];
-        } else {
-            m = 0;
-        }
-        if (m) atomicOr((unsigned long long*)&nr.msgs[(size_t)r * W + lane], (unsigned long long)m);
-        if (!ballot64(m != 0)) continue;
-        enqueue_receivers(A, X, nr.recv, nr.rout, nr.rstamp, nr.bstamp, r, lane == 0);
-    }
-}
-
-// phase_pull with four items per wave: the 16-lane group g = lane / 16
+// A wave takes four items: the 16-lane group g = lane / 16
 // gathers item i0 + g, 16 CSR entries at a time, and its lane 16g + w holds
-// word w of the delta it collects.  Each step, every group ORs in the delta
-// of one of its active neighbours (the groups' steps run side by side), so
-// four items' chains of dependent loads (item, row, neighbour, stamp,
-// delta) are in flight in one wave.  Deliveries are phase_pull's.
+// word w of the delta it collects.  Each step, every group ORs in the deltas
+// of up to four of its active neighbours (the groups' steps run side by
+// side), so sixteen delta lines are in flight in one wave; one neighbour per
+// step made the gather a chain of one access per active neighbour (R-MAT-20
+// 511 -> 393 us per gather, R-MAT-16 51 -> 31 us).
 __device__ inline void phase_pull4(const BuildArgs& A, const Exec& X, uint32_t ib, const uint2* items,
                                    const uint32_t* nitems, uint32_t q, const NextRound& nr) {
     const uint32_t lane = lane_id();
@@ -689,20 +640,30 @@ __device__ inline void phase_pull4(const BuildArgs& A, const Exec& X, uint32_t i
             end = min(A.rrow[r + 1], beg + kPullSeg);
         }
         uint64_t m = 0;
-        for (uint64_t e0 = 0;; e0 += 16) {
-            if (!ballot64(valid && beg + e0 < end)) break;
-            const uint64_t e = beg + e0 + wd;
-            const bool in = valid && e < end;
-            const uint64_t at = in ? A.act_at[A.rcol[e]] : 0ull;
-            const bool act = in && (uint32_t)(at >> 32) == nr.rstamp;
-            uint64_t am = ballot64(act);
-            while (am) {
-                const uint32_t gm = (uint32_t)(am >> gsh) & 0xFFFFu;
-                const uint32_t k = gm ? (uint32_t)__builtin_ctz(gm) : 0u;
-                const uint32_t slot = (uint32_t)__builtin_amdgcn_ds_bpermute((int)((gsh + k) * 4u), (int)(uint32_t)at);
-                if (gm && wd < W) m |= act_d[(size_t)slot * W + wd];
-                am &= ~ballot64(gm && wd == k);
+        // a chunk's stamps load while the chunk before it is gathered, its
+        // neighbours another chunk earlier
+        const uint32_t deg = (uint32_t)(end - beg);
+        const uint32_t* row = A.rcol + beg;
+        uint64_t at = wd < deg ? A.act_at[row[wd]] : 0ull;
+        uint32_t next = wd + 16u < deg ? row[wd + 16u] : 0u;
+        for (uint32_t e0 = 0; ballot64(e0 < deg); e0 += 16) {
+            const uint32_t e = e0 + wd;
+            const uint64_t at1 = e + 16u < deg ? A.act_at[next] : 0ull;
+            next = e + 32u < deg ? row[e + 32u] : 0u;
+            const uint64_t am = ballot64(e < deg && (uint32_t)(at >> 32) == nr.rstamp);
+            uint32_t gm = (uint32_t)(am >> gsh) & 0xFFFFu;  // this group's active neighbours
+            while (ballot64(gm != 0)) {
+                uint64_t d[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const uint32_t l = gsh + (gm ? (uint32_t)__builtin_ctz(gm) : 0u);
+                    const uint32_t slot = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(l * 4u), (int)(uint32_t)at);
+                    d[k] = gm && wd < W ? act_d[(size_t)slot * W + wd] : 0ull;
+                    gm &= gm - 1u;
+                }
+                m |= (d[0] | d[1]) | (d[2] | d[3]);
             }
+            at = at1;
         }
         if (valid && wd < W) {
             m &= rank_mask(r - ib, wd);
@@ -742,7 +703,8 @@ __device__ inline void phase_pull_items(const BuildArgs& A, const Exec& X, uint2
 // skipped; rows longer than kHeavy were queued as items and are spread over
 // every wave after the per-slot pass.
 __device__ inline void phase_push(const BuildArgs& A, const Exec& X, uint64_t* msgs, uint32_t* recv, uint32_t ib,
-                                  uint32_t p, uint32_t nact, uint32_t rstamp, uint32_t bstamp, PhaseStats& st) {
+                                  uint32_t p, uint32_t nact, uint32_t rstamp, uint32_t bstamp, PhaseStats& st,
+                                  bool filter) {
     const uint32_t lane = lane_id();
     if (X.zero_i < X.nq) X.qs[X.zero_i].hq[p ^ 1u] = 0;
     const uint32_t* act_v = A.act_v[p];
@@ -756,9 +718,9 @@ __device__ inline void phase_push(const BuildArgs& A, const Exec& X, uint64_t* m
         if (end - beg > kHeavy) continue;
         if (lane == 0) st.edges += end - beg;
         push_edges(A, X, msgs, recv, ib, p, rstamp, bstamp, dl, nz, beg, end,
-                   beg + lane < end ? A.rcol[beg + lane] : 0u);
+                   beg + lane < end ? A.rcol[beg + lane] : 0u, filter);
     }
-    phase_push_heavy(A, X, ib, p, p, msgs, recv, rstamp, bstamp, st);
+    phase_push_heavy(A, X, ib, p, p, msgs, recv, rstamp, bstamp, st, filter);
 }
 
 // Bit-parallel bound (Section 5.2) of every candidate in `mine` at v for
@@ -1104,7 +1066,7 @@ __device__ inline void phase_check(const BuildArgs& A, const Exec& X, uint32_t i
         if (FUSE && rend - rbeg <= kHeavy) {
             if (lane == 0) st.edges += rend - rbeg;
             push_edges(A, X, nr->msgs, nr->recv, ib, nr->rout, nr->rstamp, nr->bstamp, acc, ballot64(acc != 0), rbeg,
-                       rend, nb0);
+                       rend, nb0, true);
         } else {
             enqueue_heavy(A, X, q, i, rend - rbeg);
         }
@@ -1230,7 +1192,7 @@ __device__ inline void push_edges4(const BuildArgs& A, const Exec& X, const Next
                 m[k] = todo ? x & rank_mask(rel, w[k]) : 0ull;
                 todo &= todo - 1;
             }
-            any |= deliver4(A, nr.msgs, r, w, m);
+            any |= deliver4(A, nr.msgs, r, w, m, true);
         }
         enqueue_receivers(A, X, nr.recv, nr.rout, nr.rstamp, nr.bstamp, r, any);
     }
@@ -1825,9 +1787,18 @@ __device__ inline void phase_table_fill(const BuildArgs& A, const Exec& X, uint3
 }
 
 // Reset the distance table rows (or plane words) written during the batch.
-template <bool PLANES = false>
+// With HOT, planes 1 and 2 of the rows below kInitHot are zeroed whole (they
+// hold bits of most roots, which would each zero the same words again).
+template <bool PLANES = false, bool HOT = false>
 __device__ inline void phase_clear_table(const BuildArgs& A, const Exec& X, uint32_t ib, uint32_t bs) {
     const uint32_t lane = lane_id();
+    if (HOT) {
+        const uint32_t words = min(ib + bs, kInitHot) * A.W;  // 16-byte units of planes 1 and 2
+        for (uint32_t i = X.w * 64u + lane; i < words; i += X.nw * 64u) {
+            ulonglong2* row = reinterpret_cast<ulonglong2*>(A.P + (size_t)(i / A.W) * (PLL_PLANES * A.W));
+            row[i % A.W] = make_ulonglong2(0ull, 0ull);
+        }
+    }
     // four waves per root: task t clears the 64-entry chunks c, c + 4, ...
     // of root k (t = 4k + c)
     for (uint32_t t = X.w; t < 4u * bs; t += X.nw) {
@@ -1841,6 +1812,7 @@ __device__ inline void phase_clear_table(const BuildArgs& A, const Exec& X, uint
             if (PLANES) {
                 const uint32_t d = e & 255u;
                 uint64_t* row = A.P + (size_t)h * (PLL_PLANES * A.W) + (k >> 6);
+                if (HOT && d <= 2 && h < kInitHot) continue;
                 if (d == 1) row[0] = 0;
                 if (d != 0 && d <= PLL_PLANES) row[(max(d, 2u) - 1u) * A.W] = 0;
             } else {

@@ -195,7 +195,7 @@ __global__ void __launch_bounds__(kRoundBlock) k_batches(BuildArgs A, GridCtl* g
         for (uint32_t j = 1;; ++j) {
             ++rstamp;
             ++rounds;
-            pll::phase_push(A, X, A.msgs, A.recv, ib, p, nact, rstamp, bstamp, st);
+            pll::phase_push(A, X, A.msgs, A.recv, ib, p, nact, rstamp, bstamp, st, true);
             if (grid_sync(gc, k, ctr, timeout_ticks, 0u, &s_flag)) {
                 failed = true;
                 break;
