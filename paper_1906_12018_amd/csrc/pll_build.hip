@@ -148,6 +148,10 @@ hipError_t scan_u32_to_u64(const uint32_t* in, uint64_t n, uint64_t* out, uint64
 }
 
 // ---- input checks and relabelling ---------------------------------------------------------------
+//
+// All of it is queued before the error word is read once: the kernels that
+// follow pointers or ids of the input (from k_check_csr on) do nothing when
+// an earlier check found an error.
 
 __global__ void k_check_rowptr(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, DevCounters* ctr) {
     for (uint64_t v = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; v <= n; v += (uint64_t)gridDim.x * blockDim.x) {
@@ -179,10 +183,11 @@ __global__ void k_check_order_counts(uint32_t n, const uint32_t* cnt, DevCounter
 
 // Full CSR check (flag PLL_FLAG_VALIDATE): each row strictly ascending, no
 // self-loop, and (`symmetric`, undirected graphs) every edge present in both
-// directions.  Runs only after the row pointers and column ids passed the
-// bounds checks.
+// directions.  Does nothing unless the row pointers and column ids passed
+// the bounds checks (its own error bit does not stop its workgroups).
 __global__ void __launch_bounds__(kBlock) k_check_csr(uint32_t n, const uint64_t* row_ptr, const uint32_t* col,
                                                       uint32_t symmetric, const uint8_t* w, DevCounters* ctr) {
+    if (ctr->error & (PLL_ERR_BOUNDS | PLL_ERR_ORDER)) return;
     const uint32_t lane = lane_id();
     for (uint32_t v = global_wave(); v < n; v += num_waves()) {
         const uint64_t beg = row_ptr[v], end = row_ptr[v + 1];
@@ -204,11 +209,14 @@ __global__ void __launch_bounds__(kBlock) k_check_csr(uint32_t n, const uint64_t
     }
 }
 
-__global__ void k_make_rank(uint32_t n, const uint32_t* order, uint32_t* rank) {
+__global__ void k_make_rank(uint32_t n, const uint32_t* order, uint32_t* rank, const DevCounters* ctr) {
+    if (ctr->error) return;
     for (uint32_t k = blockIdx.x * blockDim.x + threadIdx.x; k < n; k += gridDim.x * blockDim.x) rank[order[k]] = k;
 }
 
-__global__ void k_rank_degrees(uint32_t n, const uint32_t* order, const uint64_t* row_ptr, uint32_t* deg) {
+__global__ void k_rank_degrees(uint32_t n, const uint32_t* order, const uint64_t* row_ptr, uint32_t* deg,
+                               const DevCounters* ctr) {
+    if (ctr->error) return;
     for (uint32_t k = blockIdx.x * blockDim.x + threadIdx.x; k < n; k += gridDim.x * blockDim.x) {
         uint32_t v = order[k];
         deg[k] = (uint32_t)(row_ptr[v + 1] - row_ptr[v]);
@@ -219,7 +227,9 @@ __global__ void k_rank_degrees(uint32_t n, const uint32_t* order, const uint64_t
 // neighbour replaced by its rank (neighbour order kept).
 __global__ void __launch_bounds__(kBlock) k_relabel_cols(uint32_t n, const uint32_t* order, const uint64_t* row_ptr,
                                                          const uint32_t* col, const uint32_t* rank,
-                                                         const uint64_t* rrow, uint32_t* rcol) {
+                                                         const uint64_t* rrow, uint32_t* rcol,
+                                                         const DevCounters* ctr) {
+    if (ctr->error) return;
     const uint32_t lane = lane_id();
     for (uint32_t k = global_wave(); k < n; k += num_waves()) {
         const uint32_t v = order[k];
@@ -658,7 +668,9 @@ __global__ void __launch_bounds__(kBlock) k_batch_end_w(BuildArgs A, uint32_t ib
 
 // Weights follow their CSR entries into rank space.
 __global__ void __launch_bounds__(kBlock) k_relabel_weights(uint32_t n, const uint32_t* order, const uint64_t* row_ptr,
-                                                            const uint8_t* w, const uint64_t* rrow, uint8_t* rw) {
+                                                            const uint8_t* w, const uint64_t* rrow, uint8_t* rw,
+                                                            const DevCounters* ctr) {
+    if (ctr->error) return;
     const uint32_t lane = lane_id();
     for (uint32_t k = global_wave(); k < n; k += num_waves()) {
         const uint32_t v = order[k];
@@ -1320,9 +1332,11 @@ int relayout_arena(DevAllocs& M, BuildArgs& A, uint64_t*& spare_off, uint32_t* c
     const uint32_t n = A.n;
     k_list_caps<<<blocks_for_threads(n), kBlock, 0, s>>>(n, A.rrow, A.llen, first ? 1u : 0u, caps);
     TRY_HIP(scan_u32_to_u64(caps, n, spare_off, scan_scratch, s));
-    uint64_t lists = 0;
-    TRY_HIP(hipMemcpyAsync(&lists, spare_off + n, sizeof(uint64_t), hipMemcpyDeviceToHost, s));
-    TRY_HIP(hipStreamSynchronize(s));
+    uint64_t lists = 32ull * n;  // the first layout's at most
+    if (!first || fixed_total) {
+        TRY_HIP(hipMemcpyAsync(&lists, spare_off + n, sizeof(uint64_t), hipMemcpyDeviceToHost, s));
+        TRY_HIP(hipStreamSynchronize(s));
+    }
     const uint64_t base = (lists + 63) & ~63ull;
     if (fixed_total) {
         if (fixed_total < base + PLL_SHARDS * 16ull) return PLL_ENOSPC;
@@ -1335,8 +1349,10 @@ int relayout_arena(DevAllocs& M, BuildArgs& A, uint64_t*& spare_off, uint32_t* c
     TRY_HIP(hipMemcpyAsync(A.lcap, caps, sizeof(uint32_t) * n, hipMemcpyDeviceToDevice, s));
     k_reset_tops<<<1, 64, 0, s>>>(A.ctr);
     TRY_HIP(hipGetLastError());
-    TRY_HIP(hipStreamSynchronize(s));
-    if (A.arena) M.drop(A.arena);
+    if (A.arena) {
+        TRY_HIP(hipStreamSynchronize(s));
+        M.drop(A.arena);
+    }
     std::swap(A.loff, spare_off);
     A.arena = na;
     A.region_base = base;
@@ -1370,44 +1386,38 @@ int prepare_rank_csr(DevAllocs& M, DevCounters* ctr, DevCounters* h, uint32_t n,
     TRY_HIP(hipMemsetAsync(tmp32, 0, sizeof(uint32_t) * n, s));
     k_count_order<<<blocks_for_threads(n), kBlock, 0, s>>>(n, order, tmp32, ctr);
     k_check_order_counts<<<blocks_for_threads(n), kBlock, 0, s>>>(n, tmp32, ctr);
-    TRY_HIP(hipGetLastError());
-    int rc = read_counters(ctr, h, s);
-    if (rc) return rc;
-    if (h->error) return PLL_EINVAL;
     if (nnz) k_check_cols<<<blocks_for_threads(nnz), kBlock, 0, s>>>(n, nnz, col, ctr);
     if (nnz && w) k_check_weights<<<blocks_for_threads(nnz), kBlock, 0, s>>>(nnz, w, ctr);
-    rc = read_counters(ctr, h, s);
-    if (rc) return rc;
-    if (h->error) return PLL_EINVAL;
-    if (flags & PLL_FLAG_VALIDATE) {
+    if (flags & PLL_FLAG_VALIDATE)
         k_check_csr<<<blocks_for_waves(n), kBlock, 0, s>>>(n, row_ptr, col, symmetric ? 1u : 0u, w, ctr);
-        rc = read_counters(ctr, h, s);
-        if (rc) return rc;
-        if (h->error) return PLL_EINVAL;
-    }
     // rank space (a0)
-    k_make_rank<<<blocks_for_threads(n), kBlock, 0, s>>>(n, order, R->rank);
-    k_rank_degrees<<<blocks_for_threads(n), kBlock, 0, s>>>(n, order, row_ptr, tmp32);
+    k_make_rank<<<blocks_for_threads(n), kBlock, 0, s>>>(n, order, R->rank, ctr);
+    k_rank_degrees<<<blocks_for_threads(n), kBlock, 0, s>>>(n, order, row_ptr, tmp32, ctr);
     TRY_HIP(scan_u32_to_u64(tmp32, n, R->rrow, R->scan_scratch, s));
-    k_relabel_cols<<<blocks_for_waves(n), kBlock, 0, s>>>(n, order, row_ptr, col, R->rank, R->rrow, R->rcol);
+    k_relabel_cols<<<blocks_for_waves(n), kBlock, 0, s>>>(n, order, row_ptr, col, R->rank, R->rrow, R->rcol, ctr);
     if (w) {
         R->rw = M.get<uint8_t>(nnz ? nnz : 1);
         if (M.err != hipSuccess) return status_of(M.err);
-        k_relabel_weights<<<blocks_for_waves(n), kBlock, 0, s>>>(n, order, row_ptr, w, R->rrow, R->rw);
+        k_relabel_weights<<<blocks_for_waves(n), kBlock, 0, s>>>(n, order, row_ptr, w, R->rrow, R->rw, ctr);
     }
     TRY_HIP(hipGetLastError());
-    return PLL_OK;
+    const int rc = read_counters(ctr, h, s);
+    if (rc) return rc;
+    return h->error ? PLL_EINVAL : PLL_OK;
 }
+
+size_t blk(size_t bytes) { return (std::max<size_t>(bytes, 256) + 255) & ~size_t(255); }
 
 // Working buffers of the batch phases over the rank-space CSR (rrow, rcol);
 // the pruning checks read the build's own table until the caller says
 // otherwise.  With `planes` the table is kept as bit planes (BuildArgs::P)
 // and the byte table T stays null until planes_to_bytes.  The row masks of
-// the first hot_rows table rows stay all ones.
+// the first hot_rows rows of a byte table stay all ones.  *msgs1 (if asked
+// for) is the second message buffer of the fused rounds.
 // Returns the spare offsets array of the arena relayout.
 int init_state(DevAllocs& M, BuildArgs& A, uint32_t n, uint64_t nnz, uint32_t W, const uint64_t* rrow,
                const uint32_t* rcol, DevCounters* ctr, hipStream_t s, uint64_t** spare_off,
-               bool planes, uint32_t hot_rows = kHotRows) {
+               bool planes, uint64_t** msgs1, uint32_t hot_rows = kHotRows) {
     A = BuildArgs{};
     A.n = n;
     A.W = W;
@@ -1416,19 +1426,20 @@ int init_state(DevAllocs& M, BuildArgs& A, uint32_t n, uint64_t nnz, uint32_t W,
     A.rcol = rcol;
     A.loff = M.get<uint64_t>((size_t)n + 1);
     *spare_off = M.get<uint64_t>((size_t)n + 1);
-    A.llen = M.get<uint32_t>(n);
     A.lcap = M.get<uint32_t>(n);
-    A.C = M.get<uint64_t>((size_t)n * W);
-    A.msgs = M.get<uint64_t>((size_t)n * W);
     static_assert(PLL_PLANES == 8, "the planes of a row take the bytes of a byte-table row");
-    if (planes)
-        A.P = M.get<uint64_t>((size_t)n * PLL_PLANES * W);
-    else
-        A.T = M.get<uint8_t>((size_t)n * A.bstride);
-    A.rowmask = M.get<uint64_t>(n);
-    A.Tchk = A.T;
-    A.Pchk = A.P;
-    A.rmchk = A.rowmask;
+    if (!planes) A.T = M.get<uint8_t>((size_t)n * A.bstride);
+    // what starts at zero lies in one block, cleared at once
+    size_t zero_bytes = 0;
+    auto zero = [&](size_t bytes) {
+        const size_t at = zero_bytes;
+        zero_bytes += blk(bytes);
+        return at;
+    };
+    const size_t z_llen = zero(4ull * n), z_rs = zero(4ull * n), z_ts = zero(4ull * n), z_rm = zero(8ull * n);
+    const size_t z_C = zero(8ull * n * W), z_m0 = zero(8ull * n * W), z_m1 = msgs1 ? zero(8ull * n * W) : 0;
+    const size_t z_P = planes ? zero((size_t)n * A.bstride) : 0;
+    char* z = M.get<char>(zero_bytes);
     A.hq_seg = 2 * (nnz / pll::kHeavyItem) + 64;
     for (int q = 0; q < 2; ++q) {
         A.act_v[q] = M.get<uint32_t>(n);
@@ -1436,24 +1447,27 @@ int init_state(DevAllocs& M, BuildArgs& A, uint32_t n, uint64_t nnz, uint32_t W,
         A.hq[q] = M.get<uint2>(PLL_SHARDS * A.hq_seg);
     }
     A.recv = M.get<uint32_t>((size_t)PLL_SHARDS * n);
-    A.recv_stamp = M.get<uint32_t>(n);
     A.touched = M.get<uint32_t>((size_t)PLL_SHARDS * n);
     A.tstart = M.get<uint32_t>((size_t)PLL_SHARDS * n);
-    A.touch_stamp = M.get<uint32_t>(n);
     A.ctr = ctr;
     if (M.err != hipSuccess) return status_of(M.err);
-    TRY_HIP(hipMemsetAsync(A.llen, 0, sizeof(uint32_t) * n, s));
-    TRY_HIP(hipMemsetAsync(A.C, 0, sizeof(uint64_t) * n * W, s));
-    TRY_HIP(hipMemsetAsync(A.msgs, 0, sizeof(uint64_t) * n * W, s));
-    if (planes)
-        TRY_HIP(hipMemsetAsync(A.P, 0, (size_t)n * A.bstride, s));
-    else
-        TRY_HIP(hipMemsetAsync(A.T, 0xFF, (size_t)n * A.bstride, s));
+    A.llen = reinterpret_cast<uint32_t*>(z + z_llen);
+    A.recv_stamp = reinterpret_cast<uint32_t*>(z + z_rs);
+    A.touch_stamp = reinterpret_cast<uint32_t*>(z + z_ts);
+    A.rowmask = reinterpret_cast<uint64_t*>(z + z_rm);
+    A.C = reinterpret_cast<uint64_t*>(z + z_C);
+    A.msgs = reinterpret_cast<uint64_t*>(z + z_m0);
+    if (msgs1) *msgs1 = reinterpret_cast<uint64_t*>(z + z_m1);
+    if (planes) A.P = reinterpret_cast<uint64_t*>(z + z_P);
+    A.Tchk = A.T;
+    A.rmchk = A.rowmask;
+    A.Pchk = A.P;
     A.hot = std::min<uint32_t>(n, hot_rows);
-    TRY_HIP(hipMemsetAsync(A.rowmask, 0xFF, sizeof(uint64_t) * A.hot, s));
-    TRY_HIP(hipMemsetAsync(A.rowmask + A.hot, 0, sizeof(uint64_t) * (n - A.hot), s));
-    TRY_HIP(hipMemsetAsync(A.recv_stamp, 0, sizeof(uint32_t) * n, s));
-    TRY_HIP(hipMemsetAsync(A.touch_stamp, 0, sizeof(uint32_t) * n, s));
+    TRY_HIP(hipMemsetAsync(z, 0, zero_bytes, s));
+    if (!planes) {
+        TRY_HIP(hipMemsetAsync(A.T, 0xFF, (size_t)n * A.bstride, s));
+        TRY_HIP(hipMemsetAsync(A.rowmask, 0xFF, sizeof(uint64_t) * A.hot, s));
+    }
     return PLL_OK;
 }
 
@@ -1461,21 +1475,15 @@ int init_state(DevAllocs& M, BuildArgs& A, uint32_t n, uint64_t nnz, uint32_t W,
 // build goes on with the byte table, filled from the labels the batch's
 // roots hold now, for the rest of this batch and all later ones (a graph
 // that gets here once has long distances, and mostly would in every batch).
-// The planes' memory becomes the table's where nothing can be allocated.
-// The stream has drained.  The caller points Tchk at the table to check.
-int planes_to_bytes(DevAllocs& M, BuildArgs& A, uint32_t ib, uint32_t bs, hipStream_t s) {
-    const size_t bytes = (size_t)A.n * A.bstride;
-    if (M.fixed) {
-        A.T = reinterpret_cast<uint8_t*>(A.P);
-    } else {
-        M.drop(A.P);
-        A.T = M.get<uint8_t>(bytes);
-        if (M.err != hipSuccess) return status_of(M.err);
-    }
+// The planes' memory becomes the table's.  The caller points Tchk at the
+// table to check.
+int planes_to_bytes(BuildArgs& A, uint32_t ib, uint32_t bs, hipStream_t s) {
+    A.T = reinterpret_cast<uint8_t*>(A.P);
     A.P = nullptr;
     A.Pchk = nullptr;
     A.Tchk = A.T;
-    TRY_HIP(hipMemsetAsync(A.T, 0xFF, bytes, s));
+    TRY_HIP(hipMemsetAsync(A.T, 0xFF, (size_t)A.n * A.bstride, s));
+    TRY_HIP(hipMemsetAsync(A.rowmask, 0xFF, sizeof(uint64_t) * A.hot, s));
     k_table_fill<<<blocks_for_waves(bs), kBlock, 0, s>>>(A, ib, bs);
     TRY_HIP(hipGetLastError());
     return PLL_OK;
@@ -1592,6 +1600,14 @@ struct Ahead {
     unsigned long long growth = 0;  // per batch since then
     bool fits = false;              // every round of the last batch could be queued
 
+    // A graph whose rounds cannot reach kPackMin receivers queues its first
+    // batch as well, with the usual four rounds.
+    void start(uint32_t n) {
+        if (n >= kPackMin) return;
+        rounds = 4;
+        fits = true;
+        for (uint64_t& r : recv) r = n;
+    }
     void look(const DevCounters* h, uint32_t batches_run) {
         const unsigned long long t = max_top(h);
         growth = t >= top ? (t - top) / std::max(batches_run, 1u) : t;
@@ -1679,8 +1695,10 @@ int build_attempt(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, const uint3
     // leaves the top rows sparse: their masks are kept exact then
     // the persistent loop and the recheck (testing: the byte table is their
     // only form) keep the byte table throughout
+    uint64_t* mbuf1 = nullptr;
     const bool planes = !(flags & (PLL_FLAG_PERSISTENT | PLL_FLAG_RECHECK | PLL_FLAG_RELAXED));
-    rc = init_state(M, A, n, nnz, W, RC.rrow, RC.rcol, ctr, s, &spare_off, planes, bp_req ? 0u : kHotRows);
+    rc = init_state(M, A, n, nnz, W, RC.rrow, RC.rcol, ctr, s, &spare_off, planes,
+                    flags & PLL_FLAG_PERSISTENT ? nullptr : &mbuf1, bp_req ? 0u : kHotRows);
     if (rc) return rc;
     // the round-2 neighbour check needs every higher-ranked neighbour to be a
     // hub, which bit-parallel roots (taken out of the labels) break
@@ -1728,7 +1746,7 @@ int build_attempt(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, const uint3
     }
     // the second message buffer and receiver list of the fused rounds:
     // round j's messages and receivers live in mbuf[j & 1] and rbuf[j & 1]
-    uint64_t* mbuf[2] = {A.msgs, nullptr};
+    uint64_t* mbuf[2] = {A.msgs, mbuf1};
     uint32_t* rbuf[2] = {A.recv, nullptr};
     // pulled rounds: a round whose receivers number at least n / kPullFrac
     // (the active vertices of the next round are among them) gathers at
@@ -1738,10 +1756,8 @@ int build_attempt(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, const uint3
     uint64_t pull_cap = 0;
     const bool pull_ok = !(flags & PLL_FLAG_PERSISTENT) && n >= kPullMinN;
     if (!(flags & PLL_FLAG_PERSISTENT)) {
-        mbuf[1] = M.get<uint64_t>((size_t)n * W);
         rbuf[1] = M.get<uint32_t>((size_t)PLL_SHARDS * n);
         if (M.err != hipSuccess) return status_of(M.err);
-        TRY_HIP(hipMemsetAsync(mbuf[1], 0, sizeof(uint64_t) * n * W, s));
     }
     if (pull_ok) {
         pull_cap = (uint64_t)n + nnz / pll::kPullSeg + 1;
@@ -1793,6 +1809,12 @@ int build_attempt(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, const uint3
         k_edge_end<<<std::min<uint32_t>(blocks_for_threads(n), 1024), kBlock, 0, s>>>(n, A.rrow, ctr);
         TRY_HIP(hipGetLastError());
     }
+    auto find_skip = [&](uint32_t ib) {  // batch ib runs: skipping starts after it
+        if (skip_known) return;
+        skip_known = true;
+        const uint64_t from = std::max<uint64_t>(((uint64_t)h->edge_end + b - 1) / b * b, (uint64_t)ib + b);
+        if (from < n) skip_from = (uint32_t)from;
+    };
     // round 1's receivers (the neighbours of the batch) are only counted
     // after its launch; its grid is sized by the previous batch's count,
     // which falls from batch to batch in rank order (a grid-stride loop
@@ -1800,6 +1822,7 @@ int build_attempt(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, const uint3
     uint64_t r1_est = n;
     Ahead Q;
     Q.on = A.P && !P.on && !trace && !(flags & PLL_FLAG_PACK4);
+    Q.start(n);
     uint32_t resume_j = 0;  // the queue began this batch; the host goes on at this round
     for (uint32_t ib = 0; !(flags & PLL_FLAG_PERSISTENT) && ib < n; ib += b) {
         if (ib >= skip_from) {
@@ -1808,11 +1831,12 @@ int build_attempt(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, const uint3
             rounds += left;
             break;
         }
-        if (const uint32_t depth = skip_known ? Q.ready(A, h, (skip_from - ib + b - 1) / b) : 0) {
+        if (const uint32_t depth = Q.ready(A, h, (skip_from - ib + b - 1) / b)) {
             // batches queued without a read-back between them (struct Ahead)
             const uint32_t bstamp0 = bstamp, rstamp0 = rstamp, K = Q.rounds;
             uint64_t touched = b;
             for (uint32_t j = 1; j <= K; ++j) touched += Q.recv[j];
+            if (ib == 0) k_batch_prep<<<1, 64, 0, s>>>(ctr);
             for (uint32_t d = 0; d < depth; ++d) {
                 const uint32_t ibd = ib + d * b, bsd = std::min(b, n - ibd), code = 1 + 16 * d;
                 ++bstamp;
@@ -1838,6 +1862,7 @@ int build_attempt(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, const uint3
             if (rc) return rc;
             if (h->error) return device_error_status(h->error);
             accepted_seen = sum_stat(h, PLL_ST_ACC);
+            find_skip(ib);
             const uint32_t done = h->halt ? (h->halt - 1) / 16 : depth;
             batches += done;
             Q.after(h, depth, done, K);
@@ -1898,7 +1923,7 @@ int build_attempt(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, const uint3
         for (uint32_t j = resume_j ? resume_j : 1;; ++j) {
             ++rounds;
             if (A.P && j > PLL_PLANES + 1) {
-                rc = planes_to_bytes(M, A, ib, bs, s);
+                rc = planes_to_bytes(A, ib, bs, s);
                 if (rc) return rc;
             }
             // the first round's receivers push the batch's densest deltas along
@@ -1925,11 +1950,7 @@ int build_attempt(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, const uint3
             rc = read_counters(ctr, h, s);
             if (rc) return rc;
             P.resolve();
-            if (!skip_known) {  // this batch runs: skipping starts after it
-                skip_known = true;
-                const uint64_t from = std::max<uint64_t>(((uint64_t)h->edge_end + b - 1) / b * b, (uint64_t)ib + b);
-                if (from < n) skip_from = (uint32_t)from;
-            }
+            find_skip(ib);
             const unsigned long long acc_now = sum_stat(h, PLL_ST_ACC);
             if (j == 1) r1_est = std::max<uint64_t>(bs, sum_recv(h, nr.rin));
             Q.round(j, sum_recv(h, nr.rin), sum_hq(h, nr.hout) != 0);
@@ -1975,11 +1996,13 @@ int build_attempt(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, const uint3
         }
     }
 
-    // --- finalize (a8): CSR by vertex id, hubs as ranks
-    rc = read_counters(ctr, h, s);
-    if (rc) return rc;
-    if (h->error) return device_error_status(h->error);
-    P.resolve();
+    // --- finalize (a8): CSR by vertex id, hubs as ranks (the batch ends
+    // since the last read-back raise no errors)
+    if (P.on) {
+        rc = read_counters(ctr, h, s);
+        if (rc) return rc;
+        P.resolve();
+    }
     hipEvent_t e_fin = P.mark();
     uint64_t* d_off = nullptr;
     uint32_t* d_ent = nullptr;
@@ -2086,7 +2109,7 @@ int build_attempt_weighted(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, co
     if (rc) return rc;
     BuildArgs A{};
     uint64_t* spare_off = nullptr;
-    rc = init_state(M, A, n, nnz, W, RC.rrow, RC.rcol, ctr, s, &spare_off, false);
+    rc = init_state(M, A, n, nnz, W, RC.rrow, RC.rcol, ctr, s, &spare_off, false, nullptr);
     if (rc) return rc;
     A.rw = RC.rw;
     A.D = M.get<uint8_t>((size_t)n * A.bstride);
@@ -2252,10 +2275,11 @@ int build_attempt_directed(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, co
     // side 0: forward (L_in, out-arcs); side 1: backward (L_out, in-arcs)
     BuildArgs A[2];
     uint64_t* spare_off[2] = {nullptr, nullptr};
+    uint64_t* mbuf1[2] = {nullptr, nullptr};
     const bool planes = !(flags & PLL_FLAG_RECHECK);
-    rc = init_state(M, A[0], n, nnz, W, RC.rrow, RC.rcol, ctr, s, &spare_off[0], planes);
+    rc = init_state(M, A[0], n, nnz, W, RC.rrow, RC.rcol, ctr, s, &spare_off[0], planes, &mbuf1[0]);
     if (rc) return rc;
-    rc = init_state(M, A[1], n, nnz, W, irow, icol, ctr + 1, s, &spare_off[1], planes);
+    rc = init_state(M, A[1], n, nnz, W, irow, icol, ctr + 1, s, &spare_off[1], planes, &mbuf1[1]);
     if (rc) return rc;
     for (int d = 0; d < 2; ++d) {
         A[d].Tchk = A[d ^ 1].T;
@@ -2263,13 +2287,11 @@ int build_attempt_directed(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, co
         A[d].rmchk = A[d ^ 1].rowmask;
     }
     // second message buffer and receiver list of each side's fused rounds
-    uint64_t* mbuf[2][2] = {{A[0].msgs, nullptr}, {A[1].msgs, nullptr}};
+    uint64_t* mbuf[2][2] = {{A[0].msgs, mbuf1[0]}, {A[1].msgs, mbuf1[1]}};
     uint32_t* rbuf[2][2] = {{A[0].recv, nullptr}, {A[1].recv, nullptr}};
     for (int d = 0; d < 2; ++d) {
-        mbuf[d][1] = M.get<uint64_t>((size_t)n * W);
         rbuf[d][1] = M.get<uint32_t>((size_t)PLL_SHARDS * n);
         if (M.err != hipSuccess) return status_of(M.err);
-        TRY_HIP(hipMemsetAsync(mbuf[d][1], 0, sizeof(uint64_t) * n * W, s));
     }
     const uint64_t region_cap = std::max<uint64_t>(4096, arena_hint / (2 * PLL_SHARDS));
     for (int d = 0; d < 2; ++d) {
@@ -2289,7 +2311,10 @@ int build_attempt_directed(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, co
     uint64_t rounds = 0, batches = 0;
     unsigned long long accepted_seen[2] = {0, 0};
     Ahead Q[2];  // one queue; the sides' receivers and arenas apart
-    Q[0].on = Q[1].on = planes && !P.on && !(flags & PLL_FLAG_PACK4);
+    for (Ahead& q : Q) {
+        q.on = planes && !P.on && !(flags & PLL_FLAG_PACK4);
+        q.start(n);
+    }
     uint32_t resume_j = 0;
     for (uint32_t ib = 0; ib < n; ib += b) {
         const uint32_t left = (n - ib + b - 1) / b;
@@ -2297,6 +2322,8 @@ int build_attempt_directed(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, co
             // batches queued without a read-back between them (struct Ahead)
             const uint32_t bstamp0 = bstamp, rstamp0 = rstamp, K = std::max(Q[0].rounds, Q[1].rounds);
             uint32_t nbe[2];
+            if (ib == 0)
+                for (int d = 0; d < 2; ++d) k_batch_prep<<<1, 64, 0, s>>>(A[d].ctr);
             for (int d = 0; d < 2; ++d) {
                 uint64_t touched = b;
                 for (uint32_t j = 1; j <= K; ++j) touched += Q[d].recv[j];
@@ -2405,7 +2432,7 @@ int build_attempt_directed(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, co
             ++rounds;
             if (A[0].P && j > PLL_PLANES + 1) {
                 for (int d = 0; d < 2; ++d) {
-                    rc = planes_to_bytes(M, A[d], ib, bs, s);
+                    rc = planes_to_bytes(A[d], ib, bs, s);
                     if (rc) return rc;
                 }
                 for (int d = 0; d < 2; ++d) A[d].Tchk = A[d ^ 1].T;
@@ -2473,11 +2500,11 @@ int build_attempt_directed(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, co
     }
 
     // --- finalize: L_in and L_out by vertex id
-    rc = read_both();
-    if (rc) return rc;
-    for (int d = 0; d < 2; ++d)
-        if (h[d]->error) return device_error_status(h[d]->error);
-    P.resolve();
+    if (P.on) {
+        rc = read_both();
+        if (rc) return rc;
+        P.resolve();
+    }
     hipEvent_t e_fin = P.mark();
     uint64_t* d_off[2] = {nullptr, nullptr};
     uint32_t* d_ent[2] = {nullptr, nullptr};
@@ -2692,8 +2719,6 @@ static __device__ __align__(256) uint8_t scratch[kScratchBytes];
 std::mutex g_scratch_mu[kMaxDevices];       // one allocation-free build at a time per device
 void* g_scratch_ptr[kMaxDevices];           // device address of `scratch`, set once per device under its mutex
 DevCounters g_scratch_host[kMaxDevices];    // host copy of the build's counters
-
-size_t blk(size_t bytes) { return (std::max<size_t>(bytes, 256) + 255) & ~size_t(255); }
 
 // Bytes build_attempt carves before its label arena and final CSR for a
 // graph of n vertices and nnz CSR entries at W words per candidate
