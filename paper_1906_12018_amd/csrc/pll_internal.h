@@ -46,6 +46,7 @@ enum {
     PLL_ST_COST_NEG = 8, // sum of |L(v)| over checks that pruned
     PLL_ST_BP = 9,       // candidates pruned by the bit-parallel bound
     PLL_ST_FUSED_EDGES = 10,  // CSR entries pushed inside the fused check-and-push launches
+    PLL_ST_ACC_EDGES = 11,    // weighted: CSR entries of the vertices that accepted (a pulled round's edges)
     PLL_NUM_ST = 12
 };
 

@@ -172,7 +172,7 @@ __global__ void __launch_bounds__(kMultiBlock) k_multi_build(const GraphJob* __r
                                                              GraphResult* results, MultiCtl* ctl, DevCounters* ctr,
                                                              uint32_t* out, uint32_t b, uint32_t flags) {
     __shared__ uint64_t s_pres[kMultiWaves][PLL_WMAX];
-    __shared__ uint8_t s_dist[kMultiWaves][PLL_BMAX];
+    __shared__ __align__(16) uint8_t s_dist[kMultiWaves][PLL_BMAX];
     __shared__ uint64_t s_wsum[kMultiWaves];
     __shared__ uint64_t s_carry;
     __shared__ uint32_t s_slot, s_err, s_flag;

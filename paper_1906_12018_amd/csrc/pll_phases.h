@@ -1341,6 +1341,77 @@ __device__ inline void phase_check4(const BuildArgs& A, const Exec& X, uint32_t 
     }
 }
 
+// Per byte: min(x + d, 255) with dd = d * 0x01010101.  The low 7 bits of
+// each byte are added without carries leaving the byte; the carry out of
+// bit 7 marks the bytes that saturate.
+__device__ inline uint32_t add_sat4(uint32_t x, uint32_t dd) {
+    const uint32_t H = 0x80808080u;
+    const uint32_t low = (x & ~H) + (dd & ~H);
+    const uint32_t sum = low ^ ((x ^ dd) & H);
+    const uint32_t ovf = ((x & dd) | ((x | dd) & ~sum)) & H;
+    return sum | ((ovf >> 7) * 0xFFu);
+}
+
+// Bit i: min(p[i] + d, 255) <= thr[i], for 64 consecutive table bytes p and
+// thresholds thr (le4_flags compares bytes against any per-byte threshold).
+__device__ inline uint64_t sum_le_mask64(const uint8_t* p, uint32_t dd, const uint4* thr) {
+    const uint4* q = reinterpret_cast<const uint4*>(p);
+    uint64_t m = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint4 v = q[i];
+        const uint4 t = thr[i];
+        const uint32_t b = gather16(le4_flags(add_sat4(v.x, dd), t.x), le4_flags(add_sat4(v.y, dd), t.y),
+                                    le4_flags(add_sat4(v.z, dd), t.z), le4_flags(add_sat4(v.w, dd), t.w));
+        m |= (uint64_t)b << (16 * i);
+    }
+    return m;
+}
+
+// prune_scan with a distance per candidate: s_thr (LDS, 64 * W bytes) holds
+// D(v); candidate u_k is pruned when some entry (h, d) of the list has
+// T[h][k] + d <= D(v)[k].  Lanes beyond the live candidates are masked off,
+// so bytes of 255 (no candidate) never count.  RECHECK: the candidates are
+// entries of the list themselves, and none counts as covered by its own hub
+// (ib: the batch's first rank).
+template <int WM, bool RECHECK = false>
+__device__ inline uint64_t prune_scan_w(const BuildArgs& A, uint64_t off, uint32_t len, uint64_t cw,
+                                        const uint4* s_thr, uint32_t ib, PhaseStats& st) {
+    const uint32_t lane = lane_id();
+    uint64_t pw = 0;
+    // one pass per word that still holds live candidates, its prunes reduced
+    // at once, and the next chunk's entries loaded ahead, as in prune_scan
+    uint32_t next = lane < len ? A.arena[off + lane] : 0u;
+    for (uint32_t base = 0; base < len; base += 64) {
+        const uint32_t idx = base + lane;
+        const bool ok = idx < len;
+        st.read += ok;
+        const uint32_t ent = next;
+        next = idx + 64 < len ? A.arena[off + idx + 64] : 0u;
+        const uint32_t h = ent >> 8;
+        const uint64_t rm = ok ? A.rmchk[h] : 0ull;
+        const uint32_t dd = (ent & 255u) * 0x01010101u;
+        const uint8_t* row = A.Tchk + (size_t)h * A.bstride;
+        const uint64_t live_lane = cw & ~pw;
+        uint64_t lw = ballot64(live_lane != 0) & (WM >= 64 ? ~0ull : ((1ull << WM) - 1ull));
+        while (lw) {
+            const uint32_t w = (uint32_t)__builtin_ctzll(lw);
+            lw &= lw - 1;
+            uint64_t m = 0;
+            if ((rm >> (4 * w)) & 15u) {
+                m = sum_le_mask64(row + 64u * w, dd, s_thr + 4 * w);
+                st.table += 4;
+                const uint32_t self = h - ib;
+                if (RECHECK && self >> 6 == w) m &= ~(1ull << (self & 63u));
+            }
+            const uint64_t red = wave_or64_u(m);
+            if (lane == w) pw |= red & live_lane;
+        }
+        if (!ballot64((cw & ~pw) != 0)) break;
+    }
+    return pw;
+}
+
 // Write the batch entries (u_k, s_dist[k]) of the hubs k set in s_pres (W
 // words) to the arena from `at` on, in ascending hub rank; returns how many.
 __device__ inline uint32_t segment_emit(const BuildArgs& A, uint32_t ib, uint64_t at, const uint64_t* s_pres,
@@ -1423,40 +1494,26 @@ __device__ inline void phase_batch_end(const BuildArgs& A, const Exec& X, uint32
         }
         wave_lds_sync();
         if (recheck) {
+            // one scan for all entries, each at its own distance.  No order
+            // among them matters: a canonical entry is never covered by
+            // another hub, and every other one is by a canonical hub.
             const bool in_batch = v - ib < bs;
-            uint32_t prev = 0;
-            for (;;) {
-                uint32_t mn = PLL_INF8;
-                for (uint32_t k = lane; k < bs; k += 64) {
-                    const uint32_t d = s_dist[k];
-                    if (((s_pres[k >> 6] >> (k & 63)) & 1ull) && d > prev) mn = min(mn, d);
+            const uint64_t pr = prune_scan_w<WM, true>(A, off, len, lane < W ? s_pres[lane] : 0ull,
+                                                       reinterpret_cast<const uint4*>(s_dist), ib, st);
+            if (lane < W && pr) s_pres[lane] &= ~pr;
+            st.removed += __builtin_popcountll(pr);
+            if (in_batch) {
+                uint64_t todo = ballot64(pr != 0);
+                while (todo) {
+                    const uint32_t w = (uint32_t)__builtin_ctzll(todo);
+                    todo &= todo - 1;
+                    if ((readlane64(pr, w) >> lane) & 1ull)
+                        A.T[(size_t)(ib + w * 64u + lane) * A.bstride + (v - ib)] = (uint8_t)PLL_INF8;
                 }
-                mn = wave_min32(mn);
-                if (mn == PLL_INF8) break;
-                uint64_t cw = 0;
-                if (lane < W) {
-                    const uint64_t pw = s_pres[lane];
-                    for (uint32_t bit = 0; bit < 64; ++bit) {
-                        const uint32_t k = lane * 64u + bit;
-                        if (((pw >> bit) & 1ull) && s_dist[k] == mn) cw |= 1ull << bit;
-                    }
-                }
-                const uint64_t pr = prune_scan<WM>(A, off, len, mn, cw, false, ib, st);
-                if (lane < W && pr) s_pres[lane] &= ~pr;
-                st.removed += __builtin_popcountll(pr);
-                if (in_batch) {
-                    uint64_t todo = ballot64(pr != 0);
-                    while (todo) {
-                        const uint32_t w = (uint32_t)__builtin_ctzll(todo);
-                        todo &= todo - 1;
-                        if ((readlane64(pr, w) >> lane) & 1ull)
-                            A.T[(size_t)(ib + w * 64u + lane) * A.bstride + (v - ib)] = (uint8_t)PLL_INF8;
-                    }
-                }
-                wave_lds_sync();
-                prev = mn;
             }
+            wave_lds_sync();
         }
+        // emit the batch segment in ascending hub rank
         const uint32_t total = segment_emit(A, ib, off + ts, s_pres, s_dist);
         if (lane == 0 && total != tail) A.llen[v] = ts + total;
         wave_lds_sync();
@@ -1542,79 +1599,6 @@ __device__ inline void phase_batch_end4(const BuildArgs& A, const Exec& X, uint3
 // delta L) rather than a bit-vector.  Entries accepted on the way may be
 // non-canonical; the batch-end recheck removes them.
 
-// Per byte: min(x + d, 255) with dd = d * 0x01010101.  The low 7 bits of
-// each byte are added without carries leaving the byte; the carry out of
-// bit 7 marks the bytes that saturate.
-__device__ inline uint32_t add_sat4(uint32_t x, uint32_t dd) {
-    const uint32_t H = 0x80808080u;
-    const uint32_t low = (x & ~H) + (dd & ~H);
-    const uint32_t sum = low ^ ((x ^ dd) & H);
-    const uint32_t ovf = ((x & dd) | ((x | dd) & ~sum)) & H;
-    return sum | ((ovf >> 7) * 0xFFu);
-}
-
-// Bit i: min(p[i] + d, 255) <= thr[i], for 64 consecutive table bytes p and
-// thresholds thr (le4_flags compares bytes against any per-byte threshold).
-__device__ inline uint64_t sum_le_mask64(const uint8_t* p, uint32_t dd, const uint4* thr) {
-    const uint4* q = reinterpret_cast<const uint4*>(p);
-    uint64_t m = 0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const uint4 v = q[i];
-        const uint4 t = thr[i];
-        const uint32_t b = gather16(le4_flags(add_sat4(v.x, dd), t.x), le4_flags(add_sat4(v.y, dd), t.y),
-                                    le4_flags(add_sat4(v.z, dd), t.z), le4_flags(add_sat4(v.w, dd), t.w));
-        m |= (uint64_t)b << (16 * i);
-    }
-    return m;
-}
-
-// prune_scan with a distance per candidate: s_thr (LDS, 64 * W bytes) holds
-// D(v); candidate u_k is pruned when some entry (h, d) of the list has
-// T[h][k] + d <= D(v)[k].  Lanes beyond the live candidates are masked off,
-// so bytes of 255 (no candidate) never count.
-template <int WM>
-__device__ inline uint64_t prune_scan_w(const BuildArgs& A, uint64_t off, uint32_t len, uint64_t cw,
-                                        const uint4* s_thr, PhaseStats& st) {
-    const uint32_t lane = lane_id();
-    uint64_t pw = 0;
-    uint64_t accm[WM];
-#pragma unroll
-    for (int w = 0; w < WM; ++w) accm[w] = 0;
-    uint32_t chunk = 0;
-    for (uint32_t base = 0; base < len; base += 64, ++chunk) {
-        const uint32_t idx = base + lane;
-        const bool ok = idx < len;
-        st.read += ok;
-        const uint32_t ent = ok ? A.arena[off + idx] : 0u;
-        const uint32_t h = ent >> 8;
-        const uint64_t rm = ok ? A.rmchk[h] : 0ull;
-        const uint32_t dd = (ent & 255u) * 0x01010101u;
-        const uint8_t* row = A.Tchk + (size_t)h * A.bstride;
-        const uint64_t live_lane = cw & ~pw;
-#pragma unroll
-        for (int w = 0; w < WM; ++w) {
-            const uint64_t live = readlane64(live_lane, w);
-            if (live != 0 && ((rm >> (4 * w)) & 15u)) {
-                accm[w] |= sum_le_mask64(row + 64u * w, dd, s_thr + 4 * w) & live;
-                st.table += 4;
-            }
-        }
-        if ((chunk & 3u) == 3u || base + 64 >= len) {
-#pragma unroll
-            for (int w = 0; w < WM; ++w) {
-                if (readlane64(live_lane, w)) {
-                    const uint64_t red = wave_or64_u(accm[w]);
-                    if (lane == (uint32_t)w) pw |= red;
-                    accm[w] = 0;
-                }
-            }
-            if (!ballot64((cw & ~pw) != 0)) break;
-        }
-    }
-    return pw;
-}
-
 // D[p] = min(D[p], nd) on one byte (a compare-and-swap on its aligned word);
 // true when this call lowered it.
 __device__ inline bool byte_atomic_min(uint8_t* p, uint32_t nd) {
@@ -1697,6 +1681,105 @@ __device__ inline void phase_push_w(const BuildArgs& A, const Exec& X, uint32_t 
     }
 }
 
+// A pulled round for weighted graphs: one wave per (vertex r > ib, segment of
+// kPullSeg CSR entries) of `items`.  It collects the smallest candidate
+// distance of every root in LDS (s_min, b words) from the entries that r's
+// active neighbours accepted last round (act_at carries that round's stamp),
+// then lowers D(r) and sets the message bits where that is shorter than
+// D(r): the same D, messages and receivers as push_edges_w's byte minima.
+// The pushes are bound by those minima (a read, a compare-and-swap and an OR
+// at scattered addresses per edge and entry); here an entry of an edge costs
+// a coalesced 4-byte read and an LDS minimum, and D(r) is read and written
+// once.  64 neighbours' records load side by side, and their entries are
+// walked as one concatenated range, so short entry lists fill the wave.
+constexpr uint32_t kPullWUnroll = 4;
+
+__device__ inline void phase_pull_w(const BuildArgs& A, const Exec& X, uint32_t ib, uint32_t bs, const uint2* items,
+                                    const uint32_t* nitems, uint32_t p, uint32_t rstamp, uint32_t bstamp,
+                                    uint32_t* s_min, uint32_t* s_end) {
+    const uint32_t lane = lane_id();
+    const uint32_t W = A.W;
+    if (X.zero_i < X.nq) X.qs[X.zero_i].hq[p ^ 1u] = 0;
+    const uint32_t total = *nitems;
+    for (uint32_t t = X.w; t < total; t += X.nw) {
+        const uint2 it = items[t];
+        const uint32_t r = it.x;
+        if (r <= ib) continue;
+        const uint32_t rel = min(r - ib, bs);  // roots ranked above r
+        const uint64_t rbeg = A.rrow[r], rend = A.rrow[r + 1];
+        const uint64_t beg = rbeg + (uint64_t)it.y * kPullSeg, end = min(rend, beg + kPullSeg);
+        bool met = false;
+        for (uint64_t e0 = beg; e0 < end; e0 += 64) {
+            const uint64_t e = e0 + lane;
+            bool act = e < end;
+            const uint32_t c = act ? A.rcol[e] : 0u;
+            const uint32_t wt = act ? A.rw[e] : 0u;
+            const uint64_t at = act ? A.act_at[c] : 0ull;
+            act = act && (uint32_t)(at >> 32) == rstamp - 1u;
+            if (!ballot64(act)) continue;
+            const uint2 rg = act ? A.act_rng[p][(uint32_t)at] : make_uint2(0u, 0u);
+            uint64_t off = (act ? A.loff[c] : 0ull) + rg.x;
+            const uint32_t pre = wave_excl_scan32(rg.y);
+            const uint32_t tot = readlane32(pre + rg.y, 63);
+            off -= pre;  // entry x of the concatenation is arena[off + x]
+            wave_lds_sync();
+            s_end[lane] = pre + rg.y;
+            if (!met)
+                for (uint32_t k = lane; k < 64u * W; k += 64) s_min[k] = ~0u;
+            met = true;
+            wave_lds_sync();
+            for (uint32_t x0 = 0; x0 < tot; x0 += 64u * kPullWUnroll) {
+                uint32_t ent[kPullWUnroll], w[kPullWUnroll];
+#pragma unroll
+                for (uint32_t u = 0; u < kPullWUnroll; ++u) {
+                    const uint32_t x = x0 + 64u * u + lane;
+                    // the neighbour whose entries hold x: the first whose end is above x
+                    uint32_t l = 0;
+#pragma unroll
+                    for (uint32_t step = 32; step; step >>= 1)
+                        if (s_end[l + step - 1u] <= x) l += step;
+                    l = min(l, 63u);
+                    const uint64_t o = shfl64(off, l);
+                    w[u] = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(l * 4u), (int)wt);
+                    ent[u] = x < tot ? A.arena[o + x] : ~0u;
+                }
+#pragma unroll
+                for (uint32_t u = 0; u < kPullWUnroll; ++u) {
+                    const uint32_t k = (ent[u] >> 8) - ib;
+                    if (x0 + 64u * u + lane < tot && k < rel) atomicMin(&s_min[k], (ent[u] & 255u) + w[u]);
+                }
+            }
+        }
+        if (!met) continue;
+        wave_lds_sync();
+        // rows of one segment are this wave's alone; the segments of a longer
+        // one meet in D(r) and msgs(r)
+        const bool alone = rend - rbeg <= kPullSeg;
+        bool any = false, over = false;
+        for (uint32_t k0 = 0; k0 < rel; k0 += 64) {
+            const uint32_t k = k0 + lane;
+            const uint32_t m = k < rel ? s_min[k] : ~0u;
+            bool low = false;
+            if (m != ~0u) {
+                uint8_t* pd = A.D + (size_t)r * A.bstride + k;
+                const uint32_t old = *pd;
+                // too long for the labels, and nothing shorter has come
+                over = over || (m >= PLL_INF8 && old == PLL_INF8);
+                low = m < PLL_INF8 && m < old;
+                if (low && alone) *pd = (uint8_t)m;
+                if (low && !alone) low = byte_atomic_min(pd, m);
+            }
+            const uint64_t bits = ballot64(low);
+            if (!bits) continue;
+            any = true;
+            if (lane == 0)
+                atomicOr((unsigned long long*)&A.msgs[(size_t)r * W + (k0 >> 6)], (unsigned long long)bits);
+        }
+        if (ballot64(over) && lane == 0) atomicOr(&A.ctr->error, PLL_ERR_DIST);
+        enqueue_receivers(A, X, A.recv, p, rstamp, bstamp, r, any && lane == 0);
+    }
+}
+
 // Gather phase for weighted graphs: the candidates of receiver v are the
 // bits of msgs(v); candidate u_k has distance D(v)[k], staged in this
 // wave's LDS s_thr (64 * W bytes).  Survivors are appended with that
@@ -1704,7 +1787,7 @@ __device__ inline void phase_push_w(const BuildArgs& A, const Exec& X, uint32_t 
 // the batch end keeps the last one); the slot records where they start.
 template <int WM>
 __device__ inline void phase_check_w(const BuildArgs& A, const Exec& X, uint32_t ib, uint32_t bs, uint32_t p,
-                                     uint4* s_thr, PhaseStats& st) {
+                                     uint32_t rstamp, uint4* s_thr, PhaseStats& st) {
     const uint32_t lane = lane_id();
     const uint32_t W = A.W;
     const uint32_t q = p ^ 1u;
@@ -1726,7 +1809,7 @@ __device__ inline void phase_check_w(const BuildArgs& A, const Exec& X, uint32_t
         wave_lds_sync();
         const uint32_t len = A.llen[v];
         uint64_t off = A.loff[v];
-        const uint64_t pw = prune_scan_w<WM>(A, off, len, mine, s_thr, st);
+        const uint64_t pw = prune_scan_w<WM>(A, off, len, mine, s_thr, ib, st);
         const uint64_t acc = lane < W ? (mine & ~pw) : 0ull;
         const uint32_t cnt = (uint32_t)__builtin_popcountll(acc);
         const uint32_t pos = wave_excl_scan32(cnt);
@@ -1760,7 +1843,12 @@ __device__ inline void phase_check_w(const BuildArgs& A, const Exec& X, uint32_t
                         }
                     }
                 }
-                if (lane == 0) A.llen[v] = len + total;
+                if (lane == 0) {
+                    A.llen[v] = len + total;
+                    // for a pulled next round: where v's entries are, and its edges
+                    A.act_at[v] = ((uint64_t)rstamp << 32) | i;
+                    st.pulled += A.rrow[v + 1] - A.rrow[v];
+                }
                 enqueue_heavy(A, X, q, i, A.rrow[v + 1] - A.rrow[v]);
             } else if (lane == 0) {
                 A.act_rng[q][i] = make_uint2(len, 0u);

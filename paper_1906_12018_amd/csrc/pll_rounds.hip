@@ -146,7 +146,7 @@ __global__ void __launch_bounds__(kRoundBlock) k_batches(BuildArgs A, GridCtl* g
                                                          uint32_t flags, uint32_t bstamp0, uint32_t rstamp0,
                                                          uint64_t timeout_ticks, uint32_t compact) {
     __shared__ uint64_t s_pres[kRoundWaves][PLL_WMAX];
-    __shared__ uint8_t s_dist[kRoundWaves][PLL_BMAX];
+    __shared__ __align__(16) uint8_t s_dist[kRoundWaves][PLL_BMAX];
     __shared__ unsigned long long s_part[kRoundWaves];
     __shared__ uint32_t s_flag, s_acc, s_nact;
 
