@@ -1642,6 +1642,7 @@ struct Ahead {
         if (resume_j) return;
         fits = true;
         heavy = false;
+        for (uint64_t& r : recv) r = 0;
     }
     void round(uint32_t j, uint64_t receivers, bool heavy_rows) {
         heavy = heavy || heavy_rows;
@@ -2172,7 +2173,7 @@ int build_attempt_weighted(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, co
             } else {
                 k_push_w<<<blocks_for_waves(nact + heavy_waves), kBlock, 0, s>>>(A, ib, p, nact, rstamp, bstamp);
             }
-            acc_edges_seen = rounds == 1 ? 0 : sum_stat(h, PLL_ST_ACC_EDGES);
+            acc_edges_seen = sum_stat(h, PLL_ST_ACC_EDGES);
             hipEvent_t r1 = P.mark();
             dispatch_check_w(blocks_for_waves(std::min<uint64_t>(n, 16ull * nact + 2048)), s, A, ib, bs, p, rstamp);
             hipEvent_t r2 = P.mark();

@@ -12,6 +12,7 @@ import synth
 from gpu_util import assert_labels_equal, build, check_counters
 from test_gpu_bp import check_bp
 from test_gpu_directed import build_dir, check_directed
+from test_gpu_weighted import build_w, check_weighted
 
 pytestmark = pytest.mark.gpu
 
@@ -71,6 +72,17 @@ def test_directed_queues_that_halt(gi, seed, b):
     idx = build_dir(g, order, batch_size=b)
     check_directed(idx, g, order)
     assert idx.info()["rounds"] == directed_rounds(g, order, b)
+    idx.free()
+
+
+@pytest.mark.parametrize("n,b", [(1500, 256), (4000, 1024)])
+def test_weighted_rounds_gathered_and_pushed(n, b):
+    # dense first batches gather, later ones push; rows of several gather
+    # segments beside short ones
+    g = synth.with_weights(synth.disjoint_union(synth.ba_graph(n, 6, 3), synth.star_graph(700)))
+    order = synth.degree_order(g)
+    idx = build_w(g, order, batch_size=b)
+    check_weighted(idx, g, order)
     idx.free()
 
 
