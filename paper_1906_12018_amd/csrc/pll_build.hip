@@ -849,73 +849,97 @@ __global__ void k_bp_seed(uint32_t t, const uint32_t* roots, const uint32_t* nbr
     }
 }
 
-// Level L+1 of every BP root, pushed from the vertices at level L: a
-// neighbour that is unreached, or already reached at L+1 in this launch,
-// is at L+1 and ORs in the vertex's S^-1 and S^0 (a member s of S_r at
-// distance L - 1 or L from a parent is at distance L or L + 1 from the
-// child).  The sets of level L are final here and nothing at level L is
-// written, so the pushes of one launch do not interfere.
-__global__ void __launch_bounds__(kBlock) k_bp_push(uint32_t n, uint32_t t, uint32_t L, const uint64_t* rrow,
-                                                    const uint32_t* rcol, uint8_t* bp_dist, ulonglong2* bp_sets,
-                                                    DevCounters* ctr) {
+// Level L of every BP root, gathered per (vertex, segment of pll::kPullSeg
+// CSR entries): with rl (a power of two, at least t) lanes over the roots,
+// 64 / rl neighbours are read side by side, their distances (t consecutive
+// bytes) and sets (16 t bytes) coalesced, four steps in flight.
+//
+// !SIB: a vertex that a root has not reached (or has just reached, or seeded)
+// with a neighbour at level L - 1 is at level L and ORs in that neighbour's
+// S^-1 and S^0 (a member s of S_r at distance L - 2 or L - 1 from a parent is
+// at distance L - 1 or L from the child).  SIB, after it: S^0 of a vertex at
+// level L gains S^-1 of every neighbour at the same level, then drops what
+// its S^-1 holds; the (vertex, root) pairs at level L are counted into the
+// first shard's receiver counter (the loop stops at 0).  Neither writes what
+// it reads of a neighbour.  Segments of one row meet through atomics.
+//
+// Pushing each level along the rows, one root at a time, took two 64-bit
+// atomics per edge and root and one access chain per root (R-MAT-16, 16
+// roots: 1.9 ms of pushes and 1.6 ms of sibling passes per build).
+template <bool SIB>
+__global__ void __launch_bounds__(kBlock) k_bp_level(uint32_t t, uint32_t rl, uint32_t L, const uint64_t* rrow,
+                                                     const uint32_t* rcol, uint8_t* bp_dist, ulonglong2* bp_sets,
+                                                     const uint2* items, const uint32_t* nitems, DevCounters* ctr) {
     const uint32_t lane = lane_id();
-    for (uint32_t v = global_wave(); v < n; v += num_waves()) {
-        const uint64_t at_l = ballot64(lane < t && bp_dist[(size_t)v * t + lane] == L);
-        if (!at_l) continue;
-        if (L + 1 >= PLL_INF8) {
-            if (lane == 0) atomicOr(&ctr->error, PLL_ERR_DIST);
-            continue;
-        }
-        const uint64_t beg = rrow[v], end = rrow[v + 1];
-        uint64_t todo = at_l;
-        while (todo) {
-            const uint32_t i = (uint32_t)__builtin_ctzll(todo);
-            todo &= todo - 1;
-            const ulonglong2 sv = bp_sets[(size_t)v * t + i];
-            for (uint64_t e = beg + lane; e < end; e += 64) {
-                const uint32_t w = rcol[e];
-                uint8_t* dw = &bp_dist[(size_t)w * t + i];
-                const uint32_t d = *dw;
-                if (d != PLL_INF8 && d != L + 1) continue;
-                if (d == PLL_INF8) *dw = (uint8_t)(L + 1);
-                ulonglong2* sw = &bp_sets[(size_t)w * t + i];
-                if (sv.x) atomicOr((unsigned long long*)&sw->x, (unsigned long long)sv.x);
-                if (sv.y) atomicOr((unsigned long long*)&sw->y, (unsigned long long)sv.y);
-            }
-        }
-    }
-}
-
-// Siblings at level L: S^0(v) gains S^-1 of every neighbour at the same
-// level, then drops what S^-1(v) holds.  Counts the (vertex, root) pairs at
-// level L into the first shard's receiver counter (the loop stops at 0).
-__global__ void __launch_bounds__(kBlock) k_bp_sibling(uint32_t n, uint32_t t, uint32_t L, const uint64_t* rrow,
-                                                       const uint32_t* rcol, const uint8_t* bp_dist,
-                                                       ulonglong2* bp_sets, DevCounters* ctr) {
-    const uint32_t lane = lane_id();
+    const uint32_t i = lane & (rl - 1u), slot = lane / rl, nb = PLL_WAVE / rl;
+    const uint32_t total = *nitems;
     uint32_t seen = 0;
-    for (uint32_t v = global_wave(); v < n; v += num_waves()) {
-        const uint64_t at_l = ballot64(lane < t && bp_dist[(size_t)v * t + lane] == L);
-        if (!at_l) continue;
-        seen += (uint32_t)__builtin_popcountll(at_l);
-        const uint64_t beg = rrow[v], end = rrow[v + 1];
-        uint64_t todo = at_l;
-        while (todo) {
-            const uint32_t i = (uint32_t)__builtin_ctzll(todo);
-            todo &= todo - 1;
-            uint64_t acc = 0;
-            for (uint64_t e = beg + lane; e < end; e += 64) {
-                const uint32_t w = rcol[e];
-                if (bp_dist[(size_t)w * t + i] == L) acc |= bp_sets[(size_t)w * t + i].x;
+    for (uint32_t q = global_wave(); q < total; q += num_waves()) {
+        const uint2 it = items[q];
+        const size_t at = (size_t)it.x * t + i;
+        const uint32_t dv = i < t ? bp_dist[at] : 0u;
+        const bool want = i < t && (dv == L || (!SIB && dv == PLL_INF8));
+        if (!ballot64(want)) continue;
+        if (SIB && it.y == 0 && slot == 0) seen += want;
+        const uint64_t rbeg = rrow[it.x], rend = rrow[it.x + 1];
+        const uint64_t beg = rbeg + (uint64_t)it.y * pll::kPullSeg, end = min(rend, beg + pll::kPullSeg);
+        uint64_t ax = 0, ay = 0;
+        bool found = false;
+        for (uint64_t e0 = beg; e0 < end; e0 += 4u * nb) {
+            size_t u[4];
+            bool hit[4];
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                const uint64_t e = e0 + (uint32_t)x * nb + slot;
+                u[x] = (size_t)(e < end ? rcol[e] : 0u) * t + i;
+                hit[x] = want && e < end;
             }
-            acc = wave_or64(acc);
-            if (lane == 0) {
-                ulonglong2* p = &bp_sets[(size_t)v * t + i];
-                p->y = (p->y | acc) & ~p->x;
+#pragma unroll
+            for (int x = 0; x < 4; ++x) hit[x] = hit[x] && bp_dist[u[x]] == (SIB ? L : L - 1u);
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                if (!hit[x]) continue;
+                found = true;
+                if (SIB) {
+                    ax |= bp_sets[u[x]].x;
+                } else {
+                    const ulonglong2 s = bp_sets[u[x]];
+                    ax |= s.x;
+                    ay |= s.y;
+                }
+            }
+        }
+        uint32_t f = found ? 1u : 0u;
+        for (uint32_t o = rl; o < PLL_WAVE; o <<= 1) {
+            ax |= __shfl_xor((unsigned long long)ax, (int)o, PLL_WAVE);
+            ay |= __shfl_xor((unsigned long long)ay, (int)o, PLL_WAVE);
+            f |= __shfl_xor(f, (int)o, PLL_WAVE);
+        }
+        if (!want || slot != 0) continue;
+        const bool alone = rend - rbeg <= pll::kPullSeg;
+        unsigned long long* px = reinterpret_cast<unsigned long long*>(&bp_sets[at].x);
+        unsigned long long* py = reinterpret_cast<unsigned long long*>(&bp_sets[at].y);
+        if (SIB) {
+            const unsigned long long own = *px;
+            if (alone) {
+                *py = (*py | ax) & ~own;
+            } else {
+                if (it.y == 0) atomicAnd(py, ~own);
+                if (ax & ~own) atomicOr(py, ax & ~own);
+            }
+        } else if (f) {
+            if (dv == PLL_INF8) bp_dist[at] = (uint8_t)L;
+            if (alone) {
+                *px |= ax;
+                *py |= ay;
+            } else {
+                if (ax) atomicOr(px, ax);
+                if (ay) atomicOr(py, ay);
             }
         }
     }
-    if (lane == 0 && seen) atomicAdd(&ctr->sh[0].recv[0], seen);
+    seen = wave_sum32(seen);
+    if (SIB && lane == 0 && seen) atomicAdd(&ctr->sh[0].recv[0], seen);
 }
 
 // Transposed copy of the batch vertices' BP data (root-major, so that the
@@ -1554,8 +1578,13 @@ struct BpState {
     ulonglong2* sets = nullptr;
 };
 
-int build_bp(DevAllocs& M, uint32_t n, uint32_t t_req, const uint64_t* rrow, const uint32_t* rcol, DevCounters* ctr,
-             DevCounters* h, hipStream_t s, BpState* B) {
+int build_bp(DevAllocs& M, const BuildArgs& A, uint64_t nnz, uint32_t t_req, DevCounters* ctr, DevCounters* h,
+             hipStream_t s, BpState* B) {
+    const uint32_t n = A.n;
+    const uint64_t* rrow = A.rrow;
+    const uint32_t* rcol = A.rcol;
+    uint2* items = M.get<uint2>((size_t)n + nnz / pll::kPullSeg + 1);
+    uint32_t* nitems = M.get<uint32_t>(1);
     B->used = M.get<uint8_t>(n);
     B->roots = M.get<uint32_t>(64);
     B->nbrs = M.get<uint32_t>(64 * 64);
@@ -1577,10 +1606,15 @@ int build_bp(DevAllocs& M, uint32_t n, uint32_t t_req, const uint64_t* rrow, con
     TRY_HIP(hipMemsetAsync(B->dist, 0xFF, (size_t)n * t, s));
     TRY_HIP(hipMemsetAsync(B->sets, 0, sizeof(ulonglong2) * n * t, s));
     k_bp_seed<<<t, 65, 0, s>>>(t, B->roots, B->nbrs, B->dist, B->sets);
+    TRY_HIP(hipMemsetAsync(nitems, 0, sizeof(uint32_t), s));
+    k_pull_items<<<blocks_for_waves((n + 63) / 64), kBlock, 0, s>>>(A, items, nitems);
+    uint32_t rl = 1;
+    while (rl < t) rl *= 2;
+    const uint32_t blocks = blocks_for_waves((uint64_t)n + nnz / pll::kPullSeg);
     for (uint32_t L = 1; L < PLL_INF8; ++L) {
-        k_bp_push<<<blocks_for_waves(n), kBlock, 0, s>>>(n, t, L - 1, rrow, rcol, B->dist, B->sets, ctr);
+        k_bp_level<false><<<blocks, kBlock, 0, s>>>(t, rl, L, rrow, rcol, B->dist, B->sets, items, nitems, ctr);
         TRY_HIP(hipMemsetAsync(&ctr->sh[0].recv[0], 0, sizeof(uint32_t), s));
-        k_bp_sibling<<<blocks_for_waves(n), kBlock, 0, s>>>(n, t, L, rrow, rcol, B->dist, B->sets, ctr);
+        k_bp_level<true><<<blocks, kBlock, 0, s>>>(t, rl, L, rrow, rcol, B->dist, B->sets, items, nitems, ctr);
         TRY_HIP(hipGetLastError());
         int rc = read_counters(ctr, h, s);
         if (rc) return rc;
@@ -1719,7 +1753,7 @@ int build_attempt(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, const uint3
     A.nbr_hubs = bp_req ? 0u : 1u;
     BpState BP;
     if (bp_req) {
-        rc = build_bp(M, n, bp_req, RC.rrow, RC.rcol, ctr, h, s, &BP);
+        rc = build_bp(M, A, nnz, bp_req, ctr, h, s, &BP);
         if (rc) return rc;
         A.bp_t = BP.t;
         A.bp_used = BP.used;

@@ -759,10 +759,13 @@ __device__ inline uint64_t bp_prune_words(const BuildArgs& A, uint32_t v, uint32
                 if (lane < t && dv != PLL_INF8) {
                     const uint32_t du = A.bp_dist[at];
                     if (du != PLL_INF8) {
-                        const ulonglong2 su = A.bp_sets[at];
+                        // the sets decide only where the sum is j + 1 or j + 2
                         td = du + dv;
-                        if (su.x & sv.x) td -= 2;
-                        else if ((su.x & sv.y) | (su.y & sv.x)) td -= 1;
+                        if (td > j && td <= j + 2u) {
+                            const ulonglong2 su = A.bp_sets[at];
+                            if (su.x & sv.x) td -= 2;
+                            else if ((su.x & sv.y) | (su.y & sv.x)) td -= 1;
+                        }
                     }
                 }
                 if (wave_min32(td) <= j && lane == (uint32_t)w) out |= 1ull << bit;
@@ -785,11 +788,13 @@ __device__ inline uint64_t bp_prune_words(const BuildArgs& A, uint32_t v, uint32
             const uint64_t v1 = readlane64(sv.x, i), v0 = readlane64(sv.y, i);
             if (cand) {
                 const uint32_t du = A.bpb_dist[(size_t)i * A.bstride + kk];
-                if (du != PLL_INF8) {
-                    const ulonglong2 su = A.bpb_sets[(size_t)i * A.bstride + kk];
+                if (du != PLL_INF8 && bound > j && du + dvi <= j + 2u) {
                     uint32_t td = du + dvi;
-                    if (su.x & v1) td -= 2;
-                    else if ((su.x & v0) | (su.y & v1)) td -= 1;
+                    if (td > j) {
+                        const ulonglong2 su = A.bpb_sets[(size_t)i * A.bstride + kk];
+                        if (su.x & v1) td -= 2;
+                        else if ((su.x & v0) | (su.y & v1)) td -= 1;
+                    }
                     bound = min(bound, td);
                 }
             }
