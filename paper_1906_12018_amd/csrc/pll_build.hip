@@ -582,9 +582,9 @@ __global__ void __launch_bounds__(kBlock, 4) k_check_push2(BuildArgs A0, pll::Ne
         check_push_body<WM, false, false, SCAN>(A1, side_exec(A1, nb0, gridDim.x - nb0), ib, bs, j, nr1, 0, ahead);
 }
 
-// with bit-parallel labels (no register cap: it would spill)
+// with bit-parallel labels
 template <int WM, int SCAN>
-__global__ void __launch_bounds__(kBlock) k_check_push_bp(BuildArgs A, uint32_t ib, uint32_t bs, uint32_t j,
+__global__ void __launch_bounds__(kBlock, 4) k_check_push_bp(BuildArgs A, uint32_t ib, uint32_t bs, uint32_t j,
                                                           pll::NextRound nr, uint32_t relaxed, uint32_t ahead) {
     if (ahead_check_stops(A, grid_exec(A), ahead, j, nr.rin)) return;
     check_push_body<WM, true, false, SCAN>(A, grid_exec(A), ib, bs, j, nr, relaxed, ahead);

@@ -723,6 +723,13 @@ __device__ inline void phase_push(const BuildArgs& A, const Exec& X, uint64_t* m
     phase_push_heavy(A, X, ib, p, p, msgs, recv, rstamp, bstamp, st, filter);
 }
 
+// Lane `src`'s x in every lane (the LDS crossbar; src may differ per lane).
+__device__ inline uint64_t shfl64(uint64_t x, uint32_t src) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(src * 4u), (int)(uint32_t)x);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(src * 4u), (int)(uint32_t)(x >> 32));
+    return ((uint64_t)hi << 32) | lo;
+}
+
 // Bit-parallel bound (Section 5.2) of every candidate in `mine` at v for
 // distance j: candidate u_k is pruned when, for some BP root i,
 // d_i(u_k) + d_i(v) - c <= j, with c = 2 when the S^-1 sets of u_k and v
@@ -742,41 +749,61 @@ __device__ inline uint64_t bp_prune_words(const BuildArgs& A, uint32_t v, uint32
     }
     const uint64_t roots_v = ballot64(lane < t && dv != PLL_INF8);
     uint64_t out = 0;
-    // few candidates: lanes over the BP roots, one candidate at a time (its
-    // data of all roots is one coalesced load); otherwise lanes over the
+    // few candidates: lanes over the BP roots, a few candidates at a time (a
+    // candidate's data of all roots is one coalesced load); otherwise lanes over the
     // candidates of a word, one root at a time
     const uint32_t ncand = wave_sum32(lane < WM ? (uint32_t)__builtin_popcountll(mine) : 0u);
-    const uint32_t nwords = (uint32_t)__builtin_popcountll(ballot64(lane < WM && mine != 0));
+    // (scalar loops over the words that hold candidates: one copy of the code)
+    uint64_t words = ballot64(lane < WM && mine != 0);
+    const uint32_t nwords = (uint32_t)__builtin_popcountll(words);
     if (ncand < nwords * (uint32_t)__builtin_popcountll(roots_v)) {
-#pragma unroll
-        for (int w = 0; w < WM; ++w) {
+        // rl lanes hold the roots, up to four candidates side by side
+        const uint32_t rl = t <= 16 ? 16u : t <= 32 ? 32u : 64u;
+        const uint32_t i = lane & (rl - 1u), slot = lane / rl, nb = PLL_WAVE / rl;
+        const uint32_t dvi = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(i * 4u), (int)dv);
+        const uint64_t v1 = shfl64(sv.x, i), v0 = shfl64(sv.y, i);
+        const bool root = i < t && dvi != PLL_INF8;
+        while (words) {
+            const uint32_t w = (uint32_t)__builtin_ctzll(words);
+            words &= words - 1;
             uint64_t m = readlane64(mine, w);
             while (m) {
-                const uint32_t bit = (uint32_t)__builtin_ctzll(m);
-                m &= m - 1;
-                const size_t at = (size_t)(ib + 64u * w + bit) * t + lane;
+                // the slot's candidate: the lowest bits of m in order
+                uint64_t bits[4];
+#pragma unroll
+                for (uint32_t x = 0; x < 4; ++x) {
+                    bits[x] = x < nb ? m & (0ull - m) : 0ull;
+                    m ^= bits[x];
+                }
+                const uint64_t mybit = slot == 0 ? bits[0] : slot == 1 ? bits[1] : slot == 2 ? bits[2] : bits[3];
                 uint32_t td = 0xFFFFFFFFu;
-                if (lane < t && dv != PLL_INF8) {
+                if (root && mybit) {
+                    const size_t at = (size_t)(ib + 64u * w + (uint32_t)__builtin_ctzll(mybit)) * t + i;
                     const uint32_t du = A.bp_dist[at];
                     if (du != PLL_INF8) {
                         // the sets decide only where the sum is j + 1 or j + 2
-                        td = du + dv;
+                        td = du + dvi;
                         if (td > j && td <= j + 2u) {
                             const ulonglong2 su = A.bp_sets[at];
-                            if (su.x & sv.x) td -= 2;
-                            else if ((su.x & sv.y) | (su.y & sv.x)) td -= 1;
+                            if (su.x & v1) td -= 2;
+                            else if ((su.x & v0) | (su.y & v1)) td -= 1;
                         }
                     }
                 }
-                if (wave_min32(td) <= j && lane == (uint32_t)w) out |= 1ull << bit;
+                const uint64_t pr = ballot64(td <= j);
+                uint64_t cut = 0;
+#pragma unroll
+                for (uint32_t x = 0; x < 4; ++x)
+                    if (x < nb && ((pr >> (x * rl)) & (rl == 64 ? ~0ull : (1ull << rl) - 1ull))) cut |= bits[x];
+                if (lane == w) out |= cut;
             }
         }
         return out;
     }
-#pragma unroll
-    for (int w = 0; w < WM; ++w) {
+    while (words) {
+        const uint32_t w = (uint32_t)__builtin_ctzll(words);
+        words &= words - 1;
         const uint64_t m = readlane64(mine, w);
-        if (!m) continue;
         const bool cand = (m >> lane) & 1ull;
         const uint32_t kk = 64u * w + lane;
         uint32_t bound = 0xFFFFFFFFu;
@@ -800,7 +827,7 @@ __device__ inline uint64_t bp_prune_words(const BuildArgs& A, uint32_t v, uint32
             }
         }
         const uint64_t pr = ballot64(cand && bound <= j);
-        if (lane == (uint32_t)w) out = pr;
+        if (lane == w) out = pr;
     }
     return out;
 }
@@ -819,12 +846,6 @@ __device__ inline uint64_t row_or64_dpp(uint64_t x) {
     return ((uint64_t)row_or32_dpp((uint32_t)(x >> 32)) << 32) | row_or32_dpp((uint32_t)x);
 }
 
-// Lane `src`'s x in every lane (the LDS crossbar; src may differ per lane).
-__device__ inline uint64_t shfl64(uint64_t x, uint32_t src) {
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(src * 4u), (int)(uint32_t)x);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(src * 4u), (int)(uint32_t)(x >> 32));
-    return ((uint64_t)hi << 32) | lo;
-}
 
 // x of the lane N below (mod 16) in each 16-lane row.
 template <int N>
