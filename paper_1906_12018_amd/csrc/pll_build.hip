@@ -45,7 +45,16 @@ constexpr uint32_t kHotRows = 4096;        // top-ranked table rows whose row ma
 // and n / 2.8: 136.5, 134.4 and 135.4; n / 16 and n / 24: 135.1 and 135.4.
 constexpr uint64_t kPullFrac1 = 12;
 constexpr uint32_t kPullMinN = 16384;      // smaller graphs always push (the pull's set-up outweighs it)
-constexpr uint64_t kPackMin = 16384;       // receivers from which a fused round checks four per wave
+// Receivers from which a fused round checks four per wave, and above which it
+// is not queued ahead of the host.  Packing from 2,048, 4,096, 8,192, 16,384
+// and 32,768 receivers: R-MAT 65,536 4.37, 4.33, 4.24, 4.27 and 4.49 ms,
+// BA-50000 15.2, 15.2, 14.8, 15.3 and 15.4, R-MAT-20 131.8, 130.3, 129.9,
+// 130.0 and 130.9.  Queueing up to 16,384, 32,768, 65,536 and 131,072:
+// R-MAT 200,000 15.6, 15.3, 15.0 and 15.7 ms, BA-50000 15.7, 15.6, 14.8 and
+// 14.8, R-MAT 65,536 4.41, 4.31, 4.24 and 4.23.
+constexpr uint64_t kPackMin = 8192;
+constexpr uint64_t kAheadRecv = 65536;
+constexpr uint32_t kAheadFirst = 16384;    // graphs below this many vertices queue their first batch too
 
 inline uint32_t blocks_for_waves(uint64_t waves) {
     uint64_t b = (waves + kWavesPerBlock - 1) / kWavesPerBlock;
@@ -571,15 +580,15 @@ __global__ void __launch_bounds__(kBlock, 4) k_check_push(BuildArgs A, uint32_t 
 
 // Directed graphs: both sides' fused rounds in one launch, blocks [0, nb0)
 // on the forward side and the rest on the backward side.
-template <int WM, int SCAN>
+template <int WM, int SCAN, bool PACK = false>
 __global__ void __launch_bounds__(kBlock, 4) k_check_push2(BuildArgs A0, pll::NextRound nr0, BuildArgs A1,
                                                            pll::NextRound nr1, uint32_t ib, uint32_t bs, uint32_t j,
                                                            uint32_t nb0, uint32_t ahead) {
     if (ahead_check_stops2(A0, A1, ahead, j, nr0.rin, nb0)) return;
     if (blockIdx.x < nb0)
-        check_push_body<WM, false, false, SCAN>(A0, side_exec(A0, 0, nb0), ib, bs, j, nr0, 0, ahead);
+        check_push_body<WM, false, PACK, SCAN>(A0, side_exec(A0, 0, nb0), ib, bs, j, nr0, 0, ahead);
     else
-        check_push_body<WM, false, false, SCAN>(A1, side_exec(A1, nb0, gridDim.x - nb0), ib, bs, j, nr1, 0, ahead);
+        check_push_body<WM, false, PACK, SCAN>(A1, side_exec(A1, nb0, gridDim.x - nb0), ib, bs, j, nr1, 0, ahead);
 }
 
 // with bit-parallel labels
@@ -1247,22 +1256,25 @@ void launch_check_push(uint32_t blocks, hipStream_t s, const BuildArgs& A, uint3
         k_check_push<WM, false, kScanBytes><<<blocks, kBlock, 0, s>>>(A, ib, bs, j, nr, relaxed, ahead);
 }
 
-template <int SCAN>
+template <int SCAN, bool PACK = false>
 void launch_check_push2(uint32_t nb0, uint32_t nb1, hipStream_t s, const BuildArgs& A0, const pll::NextRound& nr0,
                         const BuildArgs& A1, const pll::NextRound& nr1, uint32_t ib, uint32_t bs, uint32_t j, uint32_t ahead) {
     const uint32_t g = nb0 + nb1;
     switch (words_class(A0.W)) {
-        case 1: k_check_push2<1, SCAN><<<g, kBlock, 0, s>>>(A0, nr0, A1, nr1, ib, bs, j, nb0, ahead); break;
-        case 2: k_check_push2<2, SCAN><<<g, kBlock, 0, s>>>(A0, nr0, A1, nr1, ib, bs, j, nb0, ahead); break;
-        case 4: k_check_push2<4, SCAN><<<g, kBlock, 0, s>>>(A0, nr0, A1, nr1, ib, bs, j, nb0, ahead); break;
-        case 8: k_check_push2<8, SCAN><<<g, kBlock, 0, s>>>(A0, nr0, A1, nr1, ib, bs, j, nb0, ahead); break;
-        default: k_check_push2<16, SCAN><<<g, kBlock, 0, s>>>(A0, nr0, A1, nr1, ib, bs, j, nb0, ahead); break;
+        case 1: k_check_push2<1, SCAN, PACK><<<g, kBlock, 0, s>>>(A0, nr0, A1, nr1, ib, bs, j, nb0, ahead); break;
+        case 2: k_check_push2<2, SCAN, PACK><<<g, kBlock, 0, s>>>(A0, nr0, A1, nr1, ib, bs, j, nb0, ahead); break;
+        case 4: k_check_push2<4, SCAN, PACK><<<g, kBlock, 0, s>>>(A0, nr0, A1, nr1, ib, bs, j, nb0, ahead); break;
+        case 8: k_check_push2<8, SCAN, PACK><<<g, kBlock, 0, s>>>(A0, nr0, A1, nr1, ib, bs, j, nb0, ahead); break;
+        default: k_check_push2<16, SCAN, PACK><<<g, kBlock, 0, s>>>(A0, nr0, A1, nr1, ib, bs, j, nb0, ahead); break;
     }
 }
 
 void dispatch_check_push2(uint32_t nb0, uint32_t nb1, hipStream_t s, const BuildArgs& A0, const pll::NextRound& nr0,
-                          const BuildArgs& A1, const pll::NextRound& nr1, uint32_t ib, uint32_t bs, uint32_t j, uint32_t ahead) {
-    if (A0.P)
+                          const BuildArgs& A1, const pll::NextRound& nr1, uint32_t ib, uint32_t bs, uint32_t j, uint32_t ahead,
+                          bool pack) {
+    if (A0.P && pack)
+        launch_check_push2<kScanPlanes, true>(nb0, nb1, s, A0, nr0, A1, nr1, ib, bs, j, ahead);
+    else if (A0.P)
         launch_check_push2<kScanPlanes>(nb0, nb1, s, A0, nr0, A1, nr1, ib, bs, j, ahead);
     else if (j <= pll::kSmallT)
         launch_check_push2<kScanSmall>(nb0, nb1, s, A0, nr0, A1, nr1, ib, bs, j, ahead);
@@ -1627,8 +1639,10 @@ int build_bp(DevAllocs& M, const BuildArgs& A, uint64_t nnz, uint32_t t_req, Dev
 
 // Batches queued ahead of the host.  A round of a few thousand receivers
 // runs 10 us, and reading its counters back and launching the next one costs
-// as much again.  Once the rounds of a batch fall below kPackMin receivers
-// (so none is packed or pulled), whole batches are queued: init, push, as
+// as much again.  Once the rounds of a batch fall below kAheadRecv receivers,
+// whole batches are queued (their rounds push: gathers only where a batch is
+// run by the host; R-MAT 65,536 4.09 ms, 4.33 with the rounds that would be
+// pulled left to the host, BA-50000 14.7 and 15.6): init, push, as
 // many checks as the last batches needed, end and clear, for up to kAheadMax
 // batches, with grids sized by the last receiver counts, and one read-back at
 // the end.  A batch that needs more rounds, or that meets rows long enough
@@ -1647,10 +1661,9 @@ struct Ahead {
     unsigned long long growth = 0;  // per batch since then
     bool fits = false;              // every round of the last batch could be queued
 
-    // A graph whose rounds cannot reach kPackMin receivers queues its first
-    // batch as well, with the usual four rounds.
+    // A small graph queues its first batch as well, with the usual four rounds.
     void start(uint32_t n) {
-        if (n >= kPackMin) return;
+        if (n >= kAheadFirst) return;
         rounds = 4;
         fits = true;
         for (uint64_t& r : recv) r = n;
@@ -1664,7 +1677,7 @@ struct Ahead {
     uint32_t ready(const BuildArgs& A, const DevCounters* h, uint32_t left) {
         if (!on || !A.P || rounds == 0 || !fits || heavy) return 0;
         for (uint32_t j = 1; j <= rounds; ++j)
-            if (recv[j] >= kPackMin) return 0;
+            if (recv[j] >= kAheadRecv) return 0;
         // room for four times the recent growth in the bump regions
         const unsigned long long room = A.region_cap - std::min<unsigned long long>(max_top(h), A.region_cap);
         uint32_t d = std::min(depth, left);
@@ -1899,8 +1912,10 @@ int build_attempt(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, const uint3
                 for (uint32_t j = 1; j <= K; ++j, ++rstamp) {
                     const pll::NextRound nr{mbuf[j & 1u], rbuf[j & 1u], mbuf[(j + 1) & 1u], rbuf[(j + 1) & 1u],
                                             (j - 1) % 3, j % 3, (j + 1) % 3, j & 1u, rstamp + 1, bstamp, 0u};
-                    dispatch_check_push(blocks_for_waves(std::min<uint64_t>(n, Q.recv[j] + Q.recv[j] / 4 + 512)), s, A,
-                                        ibd, bsd, j, nr, 0, false, code + j);
+                    const bool pack = Q.recv[j] >= kPackMin;
+                    const uint64_t est = Q.recv[j] + Q.recv[j] / 4;
+                    dispatch_check_push(blocks_for_waves(std::min<uint64_t>(n, pack ? est / 4 + 512 : est + 512)), s, A,
+                                        ibd, bsd, j, nr, 0, pack, code + j);
                 }
                 dispatch_batch_end(touched, s, A, ibd, bsd, 0, code + K + 1, K);
                 launch_clear_table(A, ibd, bsd, ctr, s, 1);
@@ -2421,7 +2436,7 @@ int build_attempt_directed(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, co
                                                rstamp + 1, bstamp, 0u};
                         nb[d] = blocks_for_waves(std::min<uint64_t>(n, Q[d].recv[j] + Q[d].recv[j] / 4 + 512));
                     }
-                    dispatch_check_push2(nb[0], nb[1], s, A[0], nr[0], A[1], nr[1], ibq, bsq, j, code + j);
+                    dispatch_check_push2(nb[0], nb[1], s, A[0], nr[0], A[1], nr[1], ibq, bsq, j, code + j, false);
                 }
                 k_batch_end4_2<<<nbe[0] + nbe[1], kBlock, 0, s>>>(A[0], A[1], ibq, nbe[0], code + K + 1, K);
                 k_clear_table2<true><<<2 * blocks_for_waves(4ull * bsq), kBlock, 0, s>>>(A[0], A[1], ibq, bsq, 1);
@@ -2510,14 +2525,17 @@ int build_attempt_directed(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, co
             }
             pll::NextRound nr[2];
             uint32_t nb[2] = {0, 0};
+            // rounds with many receivers check four per wave, on both sides
+            const bool pack = A[0].P && next_est[0] + next_est[1] >= kPackMin;
             for (int d = 0; d < 2; ++d) {
                 nr[d] = pll::NextRound{mbuf[d][j & 1u], rbuf[d][j & 1u], mbuf[d][(j + 1) & 1u], rbuf[d][(j + 1) & 1u], (j - 1) % 3, j % 3, (j + 1) % 3,
                                        j & 1u, rstamp + 1, bstamp};
-                if (live[d]) nb[d] = blocks_for_waves(std::min<uint64_t>(n, next_est[d] + 2048));
+                if (live[d])
+                    nb[d] = blocks_for_waves(std::min<uint64_t>(n, pack ? next_est[d] / 4 + 512 : next_est[d] + 2048));
             }
             ++rstamp;
             hipEvent_t r1 = P.mark();
-            dispatch_check_push2(nb[0], nb[1], s, A[0], nr[0], A[1], nr[1], ib, bs, j, 0);
+            dispatch_check_push2(nb[0], nb[1], s, A[0], nr[0], A[1], nr[1], ib, bs, j, 0, pack);
             P.span(PLL_PHASE_CHECK, r1, P.mark(), 1);
             TRY_HIP(hipGetLastError());
             rc = read_both();
