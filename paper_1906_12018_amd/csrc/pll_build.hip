@@ -3,25 +3,31 @@
 //
 // Per build:   input checks -> relabel to rank space -> batches -> finalize.
 // Per batch i (ranks [ib, ib+bs)):
-//   k_batch_init   append (u,0) to L(u), spread L(u) into the distance table T
-//                  (the paper's H(u), Section 4.1), seed the active list
+//   k_batch_init_planes  append (u,0) to L(u), spread L(u) into the distance
+//                  table (the paper's H(u), Section 4.1; bit planes of the
+//                  distances 1..8, BuildArgs::P), seed the active list
+//   k_push         the first scatter: OR delta L(a) of every active a into
+//                  msgs(v) of its neighbours v ranked below the batch hubs,
+//                  minus C(v) (the scatter step of Algorithm 4); collect the
+//                  receivers
 //   rounds j = 1, 2, ... until no vertex accepts anything:
-//     k_push       scatter: OR delta L(a) of every active a into msgs(v) of its
-//                  neighbours v ranked below the batch hubs, minus C(v)
-//                  (the scatter step of Algorithm 4); collect the receivers
-//     k_check      gather: cand(v) = msgs(v); C(v) |= cand(v); a candidate
+//     k_check_push gather: cand(v) = msgs(v); C(v) |= cand(v); a candidate
 //                  u_k survives iff no (h, d) in L(v) with d < j has
 //                  T[h][k] + d <= j (its distance check); append survivors
-//                  with distance j, write T for batch vertices, build the
-//                  next active list
-//   k_batch_end    clear C(v) over the touched vertices (the batch's last step,
-//                  Section 5.2 bitmap + queue), optional recheck (Section 5.1), sort each
-//                  touched vertex's batch segment by hub rank
-//   k_clear_table  reset T and its row masks for the next batch
+//                  with distance j, write the table for batch vertices, and
+//                  scatter what was accepted for round j+1 (k_pull gathers it
+//                  instead where the round is large)
+//   k_batch_end4   clear C(v) over the touched vertices (the batch's last step,
+//                  Section 5.2 bitmap + queue), sort each touched vertex's
+//                  batch segment by hub rank (k_batch_end where the recheck
+//                  of Section 5.1 runs)
+//   k_clear_table  reset the table for the next batch
+// Weighted builds and rounds above PLL_PLANES + 1 keep the table as bytes T
+// with row masks.  Small rounds are queued ahead of the host (struct Ahead).
 //
 // A round-j candidate can only be pruned by entries of distance < j, and
 // entries accepted in round j can never prune a round-j candidate, so the
-// concurrent T and label writes of k_check do not change any decision.
+// concurrent table and label writes of a check do not change any decision.
 #include <algorithm>
 #include <chrono>
 #include <cstdio>
@@ -579,7 +585,11 @@ __global__ void __launch_bounds__(kBlock, 4) k_check_push(BuildArgs A, uint32_t 
 }
 
 // Directed graphs: both sides' fused rounds in one launch, blocks [0, nb0)
-// on the forward side and the rest on the backward side.
+// on the forward side and the rest on the backward side.  Bound as
+// k_check_push: small rounds by their chain of dependent loads (19 us each on
+// directed R-MAT 100,003), packed ones by table lines and atomics.  That
+// build's checks: 11.6 ms on the byte table, 7.2 on the planes with packing
+// (packing: 12.6 -> 12.3 ms of build).
 template <int WM, int SCAN, bool PACK = false>
 __global__ void __launch_bounds__(kBlock, 4) k_check_push2(BuildArgs A0, pll::NextRound nr0, BuildArgs A1,
                                                            pll::NextRound nr1, uint32_t ib, uint32_t bs, uint32_t j,
@@ -874,7 +884,8 @@ __global__ void k_bp_seed(uint32_t t, const uint32_t* roots, const uint32_t* nbr
 //
 // Pushing each level along the rows, one root at a time, took two 64-bit
 // atomics per edge and root and one access chain per root (R-MAT-16, 16
-// roots: 1.9 ms of pushes and 1.6 ms of sibling passes per build).
+// roots: 1.9 ms of pushes and 1.6 ms of sibling passes per build; 0.20 and
+// 0.56 ms as gathers, bound by the gathered lines).
 template <bool SIB>
 __global__ void __launch_bounds__(kBlock) k_bp_level(uint32_t t, uint32_t rl, uint32_t L, const uint64_t* rrow,
                                                      const uint32_t* rcol, uint8_t* bp_dist, ulonglong2* bp_sets,

@@ -69,8 +69,11 @@ struct GraphResult {
     unsigned long long batches, rounds, cand, acc, edges, read, table, removed, cost_pos, cost_neg;
 };
 
-// The slots are cut into queues (queue q holds slots [qbeg[q], qbeg[q + 1])).
-constexpr uint32_t kQueues = 8;  // one per XCD
+// The slots are cut into queues (queue q holds slots [qbeg[q], qbeg[q + 1])),
+// one per XCD: the members of a gang then share an L2, and the rounds of a
+// graph, which its barriers and dependent loads bound, find each other's
+// writes there (256 graphs 52.5 -> 49.1 ms, 40 graphs 9.85 -> 9.1).
+constexpr uint32_t kQueues = 8;
 
 struct MultiCtl {
     unsigned long long out_top;

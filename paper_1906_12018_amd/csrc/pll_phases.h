@@ -374,6 +374,10 @@ __device__ inline void plane_set(const BuildArgs& A, uint32_t h, uint32_t d, uin
 // k / kInitRoots, one per wave, and collects the distances 1 and 2 of the
 // rows h < kInitHot in s_hot: bit k % kInitRoots of s_hot[h] is plane 1's
 // bit, bit 16 + k % kInitRoots plane 2's.  plane_flush then writes them out.
+// Bound by the atomics on the plane words: the top-ranked rows take a bit of
+// nearly every root.  R-MAT-20, all batches: 17.8 ms with every entry an
+// atomicOr, 13.6 with the hot rows collected here and flushed by atomicOr,
+// 10.5 with plain 16-bit stores.
 constexpr uint32_t kInitHot = 8192;
 constexpr uint32_t kInitRoots = 16;
 
@@ -737,6 +741,9 @@ __device__ inline uint64_t shfl64(uint64_t x, uint32_t src) {
 // (< bp_t) holds v's data of root i; lanes run over the candidates of one
 // word at a time, reading the batch vertices' data from the transposed
 // per-batch copy.  Returns, in lane w, the pruned bits of word w.
+// Bound by the latency of a candidate's 17 bytes per root: the word loop is
+// scalar and four candidates load side by side (R-MAT-16 with 16 roots, the
+// fused checks of a build: 5.3 -> 3.8 ms).
 template <int WM>
 __device__ inline uint64_t bp_prune_words(const BuildArgs& A, uint32_t v, uint32_t ib, uint32_t j, uint64_t mine) {
     const uint32_t lane = lane_id();
@@ -888,6 +895,9 @@ __device__ inline void plane_lines(uint32_t at, uint32_t first, uint32_t (&line)
 // lane reductions per live candidate word (7.5 of them per entry in the
 // R-MAT-20 rounds 2 and 3).  Lanes whose word has no live candidate load
 // nothing.  For W < 16 the row's lanes hold 16 / WM lines side by side.
+// Bound by those two dependent accesses, then by the appends and pushes around
+// the scan.  R-MAT-20 build: 192 ms on the byte table, 167 on the planes; all
+// later steps together take its fused checks from 125.7 to 80.7 ms.
 //
 // SHARE: one receiver for the whole wave (its candidates in lanes w < W, and
 // group g takes entries 16g .. 16g + 15 of each 64); otherwise each group
@@ -1399,7 +1409,11 @@ __device__ inline uint64_t sum_le_mask64(const uint8_t* p, uint32_t dd, const ui
 // T[h][k] + d <= D(v)[k].  Lanes beyond the live candidates are masked off,
 // so bytes of 255 (no candidate) never count.  RECHECK: the candidates are
 // entries of the list themselves, and none counts as covered by its own hub
-// (ib: the batch's first rank).
+// (ib: the batch's first rank).  Bound by the dependent segment reads and the
+// byte adds (VALU): the scan stops at the chunk that leaves no candidate live
+// and makes one pass per live word.  Weighted R-MAT-16: checks 9.3 -> 5.9 ms a
+// build (34 us a round); batch ends, whose recheck now makes one scan for all
+// of a vertex's new entries instead of one per entry, 3.7 -> 3.4.
 template <int WM, bool RECHECK = false>
 __device__ inline uint64_t prune_scan_w(const BuildArgs& A, uint64_t off, uint32_t len, uint64_t cw,
                                         const uint4* s_thr, uint32_t ib, PhaseStats& st) {
@@ -1563,7 +1577,9 @@ __device__ inline uint32_t row_rank32(uint32_t x) {
 // dependent reads.  A segment of up to 16 entries is sorted in registers
 // (each entry's position is the number of smaller ones in its row); longer
 // ones take the whole wave, one after another, through the presence bitmap
-// of phase_batch_end.
+// of phase_batch_end.  Bound by the chain of dependent reads and the C rows'
+// clearing (128 bytes per vertex).  R-MAT-20, all batches: 12.9 ms one vertex
+// per wave, 6.6 so; the build 157 -> 153.7 ms.
 __device__ inline void phase_batch_end4(const BuildArgs& A, const Exec& X, uint32_t ib, uint64_t* s_pres,
                                         uint8_t* s_dist) {
     const uint32_t lane = lane_id();
@@ -1718,6 +1734,9 @@ __device__ inline void phase_push_w(const BuildArgs& A, const Exec& X, uint32_t 
 // a coalesced 4-byte read and an LDS minimum, and D(r) is read and written
 // once.  64 neighbours' records load side by side, and their entries are
 // walked as one concatenated range, so short entry lists fill the wave.
+// Bound by the gathered entries' loads (0.19 ms per round).  Weighted R-MAT-16:
+// the pushes of a build took 22.6 ms; 10 gathered rounds take 1.9 and the
+// pushes left 1.7.
 constexpr uint32_t kPullWUnroll = 4;
 
 __device__ inline void phase_pull_w(const BuildArgs& A, const Exec& X, uint32_t ib, uint32_t bs, const uint2* items,
@@ -1903,6 +1922,8 @@ __device__ inline void phase_table_fill(const BuildArgs& A, const Exec& X, uint3
 // Reset the distance table rows (or plane words) written during the batch.
 // With HOT, planes 1 and 2 of the rows below kInitHot are zeroed whole (they
 // hold bits of most roots, which would each zero the same words again).
+// Bound by the scattered stores: R-MAT-20, all batches, 6.0 ms on the byte
+// table, 4.2 so.
 template <bool PLANES = false, bool HOT = false>
 __device__ inline void phase_clear_table(const BuildArgs& A, const Exec& X, uint32_t ib, uint32_t bs) {
     const uint32_t lane = lane_id();
