@@ -182,7 +182,7 @@ __global__ void __launch_bounds__(kMultiBlock) k_multi_build(const GraphJob* __r
     __shared__ uint64_t s_wsum[kMultiWaves];
     __shared__ uint64_t s_carry;
     __shared__ uint32_t s_slot, s_err, s_flag;
-    __shared__ unsigned long long s_tot[8];
+    __shared__ unsigned long long s_tot[pll::kCounts];
     __shared__ uint32_t s_max[2];
 
     const uint32_t lane = lane_id();
@@ -306,6 +306,7 @@ __global__ void __launch_bounds__(kMultiBlock) k_multi_build(const GraphJob* __r
 
         // ---- batches (a1-a7)
         PhaseStats st;
+        if (tid < pll::kCounts) s_tot[tid] = 0;  // the first barrier below orders it before every fold
         uint32_t rstamp = 0, bstamp = 0;
         unsigned long long batches = 0, rounds = 0;
         bool failed = false;
@@ -354,12 +355,12 @@ __global__ void __launch_bounds__(kMultiBlock) k_multi_build(const GraphJob* __r
                 ++rstamp;
                 // round j+1's slot was last read after round j-2's barrier
                 if (r == 0 && tid == 0) gc->round_acc[(j + 1) % 3] = gc->round_heavy[(j + 1) % 3] = 0;
-                const uint32_t acc0 = st.acc;
                 if (planes)
                     pll::phase_check4<WM, false, true>(A, X, ib, bs, j, false, st, nr);
                 else
                     pll::phase_check4<WM, false, false>(A, X, ib, bs, j, relaxed, st, nr);
-                if (lane == 0 && st.acc != acc0) atomicAdd(&gc->round_acc[j % 3], st.acc - acc0);
+                if (lane == 0 && st.acc) atomicAdd(&gc->round_acc[j % 3], st.acc);
+                pll::fold_counts(st, s_tot);
                 __syncthreads();
                 if (tid == 0 && load_agent(&gc->shards[r].hq[nr.hout])) atomicOr(&gc->round_heavy[j % 3], 1u);
                 if (gang_sync(gc, G, k, ctr, spin_limit, &s_flag)) { failed = true; break; }
@@ -374,6 +375,7 @@ __global__ void __launch_bounds__(kMultiBlock) k_multi_build(const GraphJob* __r
                 pll::phase_batch_end<WM>(A, X, ib, bs, true, s_pres[wv], s_dist[wv], nullptr, st);
             else
                 pll::phase_batch_end4(A, X, ib, s_pres[wv], s_dist[wv]);
+            pll::fold_counts(st, s_tot);
             if (gang_sync(gc, G, k, ctr, spin_limit, &s_flag)) { failed = true; break; }
             if (planes)
                 pll::phase_clear_table<true>(A, X, ib, bs);
@@ -403,10 +405,7 @@ __global__ void __launch_bounds__(kMultiBlock) k_multi_build(const GraphJob* __r
         }
         if (gang_sync(gc, G, k, ctr, spin_limit, &s_flag)) continue;
         const unsigned long long base = gc->out_base;
-        if (tid == 0) {
-            s_max[0] = s_max[1] = 0;
-            for (int x = 0; x < 8; ++x) s_tot[x] = 0;
-        }
+        if (tid == 0) s_max[0] = s_max[1] = 0;
         __syncthreads();
         uint32_t md = 0, ml = 0;
         for (uint32_t v = X.w; v < n; v += X.nw) {
@@ -424,28 +423,23 @@ __global__ void __launch_bounds__(kMultiBlock) k_multi_build(const GraphJob* __r
                                   : make_uint2(0xFFFFFFFFu, 0u);
         }
         md = wave_max32(md);
-        const unsigned long long sums[8] = {wave_sum64(st.cand),  wave_sum64(st.acc),     wave_sum64(st.edges),
-                                            wave_sum64(st.read),  wave_sum64(st.table),   wave_sum64(st.removed),
-                                            wave_sum64(st.cost_pos), wave_sum64(st.cost_neg)};
         if (lane == 0) {
             atomicMax(&s_max[0], md);
             atomicMax(&s_max[1], ml);
-            for (int x = 0; x < 8; ++x)
-                if (sums[x]) atomicAdd(&s_tot[x], sums[x]);
         }
         __syncthreads();
         if (tid == 0) {
             GraphResult& R = results[g];
             atomicMax(&R.max_dist, s_max[0]);
             atomicMax(&R.max_label, s_max[1]);
-            atomicAdd(&R.cand, s_tot[0]);
-            atomicAdd(&R.acc, s_tot[1]);
-            atomicAdd(&R.edges, s_tot[2]);
-            atomicAdd(&R.read, s_tot[3]);
-            atomicAdd(&R.table, s_tot[4]);
-            atomicAdd(&R.removed, s_tot[5]);
-            atomicAdd(&R.cost_pos, s_tot[6]);
-            atomicAdd(&R.cost_neg, s_tot[7]);
+            atomicAdd(&R.cand, s_tot[pll::kCountCand]);
+            atomicAdd(&R.acc, s_tot[pll::kCountAcc]);
+            atomicAdd(&R.edges, s_tot[pll::kCountEdges]);
+            atomicAdd(&R.read, s_tot[pll::kCountRead]);
+            atomicAdd(&R.table, s_tot[pll::kCountTable]);
+            atomicAdd(&R.removed, s_tot[pll::kCountRemoved]);
+            atomicAdd(&R.cost_pos, s_tot[pll::kCountPos]);
+            atomicAdd(&R.cost_neg, s_tot[pll::kCountNeg]);
         }
         __syncthreads();
     }

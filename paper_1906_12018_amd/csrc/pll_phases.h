@@ -9,6 +9,7 @@
 #pragma once
 
 #include "pll_internal.h"
+#include "pll_stats.h"
 
 namespace pll {
 
@@ -27,18 +28,19 @@ struct Exec {
     uint32_t arena_sh;  // first arena region to try
 };
 
-// Per-lane statistics a phase accumulates (summed over lanes by the caller).
-struct PhaseStats {
-    // one lane's share of a launch: a few per entry that this lane read
-    uint32_t cand = 0, acc = 0, read = 0, table = 0, removed = 0, bp = 0;
-    unsigned long long edges = 0;
-    // cost of the positive / negative checks: |L(v)| at each check that
-    // added / pruned a candidate (Section 4.3, Table 3)
-    unsigned long long cost_pos = 0, cost_neg = 0;
-    // CSR entries of the vertices whose next-round deliveries are pulled: the
-    // edge accesses of Algorithm 4 (the gather itself reads more)
-    unsigned long long pulled = 0;
-};
+// Add the wave's counts since the last call to the workgroup's 64-bit totals
+// `tot` (LDS).  The whole wave calls it.
+__device__ inline void fold_counts(PhaseStats& st, unsigned long long* tot) {
+    unsigned long long v[kCounts];
+    take_counts(st, v);
+    const uint32_t lane = lane_id();
+#pragma unroll
+    for (int k = 0; k < kCounts; ++k) {
+        if (!ballot64(v[k] != 0)) continue;
+        const unsigned long long t = wave_sum64_dpp(v[k]);
+        if (lane == 0) atomicAdd(&tot[k], t);
+    }
+}
 
 // Bit 7 of each byte of the result: that byte of x is <= t, where
 // tt = t * 0x01010101 (t <= 254).  Bytes are compared without carries

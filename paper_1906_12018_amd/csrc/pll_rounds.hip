@@ -148,6 +148,7 @@ __global__ void __launch_bounds__(kRoundBlock) k_batches(BuildArgs A, GridCtl* g
     __shared__ uint64_t s_pres[kRoundWaves][PLL_WMAX];
     __shared__ __align__(16) uint8_t s_dist[kRoundWaves][PLL_BMAX];
     __shared__ unsigned long long s_part[kRoundWaves];
+    __shared__ unsigned long long s_tot[pll::kCounts];
     __shared__ uint32_t s_flag, s_acc, s_nact;
 
     const uint32_t tid = threadIdx.x, wv = tid >> 6;
@@ -172,6 +173,7 @@ __global__ void __launch_bounds__(kRoundBlock) k_batches(BuildArgs A, GridCtl* g
     if (clk.on) clk.last = wall_clock64();
 
     PhaseStats st;
+    if (tid < pll::kCounts) s_tot[tid] = 0;  // the first barrier below orders it before every fold
     uint32_t k = 0, bstamp = bstamp0, rstamp = rstamp0;
     unsigned long long batches = 0, rounds = 0;
     uint32_t next_ib = n;
@@ -203,9 +205,9 @@ __global__ void __launch_bounds__(kRoundBlock) k_batches(BuildArgs A, GridCtl* g
             clk.mark(PLL_PHASE_PUSH);
             // the counter of round j+1 was last read after round j-1
             if (blockIdx.x == 0 && tid < PLL_SHARDS) gc->acc[tid].acc[(j + 1) & 1u] = 0;
-            const unsigned long long acc0 = st.acc;
             pll::phase_check<WM>(A, X, ib, bs, j, p, relaxed, st);
-            const unsigned long long got = block_sum(st.acc - acc0, s_part);
+            const unsigned long long got = block_sum(st.acc, s_part);
+            pll::fold_counts(st, s_tot);
             if (tid == 0 && got) atomicAdd(&gc->acc[my].acc[j & 1u], (uint32_t)got);
             if (grid_sync(gc, k, ctr, timeout_ticks, 0u, &s_flag)) {
                 failed = true;
@@ -230,6 +232,7 @@ __global__ void __launch_bounds__(kRoundBlock) k_batches(BuildArgs A, GridCtl* g
         }
         if (failed) break;
         pll::phase_batch_end<WM>(A, X, ib, bs, recheck, s_pres[wv], s_dist[wv], nullptr, st);
+        pll::fold_counts(st, s_tot);
         if (grid_sync(gc, k, ctr, timeout_ticks, 0u, &s_flag)) break;
         pll::phase_clear_table(A, X, ib, bs);
         // hand back to the host for compaction once a bump region is half used
@@ -248,15 +251,10 @@ __global__ void __launch_bounds__(kRoundBlock) k_batches(BuildArgs A, GridCtl* g
     }
 
     // statistics of this workgroup, one sharded atomic each
-    const unsigned long long v[8] = {st.cand, st.acc, st.edges, st.read, st.table, st.removed, st.cost_pos,
-                                     st.cost_neg};
-    const int which[8] = {PLL_ST_CAND,  PLL_ST_ACC,     PLL_ST_EDGES,    PLL_ST_READ,
-                          PLL_ST_TABLE, PLL_ST_RECHECK, PLL_ST_COST_POS, PLL_ST_COST_NEG};
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const unsigned long long t = block_sum(v[i], s_part);
-        if (tid == 0 && t) atomicAdd(&ctr->sh[my].stat[which[i]], t);
-    }
+    const int which[pll::kCounts] = {PLL_ST_CAND,  PLL_ST_ACC,     PLL_ST_EDGES,    PLL_ST_READ,
+                                     PLL_ST_TABLE, PLL_ST_RECHECK, PLL_ST_COST_POS, PLL_ST_COST_NEG};
+    __syncthreads();
+    if (tid < pll::kCounts && s_tot[tid]) atomicAdd(&ctr->sh[my].stat[which[tid]], s_tot[tid]);
     if (blockIdx.x == 0 && tid == 0) {
         gc->next_ib = next_ib;
         gc->bstamp = bstamp;
