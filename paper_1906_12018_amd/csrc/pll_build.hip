@@ -642,10 +642,11 @@ __global__ void __launch_bounds__(kBlock) k_batch_end4(BuildArgs A, uint32_t ib,
 template <int WM>
 __global__ void __launch_bounds__(kBlock) k_batch_end(BuildArgs A, uint32_t ib, uint32_t bs) {
     __shared__ uint64_t s_pres[kWavesPerBlock][PLL_WMAX];
+    __shared__ uint32_t s_top[kWavesPerBlock][PLL_WMAX];
     __shared__ __align__(16) uint8_t s_dist[kWavesPerBlock][PLL_BMAX];
     const uint32_t wv = threadIdx.x >> 6;
     PhaseStats st;
-    pll::phase_batch_end<WM>(A, grid_exec(A), ib, bs, true, s_pres[wv], s_dist[wv], nullptr, st);
+    pll::phase_batch_end<WM>(A, grid_exec(A), ib, bs, true, s_pres[wv], s_top[wv], s_dist[wv], nullptr, st);
     const unsigned long long v[3] = {st.removed, st.read, st.table};
     const int which[3] = {PLL_ST_RECHECK, PLL_ST_READ, PLL_ST_TABLE};
     block_add_stats<3>(A.ctr, v, which);
@@ -687,11 +688,12 @@ __global__ void __launch_bounds__(kBlock) k_check_w(BuildArgs A, uint32_t ib, ui
 template <int WM>
 __global__ void __launch_bounds__(kBlock) k_batch_end_w(BuildArgs A, uint32_t ib, uint32_t bs) {
     __shared__ uint64_t s_pres[kWavesPerBlock][PLL_WMAX];
+    __shared__ uint32_t s_top[kWavesPerBlock][PLL_WMAX];
     __shared__ __align__(16) uint8_t s_dist[kWavesPerBlock][PLL_BMAX];
     __shared__ uint32_t s_pos[kWavesPerBlock][PLL_BMAX];
     const uint32_t wv = threadIdx.x >> 6;
     PhaseStats st;
-    pll::phase_batch_end<WM, true>(A, grid_exec(A), ib, bs, true, s_pres[wv], s_dist[wv], s_pos[wv], st);
+    pll::phase_batch_end<WM, true>(A, grid_exec(A), ib, bs, true, s_pres[wv], s_top[wv], s_dist[wv], s_pos[wv], st);
     const unsigned long long v[3] = {st.removed, st.read, st.table};
     const int which[3] = {PLL_ST_RECHECK, PLL_ST_READ, PLL_ST_TABLE};
     block_add_stats<3>(A.ctr, v, which);

@@ -178,6 +178,7 @@ __global__ void __launch_bounds__(kMultiBlock) k_multi_build(const GraphJob* __r
                                                              GraphResult* results, MultiCtl* ctl, DevCounters* ctr,
                                                              uint32_t* out, uint32_t b, uint32_t flags) {
     __shared__ uint64_t s_pres[kMultiWaves][PLL_WMAX];
+    __shared__ uint32_t s_top[kMultiWaves][PLL_WMAX];
     __shared__ __align__(16) uint8_t s_dist[kMultiWaves][PLL_BMAX];
     __shared__ uint64_t s_wsum[kMultiWaves];
     __shared__ uint64_t s_carry;
@@ -372,7 +373,7 @@ __global__ void __launch_bounds__(kMultiBlock) k_multi_build(const GraphJob* __r
             }
             if (failed) break;
             if (recheck)
-                pll::phase_batch_end<WM>(A, X, ib, bs, true, s_pres[wv], s_dist[wv], nullptr, st);
+                pll::phase_batch_end<WM>(A, X, ib, bs, true, s_pres[wv], s_top[wv], s_dist[wv], nullptr, st);
             else
                 pll::phase_batch_end4(A, X, ib, s_pres[wv], s_dist[wv]);
             pll::fold_counts(st, s_tot);

@@ -1411,16 +1411,24 @@ __device__ inline uint64_t sum_le_mask64(const uint8_t* p, uint32_t dd, const ui
 // T[h][k] + d <= D(v)[k].  Lanes beyond the live candidates are masked off,
 // so bytes of 255 (no candidate) never count.  RECHECK: the candidates are
 // entries of the list themselves, and none counts as covered by its own hub
-// (ib: the batch's first rank).  Bound by the dependent segment reads and the
-// byte adds (VALU): the scan stops at the chunk that leaves no candidate live
-// and makes one pass per live word.  Weighted R-MAT-16: checks 9.3 -> 5.9 ms a
-// build (34 us a round); batch ends, whose recheck now makes one scan for all
-// of a vertex's new entries instead of one per entry, 3.7 -> 3.4.
+// (ib: the batch's first rank); s_top (LDS, W words) holds the largest
+// distance in each candidate word.  A table entry other than a hub's own is
+// at least 1, so an entry at distance d covers only candidates above d and
+// is left out of the words that have none.  Bound by the dependent segment
+// reads and the byte adds (VALU): the scan stops at the chunk that leaves no
+// candidate live and makes one pass per live word.  Weighted R-MAT-16: checks
+// 5.9 ms a build (34 us a round).  Unweighted R-MAT-16 with the recheck, batch
+// ends: one scan per distance 2.41 ms and 156 M table quarters (of the build),
+// one scan for all 3.90 ms and 674 M, with s_top 2.09 ms and 150 M; with the
+// relaxed check 3.36, 8.13 and 4.30 ms.
 template <int WM, bool RECHECK = false>
 __device__ inline uint64_t prune_scan_w(const BuildArgs& A, uint64_t off, uint32_t len, uint64_t cw,
-                                        const uint4* s_thr, uint32_t ib, PhaseStats& st) {
+                                        const uint4* s_thr, uint32_t ib, PhaseStats& st,
+                                        const uint32_t* s_top = nullptr) {
     const uint32_t lane = lane_id();
     uint64_t pw = 0;
+    const uint32_t top = RECHECK && lane < A.W ? s_top[lane] : 0u;
+    const uint32_t top_all = RECHECK ? wave_max32(top) : 0u;
     // one pass per word that still holds live candidates, its prunes reduced
     // at once, and the next chunk's entries loaded ahead, as in prune_scan
     uint32_t next = lane < len ? A.arena[off + lane] : 0u;
@@ -1430,9 +1438,9 @@ __device__ inline uint64_t prune_scan_w(const BuildArgs& A, uint64_t off, uint32
         st.read += ok;
         const uint32_t ent = next;
         next = idx + 64 < len ? A.arena[off + idx + 64] : 0u;
-        const uint32_t h = ent >> 8;
-        const uint64_t rm = ok ? A.rmchk[h] : 0ull;
-        const uint32_t dd = (ent & 255u) * 0x01010101u;
+        const uint32_t h = ent >> 8, d = ent & 255u;
+        const uint64_t rm = ok && (!RECHECK || (d != 0 && d < top_all)) ? A.rmchk[h] : 0ull;
+        const uint32_t dd = d * 0x01010101u;
         const uint8_t* row = A.Tchk + (size_t)h * A.bstride;
         const uint64_t live_lane = cw & ~pw;
         uint64_t lw = ballot64(live_lane != 0) & (WM >= 64 ? ~0ull : ((1ull << WM) - 1ull));
@@ -1440,7 +1448,8 @@ __device__ inline uint64_t prune_scan_w(const BuildArgs& A, uint64_t off, uint32
             const uint32_t w = (uint32_t)__builtin_ctzll(lw);
             lw &= lw - 1;
             uint64_t m = 0;
-            if ((rm >> (4 * w)) & 15u) {
+            const uint32_t top_w = readlane32(top, w);
+            if (((rm >> (4 * w)) & 15u) && (!RECHECK || d < top_w)) {
                 m = sum_le_mask64(row + 64u * w, dd, s_thr + 4 * w);
                 st.table += 4;
                 const uint32_t self = h - ib;
@@ -1481,8 +1490,8 @@ __device__ inline uint32_t segment_emit(const BuildArgs& A, uint32_t ib, uint64_
 // entries this batch appended to L(v) by hub rank; with `recheck`, first
 // drop every such entry (u, d) that L(u) and L(v) already cover through
 // another hub at distance <= d (Section 5.1's recheck with the batch's
-// tables still in memory).  s_pres (W words) and s_dist (b bytes) are this
-// wave's LDS scratch.
+// tables still in memory).  s_pres and s_top (W words each) and s_dist (b
+// bytes) are this wave's LDS scratch.
 //
 // Weighted graphs (WEIGHTED): the recheck always runs (it is what makes the
 // labels canonical there), D(v) is reset instead of C(v), and a hub may
@@ -1491,7 +1500,8 @@ __device__ inline uint32_t segment_emit(const BuildArgs& A, uint32_t ib, uint64_
 // the position of each hub's last entry).
 template <int WM, bool WEIGHTED = false>
 __device__ inline void phase_batch_end(const BuildArgs& A, const Exec& X, uint32_t ib, uint32_t bs, bool recheck,
-                                       uint64_t* s_pres, uint8_t* s_dist, uint32_t* s_pos, PhaseStats& st) {
+                                       uint64_t* s_pres, uint32_t* s_top, uint8_t* s_dist, uint32_t* s_pos,
+                                       PhaseStats& st) {
     const uint32_t lane = lane_id();
     const uint32_t W = A.W;
     if (WEIGHTED) recheck = true;
@@ -1520,7 +1530,10 @@ __device__ inline void phase_batch_end(const BuildArgs& A, const Exec& X, uint32
             const uint32_t nx = (uint32_t)__shfl_down((int)e, 1, 64);
             if (!ballot64(lane + 1 < tail && e >= nx)) continue;
         }
-        if (lane < W) s_pres[lane] = 0;
+        if (lane < W) {
+            s_pres[lane] = 0;
+            s_top[lane] = 0;
+        }
         if (WEIGHTED) {
             for (uint32_t k = lane; k < bs; k += 64) s_pos[k] = 0;
             wave_lds_sync();
@@ -1532,6 +1545,7 @@ __device__ inline void phase_batch_end(const BuildArgs& A, const Exec& X, uint32
             const uint32_t k = (e >> 8) - ib;
             if (WEIGHTED && s_pos[k] != x - ts + 1) continue;
             s_dist[k] = (uint8_t)(e & 255u);
+            if (recheck) atomicMax(&s_top[k >> 6], e & 255u);
             atomicOr((unsigned long long*)&s_pres[k >> 6], 1ull << (k & 63));
         }
         wave_lds_sync();
@@ -1541,7 +1555,7 @@ __device__ inline void phase_batch_end(const BuildArgs& A, const Exec& X, uint32
             // another hub, and every other one is by a canonical hub.
             const bool in_batch = v - ib < bs;
             const uint64_t pr = prune_scan_w<WM, true>(A, off, len, lane < W ? s_pres[lane] : 0ull,
-                                                       reinterpret_cast<const uint4*>(s_dist), ib, st);
+                                                       reinterpret_cast<const uint4*>(s_dist), ib, st, s_top);
             if (lane < W && pr) s_pres[lane] &= ~pr;
             st.removed += __builtin_popcountll(pr);
             if (in_batch) {

@@ -146,6 +146,7 @@ __global__ void __launch_bounds__(kRoundBlock) k_batches(BuildArgs A, GridCtl* g
                                                          uint32_t flags, uint32_t bstamp0, uint32_t rstamp0,
                                                          uint64_t timeout_ticks, uint32_t compact) {
     __shared__ uint64_t s_pres[kRoundWaves][PLL_WMAX];
+    __shared__ uint32_t s_top[kRoundWaves][PLL_WMAX];
     __shared__ __align__(16) uint8_t s_dist[kRoundWaves][PLL_BMAX];
     __shared__ unsigned long long s_part[kRoundWaves];
     __shared__ unsigned long long s_tot[pll::kCounts];
@@ -231,7 +232,7 @@ __global__ void __launch_bounds__(kRoundBlock) k_batches(BuildArgs A, GridCtl* g
             p ^= 1u;
         }
         if (failed) break;
-        pll::phase_batch_end<WM>(A, X, ib, bs, recheck, s_pres[wv], s_dist[wv], nullptr, st);
+        pll::phase_batch_end<WM>(A, X, ib, bs, recheck, s_pres[wv], s_top[wv], s_dist[wv], nullptr, st);
         pll::fold_counts(st, s_tot);
         if (grid_sync(gc, k, ctr, timeout_ticks, 0u, &s_flag)) break;
         pll::phase_clear_table(A, X, ib, bs);
