@@ -2443,13 +2443,15 @@ int build_attempt_directed(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, co
                 for (uint32_t j = 1; j <= K; ++j, ++rstamp) {
                     pll::NextRound nr[2];
                     uint32_t nb[2];
+                    const bool pack = Q[0].recv[j] + Q[1].recv[j] >= kPackMin;
                     for (int d = 0; d < 2; ++d) {
                         nr[d] = pll::NextRound{mbuf[d][j & 1u], rbuf[d][j & 1u], mbuf[d][(j + 1) & 1u],
                                                rbuf[d][(j + 1) & 1u], (j - 1) % 3, j % 3, (j + 1) % 3, j & 1u,
                                                rstamp + 1, bstamp, 0u};
-                        nb[d] = blocks_for_waves(std::min<uint64_t>(n, Q[d].recv[j] + Q[d].recv[j] / 4 + 512));
+                        const uint64_t est = Q[d].recv[j] + Q[d].recv[j] / 4;
+                        nb[d] = blocks_for_waves(std::min<uint64_t>(n, (pack ? est / 4 : est) + 512));
                     }
-                    dispatch_check_push2(nb[0], nb[1], s, A[0], nr[0], A[1], nr[1], ibq, bsq, j, code + j, false);
+                    dispatch_check_push2(nb[0], nb[1], s, A[0], nr[0], A[1], nr[1], ibq, bsq, j, code + j, pack);
                 }
                 k_batch_end4_2<<<nbe[0] + nbe[1], kBlock, 0, s>>>(A[0], A[1], ibq, nbe[0], code + K + 1, K);
                 k_clear_table2<true><<<2 * blocks_for_waves(4ull * bsq), kBlock, 0, s>>>(A[0], A[1], ibq, bsq, 1);
