@@ -299,10 +299,13 @@ int pll_export_bp(const pll_index* idx, uint32_t* d_roots, uint32_t* d_nbrs, uin
  * two-pointer merge per lane; G in {4..32} lets G lanes merge the two lists
  * in windows of 4G entries; 64 gives each pair a whole wave, which merges
  * the lists in merge-path tiles of 512 entries staged in LDS; 0 picks 64
- * when the mean label holds 32 entries or more (64 or more with bit-parallel
- * roots), else the smallest G in {4..32} (from 16 bit-parallel roots on,
- * {8..32}) with 4G >= the mean, and 64 for every call of 32,768 pairs or
- * fewer.  pll_index_info.query_lanes reports the value larger calls use.
+ * when the mean label holds 32 entries or more, else the smallest G in
+ * {4..32} (from 16 bit-parallel roots on, {8..32}) with 4G >= the mean; with
+ * bit-parallel roots the line lies at 64 entries, or at 48 (at 32 with 32
+ * roots or more) where the longest label holds eight means or more.  Calls of
+ * 32,768 pairs or fewer take 64 (24,576 with fewer than 32 bit-parallel roots,
+ * 32,768 vertices or more, a mean below 32 and no label of eight means).
+ * pll_index_info.query_lanes reports the value larger calls use.
  */
 int pll_query(const pll_index* idx, uint64_t count, const uint32_t* d_u, const uint32_t* d_v, uint32_t* d_out,
               hipStream_t stream);

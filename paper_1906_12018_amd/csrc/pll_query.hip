@@ -27,6 +27,7 @@
 #include <atomic>
 
 #include "pll_internal.h"
+#include "pll_rules.h"
 
 namespace {
 
@@ -615,43 +616,22 @@ void launch_group(const pll_index* idx, uint64_t count, const uint32_t* d_u, con
                                                                           count, d_u, d_v, d_out, nullptr, nullptr, 0);
 }
 
-// Calls of up to this many pairs take a wave per pair whatever the mean label
-// (when the index leaves the lanes open): they do not fill the device, so the
-// longest pair's chain of windows decides.  Mean labels of 4 to 43 entries,
-// 8,000 pairs: 8.4-9.0 us, 14-44 us with groups; 30,000 pairs: 14-26 us
-// against 18-30; from 100,000 pairs on the groups win.
-constexpr uint64_t kSmallCall = 32768;
-
-// Lanes per pair when the index leaves it open: the window (4 entries per
-// lane) should hold about one average label.
-uint32_t query_lanes_auto(const pll_index* idx) {
-    const uint64_t mean = idx->n ? (idx->total + (idx->directed ? idx->total_out : idx->total)) / (2ull * idx->n) : 0;
-    // a whole wave per pair from a mean label of 32 entries on (measured on
-    // R-MAT indexes of 2^14..2^20 vertices, mean labels of 44..241 entries:
-    // the wave kernel was fastest at every size); smaller groups below
-    // With bit-parallel roots every pair has the bound to compute, for which
-    // a wave has more lanes than roots: groups win up to twice that mean
-    // (1,000,000 pairs, mean 38: 254 us with 16 lanes, 307 with 64; mean 43:
-    // 343 and 446), and from 16 roots on 8 lanes share them (mean 17, 16
-    // roots: 157 us, 172 with 4 lanes; mean 4.8, 64 roots: 234 and 391).
-    const bool bp = idx->info.bp_roots != 0;
-    if (mean >= (bp ? 64u : 32u)) return 64;
-    uint32_t g = idx->info.bp_roots >= 16 ? 8 : 4;
-    while (g < 32 && 4ull * g < mean) g *= 2;
-    return g;
+pll::LabelShape label_shape(const pll_index* idx) {
+    return {idx->n, idx->directed ? (idx->total + idx->total_out) / 2 : idx->total, idx->info.max_label,
+            idx->info.bp_roots};
 }
 
 }  // namespace
 
 uint32_t pll_query_lanes(const pll_index* idx) {
-    return idx->query_lanes ? idx->query_lanes : query_lanes_auto(idx);
+    return idx->query_lanes ? idx->query_lanes : pll::query_lanes(label_shape(idx));
 }
 
 int pll_query_launch(const pll_index* idx, uint64_t count, const uint32_t* d_u, const uint32_t* d_v,
                      uint32_t* d_out, hipStream_t stream) {
     if (count == 0) return PLL_OK;
     uint32_t g = pll_query_lanes(idx);
-    if (idx->query_lanes == 0 && count <= kSmallCall) g = 64;
+    if (idx->query_lanes == 0 && count <= pll::query_small_call(label_shape(idx))) g = 64;
     switch (g) {
         case 1: {
             uint64_t blocks = (count + kBlock - 1) / kBlock;
