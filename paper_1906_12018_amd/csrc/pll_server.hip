@@ -23,6 +23,7 @@
 #include <thread>
 #include <vector>
 
+#include "pll_copy.h"
 #include "pll_internal.h"
 
 namespace {
@@ -68,98 +69,6 @@ struct IndexEntry {
     pll_index* idx = nullptr;
 };
 
-// Copies between request arrays and the slots' pinned staging, split over
-// the scheduler and a few helper threads.  A full batch moves 8 MiB in and
-// 4 MiB out, and one thread's copies (about 20 GB/s) took longer than the
-// device: 2,000 requests of 11.8 M pairs on R-MAT 262,144 took 7.5 ms, 6.0 with
-// three helpers and 5.7 with six.  Small
-// sets stay on the scheduler's thread.
-constexpr uint32_t kCopyHelpers = 6;
-
-class CopyPool {
-public:
-    struct Job {
-        void* dst;
-        const void* src;
-        size_t bytes;
-    };
-    // As many helpers as start; with none the caller copies alone.
-    void start(uint32_t helpers) {
-        try {
-            for (uint32_t i = 0; i < helpers; ++i) threads_.emplace_back([this] { loop(); });
-        } catch (...) {
-        }
-    }
-    ~CopyPool() {
-        {
-            std::lock_guard<std::mutex> lk(mu_);
-            stop_ = true;
-        }
-        cv_.notify_all();
-        for (std::thread& t : threads_) t.join();
-    }
-    void add(void* dst, const void* src, size_t bytes) {
-        total_ += bytes;
-        for (size_t at = 0; at < bytes; at += kPiece)
-            jobs_.push_back(Job{static_cast<char*>(dst) + at, static_cast<const char*>(src) + at,
-                                std::min(kPiece, bytes - at)});
-    }
-    // Run what was added (one thread adds and runs; returns when all is copied).
-    void run() {
-        next_.store(0, std::memory_order_relaxed);
-        const bool share = total_ >= kShare && !threads_.empty();
-        if (share) {
-            {
-                std::lock_guard<std::mutex> lk(mu_);
-                ++generation_;
-                open_ = true;
-            }
-            cv_.notify_all();
-        }
-        work();
-        if (share) {  // every piece is taken: wait for the helpers still copying
-            std::unique_lock<std::mutex> lk(mu_);
-            open_ = false;
-            idle_.wait(lk, [this] { return inside_ == 0; });
-        }
-        jobs_.clear();
-        total_ = 0;
-    }
-
-private:
-    static constexpr size_t kPiece = 128u << 10, kShare = 1u << 20;
-    void work() {
-        for (;;) {
-            const size_t i = next_.fetch_add(1, std::memory_order_relaxed);
-            if (i >= jobs_.size()) return;
-            std::memcpy(jobs_[i].dst, jobs_[i].src, jobs_[i].bytes);
-        }
-    }
-    void loop() {
-        uint64_t seen = 0;
-        std::unique_lock<std::mutex> lk(mu_);
-        for (;;) {
-            cv_.wait(lk, [&] { return stop_ || (open_ && generation_ != seen); });
-            if (stop_) return;
-            seen = generation_;
-            ++inside_;
-            lk.unlock();
-            work();
-            lk.lock();
-            if (--inside_ == 0) idle_.notify_one();
-        }
-    }
-    std::vector<std::thread> threads_;
-    std::mutex mu_;
-    std::condition_variable cv_, idle_;
-    std::vector<Job> jobs_;  // fixed while open_
-    std::atomic<size_t> next_{0};
-    size_t total_ = 0;
-    uint64_t generation_ = 0;
-    uint32_t inside_ = 0;
-    bool open_ = false, stop_ = false;
-};
-
 uint64_t build_bytes_estimate(uint32_t n, uint64_t nnz, uint32_t b) {
     const uint64_t W = (b + 63) / 64;
     const uint64_t work = n * (64 * W)                 // distance table
@@ -192,7 +101,7 @@ struct pll_server {
     hipStream_t build_stream = nullptr;
     hipEvent_t ev_ref = nullptr;  // device time origin of the results' dev_start / dev_end
     std::thread sched, builder;
-    CopyPool copies;  // the scheduler's
+    pll::CopyPool copies;  // the scheduler's
 
     // seconds from ev_ref to a completed timing event (-1 if unavailable)
     double dev_time(hipEvent_t e) const {
@@ -587,7 +496,7 @@ int pll_server_create(const pll_server_opts* opts, pll_server** out) {
         destroy_server(s);
         return PLL_ENOMEM;
     }
-    s->copies.start(kCopyHelpers);
+    s->copies.start(pll::kCopyHelpers);
     try {
         s->sched = std::thread([s] { s->run_sched(); });
         s->builder = std::thread([s] { s->run_builder(); });
