@@ -68,7 +68,7 @@ def consumed_entries(off, hubs_rank, rank, u, v):
 # profiles/hbm_traffic.txt is used only while their hash is unchanged.
 PKG_CSRC = os.path.join(os.path.dirname(os.path.abspath(__file__)), "paper_1906_12018_amd", "csrc")
 KERNEL_SOURCES = {
-    "k_check_push": ["pll_build.hip", "pll_phases.h", "pll_internal.h"],
+    "k_check_push": ["pll_build.hip", "pll_phases.h", "pll_stats.h", "pll_internal.h"],
     "k_query_lane": ["pll_query.hip", "pll_internal.h"],
     "k_query_group": ["pll_query.hip", "pll_internal.h"],
     "k_query_wave": ["pll_query.hip", "pll_internal.h"],
@@ -94,8 +94,8 @@ def sources_hash(kernel):
 
 def measured_traffic(kernel, workload):
     """HBM bytes (FETCH_SIZE + WRITE_SIZE, calibrated) per unit recorded for
-    this kernel and workload, or None when absent or taken from other
-    sources."""
+    this kernel and workload and the launches they were summed over, or None
+    when absent or taken from other sources."""
     try:
         lines = open(TRAFFIC_FILE).read().splitlines()
     except OSError:
@@ -108,7 +108,7 @@ def measured_traffic(kernel, workload):
         if kv.get("kernel") == kernel and kv.get("workload") == workload and kv.get("sources") == want:
             return {"bytes": float(kv["fetch_bytes"]) + float(kv["write_bytes"]),
                     "fetch_bytes": float(kv["fetch_bytes"]), "write_bytes": float(kv["write_bytes"]),
-                    "per": kv.get("per", "launch")}
+                    "per": kv.get("per", "launch"), "launches": int(kv.get("launches", 1))}
     return None
 
 
@@ -891,19 +891,22 @@ def build_mode(args):
         "query_latency_note": "p50/p99 over the timed launches of the whole configured pair batch (one request "
                               "of all pairs); per-request latencies of a mixed stream come from --mode serve",
         "build_phase_ms": {k: round(x, 3) for k, x in info["phase_ms"].items()},
+        "build_phase_note": "of the profiled builds, whose host launches every round; the timed builds queue small "
+                            "rounds ahead, in more and smaller launches",
         "profiled_build_s": float(np.median([i["build_ms"] for i in prof]) / 1e3),
         "rounds": info["rounds"], "batches": info["batches"], "candidates": info["candidates"],
         "parity": parity,
         "roofline": {"kernel": "k_check_push", "bound": "hbm", "achieved": check_gbs, "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": check_gbs / HBM_PEAK_GBS,
-                     "traffic": (tr_check["bytes"] / max(check_launches, 1)) if tr_check else None,
+                     "traffic": tr_check["bytes"] / tr_check["launches"] if tr_check else None,
                      "traffic_per_step": tr_check["bytes"] if tr_check else None,
                      "launches_per_step": check_launches,
                      "avg_launch_us": check_ms * 1e3 / max(check_launches, 1),
                      "bytes_per_launch": check_bytes / max(check_launches, 1),
                      "bytes_per_step": check_bytes,
                      "timing": "HIP events around every k_check_push launch on the build stream, over --steps "
-                               "profiled builds run right after the timed steps",
+                               "profiled builds run right after the timed steps; launches, bytes and traffic are "
+                               "of a profiled build too",
                      "cost_model": {"bytes_per_step": model_bytes, "GBs": model_gbs, "frac": model_gbs / HBM_PEAK_GBS,
                                     "note": "effective rate, which can exceed the HBM peak: every candidate "
                                             "check priced at 5 B per entry of L(v) although the scans stop early "
