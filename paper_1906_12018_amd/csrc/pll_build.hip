@@ -539,17 +539,6 @@ __global__ void __launch_bounds__(kBlock) k_batch_end4_2(BuildArgs A0, BuildArgs
         pll::phase_batch_end4(A1, side_exec(A1, nb0, gridDim.x - nb0), ib, s_pres[wv], s_dist[wv]);
 }
 
-template <int WM, bool BP>
-__global__ void __launch_bounds__(kBlock) k_check(BuildArgs A, uint32_t ib, uint32_t bs, uint32_t j, uint32_t p,
-                                                  uint32_t relaxed) {
-    PhaseStats st;
-    pll::phase_check<WM, BP>(A, grid_exec(A), ib, bs, j, p, relaxed != 0, st);
-    const unsigned long long v[7] = {st.cand, st.acc, st.read, st.table, st.cost_pos, st.cost_neg, st.bp};
-    const int which[7] = {PLL_ST_CAND,     PLL_ST_ACC,      PLL_ST_READ, PLL_ST_TABLE,
-                          PLL_ST_COST_POS, PLL_ST_COST_NEG, PLL_ST_BP};
-    block_add_stats<7>(A.ctr, v, which);
-}
-
 // The table a fused round's scans read.  kScanPlanes: the bit planes (rounds
 // j <= PLL_PLANES + 1 of a build that keeps them); kScanSmall: the byte table
 // with every prune threshold at most pll::kSmallT (j <= kSmallT), so the
@@ -565,7 +554,8 @@ __device__ inline void check_push_body(const BuildArgs& A, const pll::Exec& X, u
     if (PACK && !BP)
         pll::phase_check4<WM, SCAN == kScanSmall, SCAN == kScanPlanes>(A, X, ib, bs, j, relaxed != 0, st, nr);
     else
-        pll::phase_check<WM, BP, true, false, SCAN == kScanSmall && !BP, SCAN == kScanPlanes>(A, X, ib, bs, j, nr.rin, relaxed != 0, st, &nr);
+        pll::phase_check<WM, BP, true, SCAN == kScanSmall && !BP, SCAN == kScanPlanes>(A, X, ib, bs, j, nr.rin,
+                                                                                      relaxed != 0, st, &nr);
     const unsigned long long v[9] = {st.cand,     st.acc, st.read,  st.table,          st.cost_pos,
                                      st.cost_neg, st.bp,  st.edges + st.pulled, st.edges};
     const int which[9] = {PLL_ST_CAND,     PLL_ST_ACC, PLL_ST_READ,  PLL_ST_TABLE,      PLL_ST_COST_POS,
@@ -1227,28 +1217,8 @@ int device_error_status(uint32_t err) {
     return PLL_OK;
 }
 
-template <int WM>
-void launch_check(uint32_t blocks, hipStream_t s, const BuildArgs& A, uint32_t ib, uint32_t bs, uint32_t j,
-                  uint32_t p, uint32_t relaxed) {
-    if (A.bp_t)
-        k_check<WM, true><<<blocks, kBlock, 0, s>>>(A, ib, bs, j, p, relaxed);
-    else
-        k_check<WM, false><<<blocks, kBlock, 0, s>>>(A, ib, bs, j, p, relaxed);
-}
-
 // Kernels are instantiated for 1, 2, 4, 8 and 16 candidate words.
 inline int words_class(uint32_t W) { return W <= 1 ? 1 : W <= 2 ? 2 : W <= 4 ? 4 : W <= 8 ? 8 : 16; }
-
-void dispatch_check(uint32_t blocks, hipStream_t s, const BuildArgs& A, uint32_t ib, uint32_t bs, uint32_t j,
-                    uint32_t p, uint32_t relaxed) {
-    switch (words_class(A.W)) {
-        case 1: launch_check<1>(blocks, s, A, ib, bs, j, p, relaxed); break;
-        case 2: launch_check<2>(blocks, s, A, ib, bs, j, p, relaxed); break;
-        case 4: launch_check<4>(blocks, s, A, ib, bs, j, p, relaxed); break;
-        case 8: launch_check<8>(blocks, s, A, ib, bs, j, p, relaxed); break;
-        default: launch_check<16>(blocks, s, A, ib, bs, j, p, relaxed); break;
-    }
-}
 
 template <int WM>
 void launch_check_push(uint32_t blocks, hipStream_t s, const BuildArgs& A, uint32_t ib, uint32_t bs, uint32_t j,

@@ -173,12 +173,6 @@ __device__ inline uint64_t readlane64(uint64_t x, uint32_t l) {
     return ((uint64_t)hi << 32) | lo;
 }
 
-__device__ inline uint64_t wave_or64(uint64_t x) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) x |= __shfl_xor(x, o, 64);
-    return x;
-}
-
 __device__ inline uint32_t wave_sum32(uint32_t x) {
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) x += __shfl_xor(x, o, 64);
@@ -188,12 +182,6 @@ __device__ inline uint32_t wave_sum32(uint32_t x) {
 __device__ inline unsigned long long wave_sum64(unsigned long long x) {
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) x += __shfl_xor(x, o, 64);
-    return x;
-}
-
-__device__ inline uint32_t wave_min32(uint32_t x) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) x = min(x, (uint32_t)__shfl_xor(x, o, 64));
     return x;
 }
 

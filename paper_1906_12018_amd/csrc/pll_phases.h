@@ -118,28 +118,6 @@ __device__ inline uint64_t seg_le(const uint8_t* p, uint32_t tt) {
     return SMALLT ? le_mask64s(p, tt) : le_mask64(p, tt);
 }
 
-// le_mask64 over the 16-byte quarters selected by `need` (bit i: bytes
-// 16i .. 16i+15); the other quarters are neither loaded nor matched.
-__device__ inline uint64_t le_mask64_q(const uint8_t* p, uint32_t tt, uint32_t need) {
-    const uint4* q = reinterpret_cast<const uint4*>(p);
-    uint64_t m = 0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        if ((need >> i) & 1u) {
-            const uint4 v = q[i];
-            const uint32_t b = gather16(le4_flags(v.x, tt), le4_flags(v.y, tt), le4_flags(v.z, tt), le4_flags(v.w, tt));
-            m |= (uint64_t)b << (16 * i);
-        }
-    }
-    return m;
-}
-
-// Bit i set when quarter i (candidates 16i .. 16i+15) of a word has a bit.
-__device__ inline uint32_t quarters(uint64_t x) {
-    return (uint32_t)((x & 0xFFFFull) != 0) | ((uint32_t)((x & 0xFFFF0000ull) != 0) << 1) |
-           ((uint32_t)((x & 0xFFFF00000000ull) != 0) << 2) | ((uint32_t)((x >> 48) != 0) << 3);
-}
-
 // OR over the 64 lanes (DPP wave reduction, the whole wave active); the
 // result is wave-uniform.
 __device__ inline uint64_t wave_or64_u(uint64_t x) {
@@ -160,13 +138,9 @@ __device__ inline uint64_t wave_or64_u(uint64_t x) {
 // pass, so the scan stops after the first chunk that leaves no candidate
 // live (the top-ranked hubs of the first chunk prune most candidates of the
 // late rounds).  The next chunk's entries are loaded while this chunk's
-// segments are.  With QGATE only the 16-byte
-// quarters of a table segment that both hold entries (row mask) and have
-// live candidates are loaded; without it a segment is loaded whole when any
-// of its quarters qualifies (fewer, wider loads: measured faster on the large
-// single-graph builds, while the many-graph kernel, whose small graphs leave
-// table rows sparse, gains from the gating).
-template <int WM, bool QGATE = false, bool SMALLT = false>
+// segments are.  A segment is loaded whole when any of its 16-byte quarters
+// holds an entry (row mask): fewer, wider loads than with a gate per quarter.
+template <int WM, bool SMALLT = false>
 __device__ inline uint64_t prune_scan(const BuildArgs& A, uint64_t off, uint32_t len, uint32_t j, uint64_t cw,
                                       bool relaxed, uint32_t ib, PhaseStats& st) {
     const uint32_t lane = lane_id();
@@ -199,14 +173,7 @@ __device__ inline uint64_t prune_scan(const BuildArgs& A, uint64_t off, uint32_t
             const uint32_t w = (uint32_t)__builtin_ctzll(lw);
             lw &= lw - 1;
             uint64_t m = 0;
-            if (QGATE) {
-                const uint64_t live = readlane64(live_lane, w);
-                const uint32_t need = (uint32_t)(rm >> (4 * w)) & quarters(live);
-                if (need & 15u) {
-                    m = le_mask64_q(row + 64u * w, tt, need);
-                    st.table += __builtin_popcount(need & 15u);
-                }
-            } else if ((rm >> (4 * w)) & 15u) {
+            if ((rm >> (4 * w)) & 15u) {
                 m = seg_le<SMALLT>(row + 64u * w, tt);
                 st.table += 4;
             }
@@ -231,7 +198,7 @@ __device__ inline uint64_t prune_scan(const BuildArgs& A, uint64_t off, uint32_t
 // entries).  Candidate u_k is pruned when T[h][k] <= 1; the table loads,
 // which are the same as those of the label scan, and the lane reductions
 // are those of prune_scan.
-template <int WM, bool QGATE = false, bool SMALLT = false>
+template <int WM, bool SMALLT = false>
 __device__ inline uint64_t prune_scan_nbrs(const BuildArgs& A, uint32_t v, uint32_t lim, uint64_t cw,
                                            PhaseStats& st) {
     const uint32_t lane = lane_id();
@@ -252,14 +219,7 @@ __device__ inline uint64_t prune_scan_nbrs(const BuildArgs& A, uint32_t v, uint3
             const uint32_t w = (uint32_t)__builtin_ctzll(lw);
             lw &= lw - 1;
             uint64_t m = 0;
-            if (QGATE) {
-                const uint64_t live = readlane64(live_lane, w);
-                const uint32_t need = (uint32_t)(rm >> (4 * w)) & quarters(live);
-                if (need & 15u) {
-                    m = le_mask64_q(row + 64u * w, tt, need);
-                    st.table += __builtin_popcount(need & 15u);
-                }
-            } else if ((rm >> (4 * w)) & 15u) {
+            if ((rm >> (4 * w)) & 15u) {
                 m = seg_le<SMALLT>(row + 64u * w, tt);
                 st.table += 4;
             }
@@ -990,7 +950,7 @@ __device__ inline uint64_t prune_planes(const BuildArgs& A, uint64_t off, uint32
 // and nr->rclr, cleared here); active lists and heavy items use parity
 // nr->hout.
 
-template <int WM, bool BP = false, bool FUSE = false, bool QGATE = false, bool SMALLT = false, bool PLANES = false>
+template <int WM, bool BP = false, bool FUSE = false, bool SMALLT = false, bool PLANES = false>
 __device__ inline void phase_check(const BuildArgs& A, const Exec& X, uint32_t ib, uint32_t bs, uint32_t j, uint32_t p,
                                    bool relaxed, PhaseStats& st, const NextRound* nr = nullptr) {
     const uint32_t lane = lane_id();
@@ -1046,9 +1006,9 @@ __device__ inline void phase_check(const BuildArgs& A, const Exec& X, uint32_t i
                                             min(v, ib + bs), j, scan, st);
             }
         } else if (j == 2 && A.nbr_hubs && rend - rbeg < len)
-            pw = prune_scan_nbrs<WM, QGATE, SMALLT>(A, v, min(v, relaxed ? ib : ib + bs), scan, st);
+            pw = prune_scan_nbrs<WM, SMALLT>(A, v, min(v, relaxed ? ib : ib + bs), scan, st);
         else if (j > 1)
-            pw = prune_scan<WM, QGATE, SMALLT>(A, off, len, j, scan, relaxed, ib, st);
+            pw = prune_scan<WM, SMALLT>(A, off, len, j, scan, relaxed, ib, st);
         const uint64_t acc = lane < W ? (scan & ~pw) : 0ull;
         const uint32_t cnt = (uint32_t)__builtin_popcountll(acc);
         const uint32_t pos = wave_excl_scan32(cnt);
