@@ -140,10 +140,11 @@ typedef struct {
     uint64_t check_push_edges; /* CSR entries pushed by the check launches themselves (the rounds fuse the
                                   check of round j with the push of round j+1); the rest of edges_scanned is
                                   the first push of each batch, rows longer than 1,024 entries and the senders
-                                  of gathered rounds (rounds with at least 2n/5 receivers, graphs of 16,384
-                                  vertices or more) */
+                                  of gathered rounds (rounds with at least 2n/5 receivers, in a batch's first
+                                  round n/12; graphs of 16,384 vertices or more, batches that the host runs
+                                  round by round) */
     uint32_t query_lanes;     /* lanes per pair pll_query uses on this index now (the automatic choice resolved, for
-                                 calls of more than 32,768 pairs): 1, 4, 8, 16, 32 or 64 */
+                                 calls above the small ones; see pll_query): 1, 4, 8, 16, 32 or 64 */
 } pll_index_info;
 
 /* One graph of a batched build (all pointers are device pointers). */

@@ -51,14 +51,21 @@ constexpr uint32_t kHotRows = 4096;        // top-ranked table rows whose row ma
 // and n / 2.8: 136.5, 134.4 and 135.4; n / 16 and n / 24: 135.1 and 135.4.
 constexpr uint64_t kPullFrac1 = 12;
 constexpr uint32_t kPullMinN = 16384;      // smaller graphs always push (the pull's set-up outweighs it)
-// Receivers from which a fused round checks four per wave, and above which it
-// is not queued ahead of the host.  Packing from 2,048, 4,096, 8,192, 16,384
-// and 32,768 receivers: R-MAT 65,536 4.37, 4.33, 4.24, 4.27 and 4.49 ms,
-// BA-50000 15.2, 15.2, 14.8, 15.3 and 15.4, R-MAT-20 131.8, 130.3, 129.9,
-// 130.0 and 130.9.  Queueing up to 16,384, 32,768, 65,536 and 131,072:
-// R-MAT 200,000 15.6, 15.3, 15.0 and 15.7 ms, BA-50000 15.7, 15.6, 14.8 and
-// 14.8, R-MAT 65,536 4.41, 4.31, 4.24 and 4.23.
+// Receivers from which a fused round checks four per wave.  From 8,192 and
+// from 16,384 on, a percent or two (fastest of 125 builds each): R-MAT 65,536
+// 4.09 and 4.17 ms, 100,000 6.78 and 6.88, 200,000 14.77 and 14.99, BA-50000
+// (m = 4) 11.01 and 11.09, a torus of 64,000 61.4 and 61.9, R-MAT-20 129.3 and
+// 129.4; the other way round BA-20000 3.71 and 3.68, directed R-MAT 100,003
+// 11.2 and 11.0.  From 2,048, 4,096 and 32,768 on R-MAT 65,536 took 4.37, 4.33
+// and 4.49 ms, 4.24 so.
+// Rounds with bit-parallel roots never pack, but are launched with the same
+// grid, a wave per four receivers and some: a wave for each was slower (16
+// roots: BA-50000 17.38 against 17.05 ms, a torus of 13,824 15.8 against 15.1).
 constexpr uint64_t kPackMin = 8192;
+// Receivers above which a round is not queued ahead of the host.  Queueing up
+// to 16,384, 32,768, 65,536 and 131,072: R-MAT 200,000 15.6, 15.3, 15.0 and
+// 15.7 ms, BA-50000 15.7, 15.6, 14.8 and 14.8, R-MAT 65,536 4.41,
+// 4.31, 4.24 and 4.23.
 constexpr uint64_t kAheadRecv = 65536;
 constexpr uint32_t kAheadFirst = 16384;    // graphs below this many vertices queue their first batch too
 
@@ -566,7 +573,8 @@ __device__ inline void check_push_body(const BuildArgs& A, const pll::Exec& X, u
     if (ahead && ballot64(st.acc != 0) && lane_id() == 0) A.ctr->racc[j] = 1;
 }
 
-// at most 128 VGPRs, i.e. 4 waves per SIMD, like the unfused check
+// at most 128 VGPRs, i.e. 4 waves per SIMD (16 words: 120 on the planes, 98
+// packed; on the byte table 92 to 94, 5 waves)
 template <int WM, bool PACK, int SCAN>
 __global__ void __launch_bounds__(kBlock, 4) k_check_push(BuildArgs A, uint32_t ib, uint32_t bs, uint32_t j,
                                                           pll::NextRound nr, uint32_t relaxed, uint32_t ahead) {
@@ -576,10 +584,12 @@ __global__ void __launch_bounds__(kBlock, 4) k_check_push(BuildArgs A, uint32_t 
 
 // Directed graphs: both sides' fused rounds in one launch, blocks [0, nb0)
 // on the forward side and the rest on the backward side.  Bound as
-// k_check_push: small rounds by their chain of dependent loads (19 us each on
-// directed R-MAT 100,003), packed ones by table lines and atomics.  That
-// build's checks: 11.6 ms on the byte table, 7.2 on the planes with packing
-// (packing: 12.6 -> 12.3 ms of build).
+// k_check_push: small rounds by their chain of dependent loads (11 us each on
+// directed R-MAT 100,003), packed ones by table lines and atomics (87 us).
+// That build's checks: 11.6 ms on the byte table; on the planes 7.2 with the
+// host-launched rounds packed, 6.7 with the queued ones too (builds 24.5, 12.3
+// and 11.7 ms).  Two BuildArgs and two NextRounds take registers: the unpacked
+// form on the planes spills 12 (28 bytes a lane), the packed one (112) none.
 template <int WM, int SCAN, bool PACK = false>
 __global__ void __launch_bounds__(kBlock, 4) k_check_push2(BuildArgs A0, pll::NextRound nr0, BuildArgs A1,
                                                            pll::NextRound nr1, uint32_t ib, uint32_t bs, uint32_t j,
@@ -591,7 +601,7 @@ __global__ void __launch_bounds__(kBlock, 4) k_check_push2(BuildArgs A0, pll::Ne
         check_push_body<WM, false, PACK, SCAN>(A1, side_exec(A1, nb0, gridDim.x - nb0), ib, bs, j, nr1, 0, ahead);
 }
 
-// with bit-parallel labels
+// with bit-parallel labels (16 words on the planes: 5 registers spilled)
 template <int WM, int SCAN>
 __global__ void __launch_bounds__(kBlock, 4) k_check_push_bp(BuildArgs A, uint32_t ib, uint32_t bs, uint32_t j,
                                                           pll::NextRound nr, uint32_t relaxed, uint32_t ahead) {
@@ -1560,10 +1570,9 @@ int finalize_labels(DevAllocs& M, const BuildArgs& A, const uint32_t* rank, uint
     return PLL_OK;
 }
 
-// One complete build attempt with a given initial arena size.
 // Bit-parallel labels of up to t_req roots in rank space (Section 5.2):
 // choose the roots and their sets, then grow every root's levels together,
-// one push and one sibling launch per level, until a level is empty.
+// two gathers per level (k_bp_level), until a level is empty.
 struct BpState {
     uint32_t t = 0, used_count = 0;
     uint8_t* used = nullptr;
@@ -1701,6 +1710,7 @@ struct Ahead {
     }
 };
 
+// One complete build attempt with a given initial arena size.
 int build_attempt(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, const uint32_t* col, const uint32_t* order,
                   uint32_t b, uint32_t flags, uint64_t arena_hint, bool arena_fixed, uint32_t max_workgroups,
                   uint32_t bp_req, hipStream_t s, pll_index* idx, uint64_t* used_arena, const FixedWs* fw = nullptr) {
@@ -1792,9 +1802,10 @@ int build_attempt(uint32_t n, uint64_t nnz, const uint64_t* row_ptr, const uint3
     // round j's messages and receivers live in mbuf[j & 1] and rbuf[j & 1]
     uint64_t* mbuf[2] = {A.msgs, mbuf1};
     uint32_t* rbuf[2] = {A.recv, nullptr};
-    // pulled rounds: a round whose receivers number at least n / kPullFrac
-    // (the active vertices of the next round are among them) gathers at
-    // every vertex instead of scattering atomics along every active edge
+    // pulled rounds: a round whose receivers number at least 2n / 5, in a
+    // batch's first round n / kPullFrac1 (the active vertices of the next
+    // round are among them), gathers at every vertex instead of scattering
+    // atomics along every active edge
     uint2* pull_items = nullptr;
     uint32_t* pull_n = nullptr;
     uint64_t pull_cap = 0;

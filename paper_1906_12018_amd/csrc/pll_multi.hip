@@ -172,6 +172,10 @@ __device__ uint32_t gang_sync(GangCtl* gc, uint32_t G, uint32_t& k, DevCounters*
     return *s_flag;
 }
 
+// Bound by the rounds' dependent loads and the gang barriers.  Workgroups of
+// 1,024 threads leave 128 registers a lane, and the planes' check, the byte
+// table's, the recheck and both batch ends in one kernel spill 41 of them at
+// 16 words (160 bytes a lane).
 template <int WM>
 __global__ void __launch_bounds__(kMultiBlock) k_multi_build(const GraphJob* __restrict__ jobs,
                                                              const uint2* __restrict__ slots, uint32_t nslots,

@@ -1377,10 +1377,11 @@ __device__ inline uint64_t sum_le_mask64(const uint8_t* p, uint32_t dd, const ui
 // is left out of the words that have none.  Bound by the dependent segment
 // reads and the byte adds (VALU): the scan stops at the chunk that leaves no
 // candidate live and makes one pass per live word.  Weighted R-MAT-16: checks
-// 5.9 ms a build (34 us a round).  Unweighted R-MAT-16 with the recheck, batch
-// ends: one scan per distance 2.41 ms and 156 M table quarters (of the build),
-// one scan for all 3.90 ms and 674 M, with s_top 2.09 ms and 150 M; with the
-// relaxed check 3.36, 8.13 and 4.30 ms.
+// 5.8 ms a build (34 us a round), batch ends 3.4 ms before s_top, 3.0 with it.
+// Unweighted R-MAT-16 with the recheck, batch ends: one scan per distance 2.41
+// ms and 156 M table quarters (of the build), one scan for all 3.90 ms and
+// 674 M, with s_top 2.09 ms and 150 M; with the relaxed check 3.36, 8.13 and
+// 4.30 ms.
 template <int WM, bool RECHECK = false>
 __device__ inline uint64_t prune_scan_w(const BuildArgs& A, uint64_t off, uint32_t len, uint64_t cw,
                                         const uint4* s_thr, uint32_t ib, PhaseStats& st,
