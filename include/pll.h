@@ -71,7 +71,8 @@ extern "C" {
                                   to restore the canonical labels */
 #define PLL_FLAG_PERSISTENT 0x10u /* run the batches in one persistent launch with grid-wide barriers between
                                     phases, instead of one launch per phase and a host read-back per round */
-#define PLL_FLAG_PROFILE 0x8u  /* time each build phase with HIP events on `stream` (pll_index_info.phase_ms) */
+#define PLL_FLAG_PROFILE 0x8u  /* time each build phase with HIP events on `stream` (pll_index_info.phase_ms); the
+                                  host then launches every round (no batches queued ahead) */
 #define PLL_FLAG_PACK4 0x20u   /* testing: every fused round of an undirected unweighted build without bit-parallel
                                   roots checks four receivers per wave; otherwise only rounds expected to have at
                                   least 8,192 receivers do.  The labels are the same either way; directed,
